@@ -2,10 +2,19 @@
 //
 // Same contract and epilogues as gemm.hip, specialised for the throughput
 // path:
-//   * 256 x 256 output tile per workgroup, 8 waves (two per SIMD, so one
-//     wave's LDS waits are covered by the other's matrix-core work) of
-//     128 x 64, reduction stages of 64 double-buffered in LDS (132 KB): a
-//     DMA row segment is one full 128-byte line;
+//   * large products: 256 x 256 output tile per workgroup, 8 waves (two per
+//     SIMD, so one wave's LDS waits are covered by the other's matrix-core
+//     work) of 128 x 64, reduction stages of 64 double-buffered in LDS
+//     (132 KB): a DMA row segment is one full 128-byte line;
+//   * products whose 256 x 256 tiles would leave most of the 256 CUs idle (a
+//     few hundred tokens, narrow models) run on 128 x 256 or 64 x 128 tiles
+//     with three stages in LDS, and cut the reduction into slices where the
+//     tiles are still too few; row counts past whole rounds of large tiles put
+//     the remaining rows on their own tile shape (plan_rows).  Hidden 4096,
+//     FFN 16384, against 256 x 256 tiles for everything: 37 tokens QKV 83 ->
+//     28 us, output projection 80 -> 14 us; 509 tokens 87 -> 59 and 87 -> 33
+//     us; 2048 tokens FFN-down 319 -> 236 us; hidden 1280, 1458 tokens output
+//     projection 34 -> 12 us;
 //   * operands go from HBM/L2 straight into LDS with buffer loads in LDS-DMA
 //     mode (no VGPR staging).  Buffer resources bound each operand, so rows
 //     or reduction indices past the end read as zero (ragged token tails);
@@ -33,12 +42,34 @@
 namespace flglm {
 namespace {
 
-constexpr int kBM = 256, kBN = 256, kBK = 64, kStages = 2, kThr = 512, kWaves = 8;
-// waves: 2 along M x 4 along N, each 128 x 64 (8 x 4 tiles of 16 x 16)
-constexpr int kWTM = 8, kWTN = 4;
-// LDS region of one operand tile: the MN-contiguous layout pads each 1 KB
-// DMA block to 1056 bytes (33 KB in all)
-constexpr int kRegionElems = 16896, kMBlock = 528, kMCol = 8 * kMBlock, kKBlock = 520;
+constexpr int kBK = 64;
+// LDS strides of the operand tiles' 1 KB DMA blocks (1056 bytes for the
+// MN-contiguous layout, 1040 for the K-contiguous one)
+constexpr int kMBlock = 528, kMCol = 8 * kMBlock, kKBlock = 520;
+
+// Output tile of one workgroup: BM x BN by WM x WN waves of (16 kWTM) x
+// (16 kWTN), a ring of S operand slots of a 64-wide reduction stage in LDS.
+template <int BM, int BN, int WM, int WN, int S, int OCC>
+struct Tile {
+  static constexpr int kBM = BM, kBN = BN, kWM = WM, kWN = WN, kWaves = WM * WN, kThr = 64 * kWaves;
+  static constexpr int kStages = S;
+  static constexpr int kOcc = OCC;  // workgroups per CU the LDS holds
+  static constexpr int kWTM = BM / (16 * WM), kWTN = BN / (16 * WN);
+  static constexpr int kRegA = BM * 66, kRegB = BN * 66;  // elements, room for either layout's padding
+  static constexpr int kSlot = kRegA + kRegB;
+  static constexpr bool kBig = BM == 256;
+  // epilogue staging: the whole tile as fp32 where it fits, else one wave row at a time
+  static constexpr int kPasses = BM * BN * 4 <= S * kSlot * 2 ? 1 : WM;
+  static_assert(BM / kPasses * BN * 4 <= S * kSlot * 2, "staging");
+};
+using Tile256 = Tile<256, 256, 2, 4, 2, 1>;   // 132 KB
+using Tile128 = Tile<128, 256, 2, 4, 3, 1>;   // 149 KB
+using Tile64 = Tile<64, 128, 1, 4, 3, 2>;     // 74 KB
+// weight gradients: more workgroups per CU, so that one's fp32 read-modify-
+// write epilogue runs beside the others' reductions
+using Tile128w = Tile<128, 128, 2, 2, 2, 2>;  // 66 KB
+using Tile64w = Tile<64, 128, 1, 4, 2, 3>;    // 50 KB
+constexpr int EPI_PART = 7;  // fp32 partial sums of one reduction slice
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 #define LDS_AS __attribute__((address_space(3)))
 
@@ -55,12 +86,11 @@ struct G2Args {
   long ldc2;
   const bf16* Z;
   long ldz;
-  // Split reduction for the last, partial round of tiles: the final `tail`
-  // tiles are cut into `splits` reduction slices whose fp32 partial
-  // accumulators go to `part`; a second launch (fixup = 1) sums them in a
-  // fixed order and runs the epilogue.
+  // Split reduction: every tile's reduction is cut into `slices` slices whose
+  // fp32 sums go to `part` ([slices][M][N], EPI_PART); gemm_slices_kernel adds
+  // them in slice order and runs the epilogue.
   float* part;
-  int tail, splits, fixup;
+  int slices;
   int nb;  // rows of B that exist (see GemmDesc::b_rows)
   float res_scale;
   // EPI_GELU_BWD: per 256-row tile, the column sums of the stored C (fp32
@@ -111,11 +141,11 @@ __device__ __forceinline__ uint32_t k_dst(int inst) { return (uint32_t)inst * (2
 __device__ __forceinline__ uint32_t m_dst(int inst) { return (uint32_t)((inst >> 3) * kMCol + (inst & 7) * kMBlock) * 2u; }
 
 // Per-lane fragment bases (element offsets inside one operand tile).
-// K-contiguous: fragment j of a wave (rows row0 + 16 j, row0 a multiple of
-// 64), reduction half c: lane (fr, fg) reads chunk fg + 4 c of row
+// K-contiguous: fragment j of a wave (rows row0 + 16 j; a wave's fragments
+// stay inside a 64-row group or start at one), reduction half c: lane (fr, fg) reads chunk fg + 4 c of row
 // row0 + 16 j + fr.
 __device__ __forceinline__ int frag_k_base(int row0, int fr, int fg) {
-  return (fr & 7) * kKBlock + 64 * (fr >> 3) + 8 * fg + 8 * kKBlock * (row0 >> 6);
+  return (fr & 7) * kKBlock + 64 * (fr >> 3) + 8 * fg + 8 * kKBlock * (row0 >> 6) + 128 * ((row0 >> 4) & 3);
 }
 // MN-contiguous: fragment j (columns col0 + 16 j), reduction half c: lane s
 // of a 16-lane group points at k-row 8 g + s / 4 (block s / 4, row
@@ -123,7 +153,8 @@ __device__ __forceinline__ int frag_k_base(int row0, int fr, int fg) {
 // col0 / 64 + j / 4; the second read is k + 4 (row + 2), half c = k + 32
 // (block + 4).
 __device__ __forceinline__ int frag_m_base(int col0, int fr, int fg) {
-  return (col0 >> 6) * kMCol + (fr >> 2) * kMBlock + ((fg & 1) + 4 * (fg >> 1)) * 64 + 4 * (fr & 3);
+  return (col0 >> 6) * kMCol + 16 * ((col0 >> 4) & 3) + (fr >> 2) * kMBlock + ((fg & 1) + 4 * (fg >> 1)) * 64 +
+         4 * (fr & 3);
 }
 __device__ __forceinline__ bf16x8 frag_k(const bf16* tile, int base, int c, int j) {
   return __builtin_bit_cast(bf16x8, ld16(tile + base + 8 * kKBlock * (j >> 2) + 128 * (j & 3) + 32 * c));
@@ -152,26 +183,29 @@ __device__ __forceinline__ float gelu2_grad(float z) {
   return s + 2.0f * c * z * s * (1.0f - s) * (1.0f + 3.0f * a * z * z);
 }
 
-// Tile order: workgroup wg runs on XCD wg % 8, and each XCD takes a contiguous
-// range of tile ids, walked column by column inside bands of kGroupM tile rows.
-// With 4-row bands the 32 tiles one XCD holds at a time span 4 row panels of A
-// and 8 column panels of B; for the token-major products (forward, dgrad)
-// that is 1.5-3 % faster than 8-row bands (16 rows: 5-18 % slower than 8).
-// The weight gradient (both operands MN-contiguous) measures 0.6 % faster
-// with 8.
-template <int kGroupM>
-__device__ __forceinline__ void tile_coords2(int wg, int nwg, int tiles_m, int tiles_n, int& tm, int& tn) {
+// Work order: workgroup wg runs on XCD wg % 8, and each XCD takes a contiguous
+// range of work items.  Items walk bands of kBand tile rows column by column
+// (kAlongN: bands of tile columns row by row); a tile's reduction slices lie
+// between the band's rows and the next column, so the workgroups of an XCD
+// that run together read the same reduction range of the same rows.
+template <int kBand, bool kAlongN>
+__device__ __forceinline__ void work_coords(int wg, int nwg, int tiles_m, int tiles_n, int slices, int& tm, int& tn,
+                                            int& slice) {
   constexpr int kXcd = 8;
   const int q = nwg / kXcd, r = nwg % kXcd;
   const int x = wg % kXcd, j = wg / kXcd;
   const int id = (x < r) ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
-  const int per_group = kGroupM * tiles_n;
-  const int group = id / per_group;
-  const int first_m = group * kGroupM;
-  const int gsize = min(tiles_m - first_m, kGroupM);
-  const int in_group = id % per_group;
-  tm = first_m + in_group % gsize;
-  tn = in_group / gsize;
+  const int ta = kAlongN ? tiles_n : tiles_m, tb = kAlongN ? tiles_m : tiles_n;
+  const int per_band = kBand * tb * slices;
+  const int band = id / per_band;
+  const int first = band * kBand;
+  const int size = min(ta - first, kBand);
+  const int in_band = id % per_band;
+  const int a = first + in_band % size, rest = in_band / size;
+  slice = rest % slices;
+  const int b = rest / slices;
+  tm = kAlongN ? b : a;
+  tn = kAlongN ? a : b;
 }
 
 // Bare workgroup barrier: a fence would also wait for DMA stages in flight.
@@ -198,14 +232,17 @@ __device__ __forceinline__ void wg_barrier() {
 // both hit 16 distinct bank groups.
 __device__ __forceinline__ int stg_swz(int r, int c) { return c ^ (r & 15) ^ ((c >> 4) & 1); }
 
-template <int EPI, int BATCH>
-__device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc)[kWTN][kWTM], float* stg, int tm,
-                                              int m0, int n0, int tid) {
+template <class TL, int EPI, int STEPS>
+__device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc)[TL::kWTN][TL::kWTM], float* stg,
+                                              int tm, int m0, int n0, int tid) {
+  constexpr int kWaves = TL::kWaves, kWTM = TL::kWTM, kWTN = TL::kWTN, kBN = TL::kBN, NP = TL::kPasses;
+  constexpr int kLpr = kBN / 8, kRpi = 64 / kLpr;  // lanes per row, rows per wave instruction
+  constexpr int kRows = TL::kBM / NP, kSteps = kRows / (kWaves * kRpi);
   asm volatile("" : "+v"(tid));  // keeps the epilogue's per-lane values out of the main loop's live range
   const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
+  const int wm = wave % TL::kWM, wn = wave / TL::kWM;
   const int fr = lane & 15, fg = lane >> 4;
-  const int sh = lane >> 5, cg = lane & 31;
+  const int sh = lane / kLpr, cg = lane % kLpr;
   const int n = n0 + 8 * cg;
   float bias[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   // EPI_GELU_BWD with colsum: this lane's eight columns over its rows (the
@@ -218,31 +255,31 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
     for (int e = 0; e < 8; ++e) bias[e] = b.get(e);
   }
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int mbase = m0 + half * 128 + wave;
-    if (wm == half) {
+  for (int half = 0; half < NP; ++half) {
+    const int mbase = m0 + half * kRows + wave;
+    if (NP == 1 || wm == half) {
 #pragma unroll
       for (int j = 0; j < kWTM; ++j) {
-        const int r = 16 * j + fr;
+        const int r = (NP == 1 ? wm * 16 * kWTM : 0) + 16 * j + fr;
 #pragma unroll
         for (int i = 0; i < kWTN; ++i) {
-          const int c = (wn * 64 + 16 * i + 4 * fg) >> 2;
-          st16(stg + r * 256 + (stg_swz(r, c) << 2), __builtin_bit_cast(u32x4, acc[i][j]));
+          const int c = (wn * 16 * kWTN + 16 * i + 4 * fg) >> 2;
+          st16(stg + r * kBN + (stg_swz(r, c) << 2), __builtin_bit_cast(u32x4, acc[i][j]));
         }
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     wg_barrier();
-    // Rows wave + 8 q, q = 2 t + sh (t = 0..7), in batches of row pairs
-    // whose global loads are issued together before their first use.
-    constexpr int kB = BATCH / 2 > 0 ? BATCH / 2 : 1;
+    // Rows wave + kWaves q, q = kRpi t + sh (t = 0 .. kSteps - 1), in batches
+    // of steps whose global loads are issued together before their first use.
+    constexpr int kB = STEPS < kSteps ? STEPS : kSteps;
 #pragma unroll
-    for (int t0 = 0; t0 < 8; t0 += kB) {
+    for (int t0 = 0; t0 < kSteps; t0 += kB) {
       Vec8<bf16> ext[kB];
       Vec8<float> cacc[kB];
 #pragma unroll
       for (int u = 0; u < kB; ++u) {
-        const long m = mbase + (2 * (t0 + u) + sh) * kWaves;
+        const long m = mbase + (kRpi * (t0 + u) + sh) * kWaves;
         if (m < p.M) {
           if constexpr (EPI == EPI_BIAS_RES || EPI == EPI_RES) ext[u].load(p.R + m * p.ldr + n);
           if constexpr (EPI == EPI_GELU_BWD) ext[u].load(p.Z + m * p.ldz + n);
@@ -251,19 +288,23 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
       }
 #pragma unroll
       for (int u = 0; u < kB; ++u) {
-        const int q = 2 * (t0 + u) + sh;
+        const int q = kRpi * (t0 + u) + sh;
         const int r = wave + q * kWaves;
         const long m = mbase + q * kWaves;
         if (m >= p.M) break;
-        const u32x4 raw0 = ld16(stg + r * 256 + (stg_swz(r, 2 * cg) << 2));
-        const u32x4 raw1 = ld16(stg + r * 256 + (stg_swz(r, 2 * cg + 1) << 2));
+        const u32x4 raw0 = ld16(stg + r * kBN + (stg_swz(r, 2 * cg) << 2));
+        const u32x4 raw1 = ld16(stg + r * kBN + (stg_swz(r, 2 * cg + 1) << 2));
         float v[8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           v[e] = __uint_as_float(raw0[e]) + bias[e];
           v[4 + e] = __uint_as_float(raw1[e]) + bias[4 + e];
         }
-        if constexpr (EPI == EPI_ACC_F32) {
+        if constexpr (EPI == EPI_PART) {
+          Vec8<float> o;
+          o.set(v);
+          o.store(static_cast<float*>(p.C) + m * p.ldc + n);
+        } else if constexpr (EPI == EPI_ACC_F32) {
           float o[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = cacc[u].get(e) + v[e];
@@ -300,12 +341,12 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     wg_barrier();
   }
-  if constexpr (EPI == EPI_GELU_BWD) {
+  if constexpr (EPI == EPI_GELU_BWD && TL::kBig) {
     if (p.colsum) {
       // the sixteen half-waves' partial column sums, added in (wave, half)
       // order (the operand tiles are free: every wave passed the barrier)
       float* cs = stg;
-      float* mine = cs + (wave * 2 + sh) * kBN + 8 * cg;
+      float* mine = cs + (wave * kRpi + sh) * kBN + 8 * cg;
       st16(mine, __builtin_bit_cast(u32x4, f32x4{csum[0], csum[1], csum[2], csum[3]}));
       st16(mine + 4, __builtin_bit_cast(u32x4, f32x4{csum[4], csum[5], csum[6], csum[7]}));
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -313,7 +354,7 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
       if (tid < kBN) {
         float t = 0.f;
 #pragma unroll
-        for (int w2 = 0; w2 < 2 * kWaves; ++w2) t += cs[w2 * kBN + tid];
+        for (int w2 = 0; w2 < kRpi * kWaves; ++w2) t += cs[w2 * kBN + tid];
         p.colsum[(long)tm * p.N + n0 + tid] = t;
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -322,48 +363,48 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
   }
 }
 
-// Rows of the epilogue whose global reads are issued together: 16 for the
-// residual epilogues (a half's whole share: 6 % faster on the 41447 x 4096 x
-// 4096 output projection than 8), 8 elsewhere (16 measured no faster), 4 for
-// the fp32 accumulator.
+// Row steps of the epilogue whose global reads are issued together: 8 for the
+// residual epilogues (a 128-row half's whole share: 6 % faster on the 41447 x
+// 4096 x 4096 output projection than 4), 4 elsewhere (8 measured no faster),
+// 2 for the fp32 accumulator.
 template <int EPI>
-constexpr int epi_batch() { return (EPI == EPI_BIAS_RES || EPI == EPI_RES) ? 16 : EPI == EPI_ACC_F32 ? 4 : 8; }
+constexpr int epi_steps() { return (EPI == EPI_BIAS_RES || EPI == EPI_RES) ? 8 : EPI == EPI_ACC_F32 ? 2 : 4; }
 
-template <bool AK, bool BKc, int EPI, int BATCH = epi_batch<EPI>()>
-__global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
-  __shared__ __attribute__((aligned(1024))) bf16 smem[kStages][2][kRegionElems];  // [stage][A/B]
+template <bool AK, bool BKc, int EPI, class TL>
+__global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16_kernel(G2Args p) {
+  constexpr int kBM = TL::kBM, kBN = TL::kBN, kThr = TL::kThr, kWaves = TL::kWaves;
+  constexpr int kWTM = TL::kWTM, kWTN = TL::kWTN, kSlot = TL::kSlot, kStages = TL::kStages;
+  __shared__ __attribute__((aligned(1024))) bf16 smem[kStages * kSlot];  // [slot][A | B]
 
   const int tiles_m = (p.M + kBM - 1) / kBM, tiles_n = p.N / kBN;
   const int ntiles = tiles_m * tiles_n;
   const int nk = (p.K + kBK - 1) / kBK;
-  const int full = ntiles - p.tail;
-  const int nwork = p.fixup ? p.tail : full + p.tail * p.splits;
-  // Persistent: one workgroup per CU walks the work items (whole tiles, then
-  // the reduction slices of the tail tiles); a tile's epilogue stores drain
-  // while the next item's first stages load.
+  const int nwork = ntiles * p.slices;
+  // Persistent where the grid is smaller than the work (256 x 256 tiles: one
+  // workgroup per CU); a tile's epilogue stores drain while the next item's
+  // first stages load.
   for (int wi = blockIdx.x; wi < nwork; wi += gridDim.x) {
-  int t, kt0 = 0, kt1 = nk, slice = -1;
-  if (p.fixup) {
-    t = full + wi;
-  } else if (wi < full) {
-    t = wi;
-  } else {
-    slice = wi - full;
-    t = full + slice / p.splits;
-    const int per = (nk + p.splits - 1) / p.splits;
-    kt0 = min(nk, (slice % p.splits) * per);
-    kt1 = min(nk, kt0 + per);
-  }
+  int tm, tn, slice;
+  // Bands of 4 tile rows for the forward and dgrad products on 256 x 256
+  // tiles (the 32 tiles one XCD holds span 4 row panels of A and 8 column
+  // panels of B): 1.5-3 % faster than 8 (16: 5-18 % slower than 8).  Their
+  // weight gradients are 0.6 % faster with 8.  Weight gradients on smaller
+  // tiles walk bands of tile columns: the C rows that run together are then
+  // read and written as 4 KB runs (4096 x 16384 x 256 tokens: 116 us against
+  // 159 in bands of tile rows).
+  constexpr bool kWgrad = !AK && !BKc;
+  work_coords<TL::kBig && !kWgrad ? 4 : 8, kWgrad && !TL::kBig>(wi, nwork, tiles_m, tiles_n, p.slices, tm, tn, slice);
+  const int kt0 = p.slices == 1 ? 0 : (int)((long)nk * slice / p.slices);
+  const int kt1 = p.slices == 1 ? nk : (int)((long)nk * (slice + 1) / p.slices);
   // Per-lane values are rederived in every tile (the opaque copy keeps the
   // compiler from hoisting them out of the tile loop, where they would stay
   // live across the whole body and spill).
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;  // wave tile: rows wm*128.., columns wn*64..
+  // wave tile: rows wm * 16 kWTM .., columns wn * 16 kWTN ..
+  const int wm = wave % TL::kWM, wn = wave / TL::kWM;
   const int fr = lane & 15, fg = lane >> 4;
-  int tm, tn;
-  tile_coords2<(AK || BKc) ? 4 : 8>(t, ntiles, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * kBM, n0 = tn * kBN;
 
   // Resources: K-contiguous -> base at the tile's first row, bound = its
@@ -384,9 +425,10 @@ __global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
   } else {
     rb = buf_rsrc(p.B + n0, (uint32_t)(((long)p.nb * p.ldb - n0) * 2));
   }
-  // DMA bookkeeping.  Each stage takes 32 DMA instructions per operand.
-  // Forward and dgrad: every wave issues 4 per operand, instruction i of
-  // wave w being instruction 8 i + w of the tile.  Weight gradient: waves 0-3
+  // DMA bookkeeping.  Each stage takes one DMA instruction per 8 rows of an
+  // operand (32 for a 256-row tile).  Forward and dgrad: every wave issues an
+  // equal share, instruction i of wave w being instruction kWaves i + w of
+  // the tile.  Weight gradient on 256 x 256 tiles: waves 0-3
   // issue 8 per operand (instruction 4 i + w) and waves 4-7 none.  Waves w
   // and w + 4 share a SIMD, so each SIMD then pairs a loading wave with one
   // that only computes: a load stalled on the texture unit's address queue
@@ -396,43 +438,45 @@ __global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
   // the instruction index for these wave numbers, so a wave adds its own
   // offset once.  The per-lane source offsets are fixed up to the stage's
   // reduction offset, added per stage.
-  constexpr bool kLoaders = !AK && !BKc;
-  constexpr int kDmaPer = kLoaders ? 8 : 4;          // per operand per stage per loading wave
-  constexpr int kDmaStride = 32 / kDmaPer;           // tile instruction stride between a wave's DMAs
+  constexpr bool kLoaders = TL::kBig && kWgrad;
+  constexpr int kDmaStride = kLoaders ? 4 : kWaves;  // tile instruction stride between a wave's DMAs
+  constexpr int kDmaA = kBM / 8 / kDmaStride, kDmaB = kBN / 8 / kDmaStride;  // per stage per loading wave
+  constexpr int kDma = kDmaA + kDmaB;
   const bool loader = !kLoaders || wave < 4;
   const int wq = kLoaders ? (wave & 3) : wave;
-  const uint32_t lds0 = FL_LDS_ADDR(&smem[0][0][0]);
+  const uint32_t lds0 = FL_LDS_ADDR(&smem[0]);
   const uint32_t lds_a = __builtin_amdgcn_readfirstlane(lds0 + (AK ? k_dst(wq) : m_dst(wq)));
   const uint32_t lds_b =
-      __builtin_amdgcn_readfirstlane(lds0 + kRegionElems * 2 + (BKc ? k_dst(wq) : m_dst(wq)));
-  uint32_t voa[kDmaPer], vob[kDmaPer];
+      __builtin_amdgcn_readfirstlane(lds0 + TL::kRegA * 2 + (BKc ? k_dst(wq) : m_dst(wq)));
+  uint32_t voa[kDmaA], vob[kDmaB];
 #pragma unroll
-  for (int i = 0; i < kDmaPer; ++i) {
+  for (int i = 0; i < kDmaA; ++i)
     voa[i] = AK ? k_src(p.lda, i * kDmaStride + wq, lane) : m_src(p.lda, i * kDmaStride + wq, lane);
+#pragma unroll
+  for (int i = 0; i < kDmaB; ++i)
     vob[i] = BKc ? k_src(p.ldb, i * kDmaStride + wq, lane) : m_src(p.ldb, i * kDmaStride + wq, lane);
-  }
   // byte offset of reduction index k0 along each operand
   auto kstep_a = [&](int k0) { return AK ? (uint32_t)k0 * 2u : (uint32_t)((long)k0 * p.lda * 2); };
   auto kstep_b = [&](int k0) { return BKc ? (uint32_t)k0 * 2u : (uint32_t)((long)k0 * p.ldb * 2); };
-  // DMA instruction g (A 0 .. kDmaPer-1, then B) of this wave for stage kt
-  auto dma_one = [&](int kt, int g) {
-    const uint32_t slot_off = (uint32_t)(kt & (kStages - 1)) * (2 * kRegionElems * 2);
-    if (g < kDmaPer) {
+  // DMA instruction g (A 0 .. kDmaA-1, then B) of this wave for stage kt, into slot
+  auto dma_one = [&](int kt, int slot, int g) {
+    const uint32_t slot_off = (uint32_t)slot * (kSlot * 2);
+    if (g < kDmaA) {
       const int o = kDmaStride * g;
       dma16(ra, lds_a + slot_off + (AK ? k_dst(o) : m_dst(o)), voa[g] + kstep_a(kt * kBK));
     } else {
-      const int o = kDmaStride * (g - kDmaPer);
-      dma16(rb, lds_b + slot_off + (BKc ? k_dst(o) : m_dst(o)), vob[g - kDmaPer] + kstep_b(kt * kBK));
+      const int o = kDmaStride * (g - kDmaA);
+      dma16(rb, lds_b + slot_off + (BKc ? k_dst(o) : m_dst(o)), vob[g - kDmaA] + kstep_b(kt * kBK));
     }
   };
-  auto issue = [&](int kt) {
+  auto issue = [&](int kt, int slot) {
     if (loader) {
 #pragma unroll
-      for (int g = 0; g < 2 * kDmaPer; ++g) dma_one(kt, g);
+      for (int g = 0; g < kDma; ++g) dma_one(kt, slot, g);
     }
   };
-  const int abase = AK ? frag_k_base(wm * 128, fr, fg) : frag_m_base(wm * 128, fr, fg);
-  const int bbase = BKc ? frag_k_base(wn * 64, fr, fg) : frag_m_base(wn * 64, fr, fg);
+  const int abase = AK ? frag_k_base(wm * 16 * kWTM, fr, fg) : frag_m_base(wm * 16 * kWTM, fr, fg);
+  const int bbase = BKc ? frag_k_base(wn * 16 * kWTN, fr, fg) : frag_m_base(wn * 16 * kWTN, fr, fg);
 
   f32x4 acc[kWTN][kWTM];
 #pragma unroll
@@ -441,11 +485,11 @@ __global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
     for (int j = 0; j < kWTM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   auto rd_a = [&](int slot, int c, int j) {
-    const bf16* as = smem[slot][0];
+    const bf16* as = smem + slot * kSlot;
     return AK ? frag_k(as, abase, c, j) : frag_m(as, abase, c, j);
   };
   auto rd_b = [&](int slot, int c, int i) {
-    const bf16* bs = smem[slot][1];
+    const bf16* bs = smem + slot * kSlot + TL::kRegA;
     return BKc ? frag_k(bs, bbase, c, i) : frag_m(bs, bbase, c, i);
   };
   // fragments of reduction half c of the stage in slot `slot`
@@ -468,33 +512,21 @@ __global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
     asm volatile("" ::: "memory");
   };
 
-  if (p.fixup) {
-    // sum the tile's reduction slices in slice order (deterministic)
-    const float* src = p.part + (long)(t - full) * p.splits * (kWTN * kWTM * kThr * 4);
-    for (int c = 0; c < p.splits; ++c) {
+  if (kt1 > kt0) {
+  // Stage kt lives in slot (kt - kt0) % kStages.  Prologue: kStages stages in
+  // flight; once the first is visible, read its first half.
 #pragma unroll
-      for (int i = 0; i < kWTN; ++i)
-#pragma unroll
-        for (int j = 0; j < kWTM; ++j)
-          acc[i][j] += __builtin_bit_cast(f32x4, ld16(src + ((long)(c * kWTN * kWTM + i * kWTM + j) * kThr + tid) * 4));
-    }
-  } else if (kt1 > kt0) {
-  // Stage kt lives in slot kt % 2.  Prologue: stages 0 and 1 in flight; once
-  // stage 0 is visible, read its first half.
-  issue(kt0);
-  if (kt1 - kt0 > 1) {
-    issue(kt0 + 1);
-    // the older stage's loads done: at most one stage (2 kDmaPer) in flight
-    if constexpr (kLoaders)
-      asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-  } else {
+  for (int u = 0; u < kStages; ++u)
+    if (u == 0 || kt0 + u < kt1) issue(kt0 + u, u);
+  // the first stage's loads done: the younger ones may stay in flight
+  if (kt1 - kt0 >= kStages)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 1) * kDma) : "memory");
+  else
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
   barrier();
   bf16x8 fa0[kWTM], fb0[kWTN], fa1[kWTM], fb1[kWTN];
-  load_frags(kt0 & 1, 0, fa0, fb0);
+  load_frags(0, 0, fa0, fb0);
+  int slot = 0;
   // Main loop, one stage per iteration, in two halves of 32 reductions.  The
   // issue order is fixed by scheduling barriers: each group of four matrix
   // instructions (one A fragment against the four B fragments) is preceded
@@ -505,7 +537,7 @@ __global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
   // The last stage is peeled so that every path through the body passes the
   // barrier (the compiler then never waits for next-half reads early).
   for (int kt = kt0; kt < kt1 - 1; ++kt) {
-    const int slot = kt & 1;
+    const int next = kStages == 2 ? slot ^ 1 : slot + 1 == kStages ? 0 : slot + 1;
 #pragma unroll
     for (int j = 0; j < kWTM; ++j) {
       fa1[j] = rd_a(slot, 1, j);
@@ -517,20 +549,24 @@ __global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
       __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // stage kt+1 landed (own loads) and every wave has finished reading
-    // slot kt: refill it with stage kt+2, read stage kt+1's first half
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // stage kt+1 landed (own loads; the stages behind it may stay in flight)
+    // and every wave has finished reading slot kt: refill it with stage kt +
+    // kStages, read stage kt+1's first half
+    if (kStages > 2 && kt + kStages <= kt1)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 2) * kDma) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     barrier();
-    const bool more = kt + 2 < kt1;
+    const bool more = kt + kStages < kt1;
 #pragma unroll
     for (int j = 0; j < kWTM; ++j) {
       if (more && loader) {
-        dma_one(kt + 2, (kDmaPer / 4) * j);
-        if constexpr (kLoaders) dma_one(kt + 2, 2 * j + 1);
+#pragma unroll
+        for (int g = j * kDma / kWTM; g < (j + 1) * kDma / kWTM; ++g) dma_one(kt + kStages, slot, g);
       }
-      fa0[j] = rd_a(slot ^ 1, 0, j);
-      if (j < kWTN) fb0[j] = rd_b(slot ^ 1, 0, j);
+      fa0[j] = rd_a(next, 0, j);
+      if (j < kWTN) fb0[j] = rd_b(next, 0, j);
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -538,33 +574,90 @@ __global__ void __launch_bounds__(kThr) gemm_bf16_kernel(G2Args p) {
       __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
     }
+    slot = next;
   }
-  load_frags((kt1 - 1) & 1, 1, fa1, fb1);
+  load_frags(slot, 1, fa1, fb1);
   mma_all(fa0, fb0);
   mma_all(fa1, fb1);
   }
-  if (slice >= 0) {
-    // a reduction slice of a tail tile: store the partial accumulators
-    // ([slice][i][j][thread][4], coalesced) and move on
-    float* dst = p.part + (long)slice * (kWTN * kWTM * kThr * 4);
-#pragma unroll
-    for (int i = 0; i < kWTN; ++i)
-#pragma unroll
-      for (int j = 0; j < kWTM; ++j)
-        st16(dst + ((long)(i * kWTM + j) * kThr + tid) * 4, __builtin_bit_cast(u32x4, acc[i][j]));
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    barrier();  // every wave is done with the operand tiles before the next item's loads
-    continue;
-  }
-
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   barrier();  // every wave is done with the operand tiles
-  tile_epilogue<EPI, BATCH>(p, acc, reinterpret_cast<float*>(&smem[0][0][0]), tm, m0, n0, tid);
+  if constexpr (EPI == EPI_PART) {
+    G2Args q = p;
+    q.C = p.part + (long)slice * p.M * p.N;
+    q.ldc = p.N;
+    tile_epilogue<TL, EPI, epi_steps<EPI>()>(q, acc, reinterpret_cast<float*>(&smem[0]), tm, m0, n0, tid);
+  } else {
+    tile_epilogue<TL, EPI, epi_steps<EPI>()>(p, acc, reinterpret_cast<float*>(&smem[0]), tm, m0, n0, tid);
+  }
   }
 }
 
-// fp32 partial accumulators of one 256 x 256 tile slice
-constexpr size_t kSliceBytes = (size_t)kBM * kBN * 4;
+// Sums the reduction slices of a whole product (fp32 [slices][M][N], in slice
+// order) and applies the epilogue; eight columns per lane.
+template <int EPI>
+__global__ void __launch_bounds__(256) gemm_slices_kernel(G2Args p) {
+  const long idx = (long)blockIdx.x * 256 + threadIdx.x;
+  const int ng = p.N / 8;
+  const long m = idx / ng;
+  if (m >= p.M) return;
+  const int n = (int)(idx % ng) * 8;
+  const long plane = (long)p.M * p.N;
+  const float* src = p.part + m * p.N + n;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < p.slices; s0 += 4) {
+    Vec8<float> x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < p.slices) x[u].load(src + (s0 + u) * plane);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < p.slices) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += x[u].get(e);
+      }
+  }
+  if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU) {
+    Vec8<bf16> b;
+    b.load(p.bias + n);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += b.get(e);
+  }
+  if constexpr (EPI == EPI_ACC_F32) {
+    float* c = static_cast<float*>(p.C) + m * p.ldc + n;
+    Vec8<float> o;
+    o.load(c);
+    float t[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = o.get(e) + v[e];
+    o.set(t);
+    o.store(c);
+    return;
+  }
+  if constexpr (EPI == EPI_BIAS_RES || EPI == EPI_RES) {
+    Vec8<bf16> r;
+    r.load(p.R + m * p.ldr + n);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += p.res_scale * r.get(e);
+  }
+  if constexpr (EPI == EPI_GELU_BWD) {
+    Vec8<bf16> z;
+    z.load(p.Z + m * p.ldz + n);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] *= gelu2_grad(z.get(e));
+  }
+  Vec8<bf16> o;
+  o.set(v);
+  if (EPI != EPI_BIAS_GELU || p.C) o.store(static_cast<bf16*>(p.C) + m * p.ldc + n);
+  if constexpr (EPI == EPI_BIAS_GELU) {
+    float g[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[e] = gelu2(v[e]);
+    Vec8<bf16> og;
+    og.set(g);
+    og.store(p.C2 + m * p.ldc2 + n);
+  }
+}
 
 // Compute units of the current device (one persistent workgroup each; a
 // multiple of the 8 XCDs on MI355X, which the tile order relies on).
@@ -580,51 +673,176 @@ int num_cus() {
   return cached[dev];
 }
 
-template <bool AK, bool BKc, int EPI>
-hipError_t launch2(const GemmDesc& d, hipStream_t st) {
+// One launch of a product's rows on one tile shape.
+struct GemmPart {
+  int rows, tile, slices;
+};
+
+// Estimated time (us) of an NT or NN product of M rows on 64-, 128- or 256-row
+// tiles with its reduction in s slices, fitted to a sweep on MI355X (M 16 ..
+// 4409, N and K of hidden 1280 and 4096, every tile and slice count): a
+// 64-wide stage takes 0.45 us with one 64-row workgroup on a CU and 0.72 with
+// two, 0.79 for a 128-row one and 1.31 for a 256-row one; slices cost the
+// round trip of their fp32 sums and a launch.  Choosing by it comes within 1 %
+// (geometric mean) of the fastest choice of each product.
+double part_us(int M, int N, int K, int tile, int s) {
+  const double n = (double)(K / kBK) / s;
+  double t;
+  if (tile == 64) {
+    const long items = (long)((M + 63) / 64) * (N / 128) * s, full = items / 512, rem = items % 512;
+    t = 2.0 + 0.97 * (full + (rem > 0)) + n * (0.723 * full + (rem > 256 ? 0.723 : rem > 0 ? 0.449 : 0.0));
+  } else if (tile == 128) {
+    const long items = (long)((M + 127) / 128) * (N / 256) * s;
+    t = 2.4 + (double)((items + 255) / 256) * (4.5 + 0.791 * n);
+  } else {
+    const long items = (long)((M + 255) / 256) * (N / 256) * s;
+    t = 3.7 + (double)((items + 255) / 256) * (11.9 + 1.31 * n);
+  }
+  t = std::max(t, 4.5 + 2.0 * N * (double)K / 7.03e6);
+  if (s > 1) {
+    const double bytes = 8.0 * s * M * (double)N;
+    t += 4.3 + std::min(bytes, 21e6) / 4.37e6 + std::max(bytes - 21e6, 0.0) / 6.39e6;
+  }
+  return t;
+}
+
+constexpr int kSlices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
+
+// Best single launch for M rows (slices only as far as the scratch allows and
+// at least two stages each).
+double best_part(int M, int N, int K, size_t part_bytes, bool big, GemmPart* out) {
+  double best = 1e30;
+  for (int tile = 64; tile <= (big ? 256 : 128); tile *= 2)
+    for (int s : kSlices) {
+      if (s > 1 && ((size_t)s * M * N * 4 > part_bytes || 2 * s > K / kBK)) break;
+      const double t = part_us(M, N, K, tile, s);
+      if (t < best) {
+        best = t;
+        *out = GemmPart{M, tile, s};
+      }
+    }
+  return best;
+}
+
+// NT / NN: one launch over all rows, or two: as many whole rounds of large
+// tiles as fill every CU, and the remaining rows on the shape that suits them.
+int plan_rows(const GemmDesc& d, GemmPart (&parts)[2]) {
+  const size_t pb = d.part ? d.part_bytes : 0;
+  double best = best_part(d.M, d.N, d.K, pb, true, &parts[0]);
+  int n = 1;
+  if (d.M <= 256) return n;
+  const int nt = d.N / 256;
+  for (int tile = 128; tile <= 256; tile *= 2)
+    for (int s = 1; s <= 4; ++s) {
+      const long rows_t = d.M / tile;  // whole tile rows
+      long k = rows_t * nt * s / 256 * 256 / ((long)nt * s);
+      const int m1 = (int)(k * tile) / 256 * 256;
+      if (m1 <= 0 || m1 >= d.M || (s > 1 && ((size_t)s * m1 * d.N * 4 > pb || 2 * s > d.K / kBK))) continue;
+      GemmPart rest;
+      const double t = part_us(m1, d.N, d.K, tile, s) + best_part(d.M - m1, d.N, d.K, pb, false, &rest);
+      if (t < best) {
+        best = t;
+        parts[0] = GemmPart{m1, tile, s};
+        parts[1] = rest;
+        n = 2;
+      }
+    }
+  return n;
+}
+
+template <bool AK, bool BKc, int EPI, class TL>
+hipError_t launch_tile(const G2Args& a, hipStream_t st) {
+  const int items = ((a.M + TL::kBM - 1) / TL::kBM) * (a.N / TL::kBN) * a.slices;
+  const int cus = num_cus();
+  const int grid = TL::kBig && items > cus ? cus : items;
+  hipLaunchKernelGGL((gemm_bf16_kernel<AK, BKc, EPI, TL>), dim3(grid), dim3(TL::kThr), 0, st, a);
+  return hipGetLastError();
+}
+
+template <bool AK, bool BKc, int EPI, class TL>
+hipError_t launch_rows(const G2Args& a, hipStream_t st) {
+  if (a.slices == 1) return launch_tile<AK, BKc, EPI, TL>(a, st);
+  hipError_t e = launch_tile<AK, BKc, EPI_PART, TL>(a, st);
+  if (e != hipSuccess) return e;
+  const long groups = (long)a.M * (a.N / 8);
+  hipLaunchKernelGGL((gemm_slices_kernel<EPI>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+G2Args make_args(const GemmDesc& d, bool bk) {
   G2Args a;
   a.A = (const bf16*)d.A; a.B = (const bf16*)d.B; a.C = d.C;
   a.M = d.M; a.N = d.N; a.K = d.K; a.lda = d.lda; a.ldb = d.ldb; a.ldc = d.ldc;
   a.bias = (const bf16*)d.bias; a.R = (const bf16*)d.R; a.ldr = d.ldr;
   a.C2 = (bf16*)d.C2; a.ldc2 = d.ldc2; a.Z = (const bf16*)d.Z; a.ldz = d.ldz;
-  a.part = d.part; a.tail = 0; a.splits = 1; a.fixup = 0;
-  a.nb = gemm_b_rows(BKc, d);
+  a.part = d.part; a.slices = 1;
+  a.nb = gemm_b_rows(bk, d);
   a.res_scale = d.res_scale;
-  a.colsum = EPI == EPI_GELU_BWD ? d.colsum : nullptr;
-  const int tiles = ((d.M + kBM - 1) / kBM) * (d.N / kBN);
-  if (tiles == 0) return hipSuccess;
-  const int cus = num_cus();
-  // A last round that would leave three quarters of the CUs idle is cut
-  // into reduction slices (at least 4 stages each) spread over all CUs.
-  // Measured on MI355X: worth it from 128 stages (K = 8192) on; below that
-  // the partial stores and the fixup launch cost more than the idle CUs.
-  const int rem = tiles % cus, nk = (d.K + kBK - 1) / kBK;
-  if (d.part && rem > 0 && 4 * rem <= cus && nk >= 128) {
-    int splits = std::min(std::min(cus / rem, nk / 4), 16);
-    while (splits > 1 && (size_t)rem * splits * kSliceBytes > d.part_bytes) --splits;
-    if (splits > 1) {
-      a.tail = rem;
-      a.splits = splits;
-    }
+  a.colsum = nullptr;
+  return a;
+}
+
+// Forward and input-gradient products (rows = tokens).
+template <bool BKc, int EPI>
+hipError_t launch_tokens(const GemmDesc& d, hipStream_t st) {
+  if (d.M <= 0 || d.N <= 0) return hipSuccess;
+  GemmPart parts[2];
+  int n = 1;
+  if (d.tile) parts[0] = GemmPart{d.M, d.tile, d.slices};
+  else n = plan_rows(d, parts);
+  long m0 = 0;
+  for (int i = 0; i < n; ++i) {
+    G2Args a = make_args(d, BKc);
+    a.M = parts[i].rows;
+    a.slices = parts[i].slices;
+    a.A += m0 * d.lda;
+    const long cb = sizeof(bf16) * m0 * d.ldc;
+    if (a.C) a.C = static_cast<char*>(a.C) + cb;
+    if (a.R) a.R += m0 * d.ldr;
+    if (a.C2) a.C2 += m0 * d.ldc2;
+    if (a.Z) a.Z += m0 * d.ldz;
+    float* colsum = EPI == EPI_GELU_BWD && d.colsum ? d.colsum + m0 / kColsumRows * d.N : nullptr;
+    // only whole 256-row tiles form the column sums in their epilogue
+    const bool fused = parts[i].tile == 256 && parts[i].slices == 1;
+    if (fused) a.colsum = colsum;
+    hipError_t e = parts[i].tile == 256   ? launch_rows<true, BKc, EPI, Tile256>(a, st)
+                   : parts[i].tile == 128 ? launch_rows<true, BKc, EPI, Tile128>(a, st)
+                                          : launch_rows<true, BKc, EPI, Tile64>(a, st);
+    if (e == hipSuccess && colsum && !fused)
+      e = colsum_partial(DT_BF16, 0, a.C, d.ldc, nullptr, nullptr, nullptr, a.M, d.N, colsum, nullptr, st);
+    if (e != hipSuccess) return e;
+    m0 += parts[i].rows;
   }
-  const int items = tiles - a.tail + a.tail * a.splits;
-  hipLaunchKernelGGL((gemm_bf16_kernel<AK, BKc, EPI>), dim3(items < cus ? items : cus), dim3(kThr), 0, st, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.tail == 0) return e;
-  a.fixup = 1;
-  hipLaunchKernelGGL((gemm_bf16_kernel<AK, BKc, EPI>), dim3(a.tail), dim3(kThr), 0, st, a);
-  return hipGetLastError();
+  return hipSuccess;
+}
+
+// Weight gradients (reduction over the tokens).  Short reductions are bound by
+// the fp32 read-modify-write of C.
+hipError_t launch_wgrad(const GemmDesc& d, hipStream_t st) {
+  if (d.M <= 0 || d.N <= 0) return hipSuccess;
+  const G2Args a = make_args(d, false);
+  const long tiles256 = (long)((d.M + 255) / 256) * (d.N / 256), tiles64 = (long)((d.M + 63) / 64) * (d.N / 128);
+  int tile = d.tile;
+  // (16384 x 4096: 64-row tiles 161 us against 165 on 256-row ones at 509
+  // tokens, 128-row 194 against 177 at 768; 12288 x 4096: 64-row 94 against
+  // 113 at 509; too few 256-row tiles to fill the chip, 3840 x 1280: 64-row 22
+  // against 37 at 1024, 128-row 48 against 71 at 3072)
+  const bool few = tiles256 < 256;
+  if (!tile) tile = tiles64 <= 512 || d.K <= (few ? 1536 : 640) ? 64 : few || d.K < 768 ? 128 : 256;
+  if (tile == 256) return launch_tile<false, false, EPI_ACC_F32, Tile256>(a, st);
+  if (tile == 128) return launch_tile<false, false, EPI_ACC_F32, Tile128w>(a, st);
+  if (tiles64 <= 512) return launch_tile<false, false, EPI_ACC_F32, Tile64>(a, st);
+  return launch_tile<false, false, EPI_ACC_F32, Tile64w>(a, st);
 }
 
 }  // namespace
 
-// One slice per compute unit of an MI355X (256); launches split only as far
-// as the scratch they are given allows.
-size_t gemm_part_bytes() { return (size_t)256 * kSliceBytes; }
+size_t gemm_part_bytes() { return (size_t)64 << 20; }
 
 // Shapes the DMA kernel takes: N a multiple of 256, K-contiguous operands
 // with K a multiple of 64, and every buffer offset below 2^31 bytes.
 bool gemm_bf16_dma_ok(GemmLayout layout, const GemmDesc& d) {
+  constexpr int kBM = 256, kBN = 256;
   if (d.N % kBN != 0 || d.M <= 0) return false;
   const bool ak = layout != GEMM_TN, bk = layout == GEMM_NT;
   if ((ak || bk) && d.K % kBK != 0) return false;
@@ -637,7 +855,7 @@ bool gemm_bf16_dma_ok(GemmLayout layout, const GemmDesc& d) {
 }
 
 bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d) {
-  return dt == DT_BF16 && layout == GEMM_NN && epi == EPI_GELU_BWD && kBM == kColsumRows &&
+  return dt == DT_BF16 && layout == GEMM_NN && epi == EPI_GELU_BWD && Tile256::kBM == kColsumRows &&
          gemm_bf16_dma_ok(layout, d);
 }
 
@@ -645,21 +863,21 @@ hipError_t gemm_bf16_dma(GemmLayout layout, int epi, const GemmDesc& d, hipStrea
   switch (layout) {
     case GEMM_NT:
       switch (epi) {
-        case EPI_STORE: return launch2<true, true, EPI_STORE>(d, st);
-        case EPI_BIAS: return launch2<true, true, EPI_BIAS>(d, st);
-        case EPI_BIAS_RES: return launch2<true, true, EPI_BIAS_RES>(d, st);
-        case EPI_BIAS_GELU: return launch2<true, true, EPI_BIAS_GELU>(d, st);
+        case EPI_STORE: return launch_tokens<true, EPI_STORE>(d, st);
+        case EPI_BIAS: return launch_tokens<true, EPI_BIAS>(d, st);
+        case EPI_BIAS_RES: return launch_tokens<true, EPI_BIAS_RES>(d, st);
+        case EPI_BIAS_GELU: return launch_tokens<true, EPI_BIAS_GELU>(d, st);
       }
       break;
     case GEMM_NN:
       switch (epi) {
-        case EPI_STORE: return launch2<true, false, EPI_STORE>(d, st);
-        case EPI_GELU_BWD: return launch2<true, false, EPI_GELU_BWD>(d, st);
-        case EPI_RES: return launch2<true, false, EPI_RES>(d, st);
+        case EPI_STORE: return launch_tokens<false, EPI_STORE>(d, st);
+        case EPI_GELU_BWD: return launch_tokens<false, EPI_GELU_BWD>(d, st);
+        case EPI_RES: return launch_tokens<false, EPI_RES>(d, st);
       }
       break;
     case GEMM_TN:
-      if (epi == EPI_ACC_F32) return launch2<false, false, EPI_ACC_F32>(d, st);
+      if (epi == EPI_ACC_F32) return launch_wgrad(d, st);
       break;
   }
   return hipErrorInvalidValue;

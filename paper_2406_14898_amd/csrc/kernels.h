@@ -23,8 +23,8 @@ struct GemmDesc {
   long ldc2 = 0;
   const void* Z = nullptr;
   long ldz = 0;
-  // Optional fp32 scratch for splitting the reduction of a partial last
-  // round of tiles (bf16 LDS-DMA kernel); null = never split.
+  // Optional fp32 scratch for splitting the reduction of products with few
+  // tiles (bf16 LDS-DMA kernel); null = never split.
   float* part = nullptr;
   size_t part_bytes = 0;
   // Rows B really has (the N index for NT, the reduction index for NN / TN);
@@ -36,14 +36,16 @@ struct GemmDesc {
   // receives, per 256-row block, the column sums of the stored C (the
   // layout colsum_partial writes, so colsum_finish completes them).
   float* colsum = nullptr;
+  // bf16 LDS-DMA kernel: tile height (256, 128 or 64) and reduction slices
+  // (NT and NN, with scratch) to use for all rows; 0: chosen from the shape.
+  int tile = 0, slices = 1;
 };
 // Rows of B a kernel may read for a layout and shape.
 inline int gemm_b_rows(bool b_kcontig, const GemmDesc& d) {
   const int full = b_kcontig ? d.N : d.K;
   return d.b_rows > 0 && d.b_rows < full ? d.b_rows : full;
 }
-// Scratch that lets gemm() split the partial last round of tiles (one
-// 256 KB slice per compute unit).
+// Scratch that lets gemm() split the reduction of products with few tiles.
 size_t gemm_part_bytes();
 enum GemmEpi : int {
   EPI_STORE = 0,      // C = acc

@@ -31,6 +31,14 @@ int fl_test_gemm(int dtype, int layout, int epi, const void* A, const void* B, v
                  int64_t lda, int64_t ldb, int64_t ldc, const void* bias, const void* R, int64_t ldr, void* C2,
                  int64_t ldc2, const void* Z, int64_t ldz, float* part, int64_t part_bytes, int b_rows,
                  float res_scale, float* colsum, void* stream) {
+  return fl_test_gemm_tiled(dtype, layout, epi, A, B, C, M, N, K, lda, ldb, ldc, bias, R, ldr, C2, ldc2, Z, ldz, part,
+                            part_bytes, b_rows, res_scale, colsum, 0, 1, stream);
+}
+
+int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void* B, void* C, int M, int N, int K,
+                       int64_t lda, int64_t ldb, int64_t ldc, const void* bias, const void* R, int64_t ldr, void* C2,
+                       int64_t ldc2, const void* Z, int64_t ldz, float* part, int64_t part_bytes, int b_rows,
+                       float res_scale, float* colsum, int tile, int slices, void* stream) {
   if (!dtype_ok(dtype)) return set_error(FL_ERR_ARG, "bad dtype");
   if (!A || !B || !C) return set_error(FL_ERR_NULL, "A / B / C is NULL");
   if (!al16(A) || !al16(B) || !al16(C)) return set_error(FL_ERR_ALIGN, "A / B / C not 16-byte aligned");
@@ -70,6 +78,17 @@ int fl_test_gemm(int dtype, int layout, int epi, const void* A, const void* B, v
   d.part = part; d.part_bytes = part ? (size_t)part_bytes : 0;
   d.b_rows = b_rows;
   d.res_scale = res_scale;
+  if (tile) {
+    if (tile != 64 && tile != 128 && tile != 256) return set_error(FL_ERR_ARG, "tile must be 0, 64, 128 or 256");
+    if (dtype != FL_BF16 || !gemm_bf16_dma_ok((GemmLayout)layout, d))
+      return set_error(FL_ERR_ARG, "a forced tile needs a product the LDS-DMA kernel takes");
+    if (slices < 1 || (layout == FL_GEMM_TN && slices != 1) || slices > (K + 63) / 64)
+      return set_error(FL_ERR_ARG, "slices outside [1, reduction stages]");
+    if (slices > 1 && d.part_bytes / 4 / slices < (size_t)M * N)
+      return set_error(FL_ERR_WORKSPACE, "part too small for the slices");
+    d.tile = tile;
+    d.slices = slices;
+  }
   if (colsum) {
     if (!al16(colsum)) return set_error(FL_ERR_ALIGN, "colsum misaligned");
     if (!gemm_fuses_colsum((DType)dtype, (GemmLayout)layout, epi, d))

@@ -43,7 +43,7 @@ EXPORTS = (
     "fl_client_create", "fl_client_destroy", "fl_client_workspace_bytes", "fl_embedding_forward",
     "fl_embedding_backward", "fl_lm_head_forward", "fl_lm_head_backward",
     "fl_stack_profile", "fl_stack_profile_classes", "fl_stack_profile_read", "fl_profile_class_name",
-    "fl_test_gemm", "fl_test_layernorm_fwd", "fl_test_layernorm_bwd", "fl_test_layernorm_bwd_fused",
+    "fl_test_gemm", "fl_test_gemm_tiled", "fl_test_layernorm_fwd", "fl_test_layernorm_bwd", "fl_test_layernorm_bwd_fused",
     "fl_test_colsum",
     "fl_test_rope", "fl_test_attention_fwd", "fl_test_attention_bwd", "fl_test_attention_ds_bytes",
 )
@@ -126,6 +126,9 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         "fl_test_gemm": [ctypes.c_int] * 3 + [vp] * 3 + [ctypes.c_int] * 3 + [i64] * 3 + [vp, vp, i64, vp, i64, vp,
                                                                                           i64, vp, i64, ctypes.c_int,
                                                                                           ctypes.c_float, vp, vp],
+        "fl_test_gemm_tiled": [ctypes.c_int] * 3 + [vp] * 3 + [ctypes.c_int] * 3 + [i64] * 3 +
+                              [vp, vp, i64, vp, i64, vp, i64, vp, i64, ctypes.c_int, ctypes.c_float, vp, ctypes.c_int,
+                               ctypes.c_int, vp],
         "fl_test_layernorm_fwd": [ctypes.c_int, vp, vp, vp, vp, vp, vp, ctypes.c_int, ctypes.c_int, ctypes.c_float,
                                   vp],
         "fl_test_layernorm_bwd": [ctypes.c_int] + [vp] * 7 + [ctypes.c_int, ctypes.c_int, vp],
@@ -403,14 +406,19 @@ def profile_table(handle: int):
 # ---------------------------------------------------------------------------
 
 def fl_test_gemm(dtype, layout, epi, A, B, C, M, N, K, lda, ldb, ldc, bias=None, R=None, ldr=0, C2=None, ldc2=0,
-                 Z=None, ldz=0, part=None, b_rows=0, res_scale=1.0, colsum=None, stream=None) -> None:
+                 Z=None, ldz=0, part=None, b_rows=0, res_scale=1.0, colsum=None, stream=None, tile=0,
+                 slices=1) -> None:
     """part: optional fp32 device tensor, split-reduction scratch; b_rows:
     rows B really has (0 = all); colsum: fp32 [ceil(M/256), N] per-block
-    column sums of C (bf16 NN GELU_BWD only)."""
+    column sums of C (bf16 NN GELU_BWD only); tile / slices: the bf16 kernel's
+    tile height and reduction slices (0: chosen from the shape)."""
     nbytes = part.numel() * part.element_size() if part is not None else 0
-    _check(load().fl_test_gemm(dtype, layout, epi, _ptr(A), _ptr(B), _ptr(C), M, N, K, lda, ldb, ldc, _ptr(bias),
-                               _ptr(R), ldr, _ptr(C2), ldc2, _ptr(Z), ldz, _ptr(part), nbytes, b_rows,
-                               res_scale, _ptr(colsum), _stream(stream)))
+    args = (dtype, layout, epi, _ptr(A), _ptr(B), _ptr(C), M, N, K, lda, ldb, ldc, _ptr(bias), _ptr(R), ldr, _ptr(C2),
+            ldc2, _ptr(Z), ldz, _ptr(part), nbytes, b_rows, res_scale, _ptr(colsum))
+    if tile:
+        _check(load().fl_test_gemm_tiled(*args, tile, slices, _stream(stream)))
+    else:
+        _check(load().fl_test_gemm(*args, _stream(stream)))
 
 
 def fl_test_layernorm_fwd(dtype, x, g, b, y, mean, rstd, T, H, eps, stream=None) -> None:

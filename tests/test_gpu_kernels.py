@@ -69,6 +69,100 @@ def test_gemm_nn(dt, epi, N):
     assert rel_l2(host(C), ref) < TOL[dt] / 4
 
 
+def _tiled_case(lay, epi, M, N, K, seed=31):
+    """Operands and the fp64 reference (C, second output or None) of one
+    product of the bf16 kernel, every epilogue's extra input included."""
+    ka, kb = ((K, M) if lay == F.FL_GEMM_TN else (M, K)), ((N, K) if lay == F.FL_GEMM_NT else (K, N))
+    A, B = rnd(ka, seed), rnd(kb, seed + 1, 0.1)
+    bias, R, C0 = rnd((N,), seed + 2), rnd((M, N), seed + 3), rnd((M, N), seed + 4, dt="f32")
+    a = A.T if lay == F.FL_GEMM_TN else A
+    b = B.T if lay == F.FL_GEMM_NT else B
+    ref, second = a.astype(np.float64) @ b.astype(np.float64), None
+    if epi in (F.FL_EPI_BIAS, F.FL_EPI_BIAS_RES, F.FL_EPI_BIAS_GELU):
+        ref = ref + bias
+    if epi in (F.FL_EPI_BIAS_RES, F.FL_EPI_RES):
+        ref = ref + 1.5 * R
+    if epi == F.FL_EPI_BIAS_GELU:
+        second = oracle.gelu(ref)
+    if epi == F.FL_EPI_GELU_BWD:
+        ref = ref * oracle.gelu_grad(R.astype(np.float64))
+    if epi == F.FL_EPI_ACC_F32:
+        ref = ref + C0
+    return A, B, bias, R, C0, ref, second
+
+
+# every layout and epilogue, at row counts around the tile heights and on
+# token counts that are no multiple of anything
+TILED = [(F.FL_GEMM_NT, F.FL_EPI_STORE), (F.FL_GEMM_NT, F.FL_EPI_BIAS), (F.FL_GEMM_NT, F.FL_EPI_BIAS_RES),
+         (F.FL_GEMM_NT, F.FL_EPI_BIAS_GELU), (F.FL_GEMM_NN, F.FL_EPI_STORE), (F.FL_GEMM_NN, F.FL_EPI_GELU_BWD),
+         (F.FL_GEMM_NN, F.FL_EPI_RES), (F.FL_GEMM_TN, F.FL_EPI_ACC_F32)]
+
+
+@pytest.mark.parametrize("tile,slices", [(64, 1), (64, 3), (64, 7), (128, 1), (128, 2), (128, 5), (256, 1), (256, 4)])
+@pytest.mark.parametrize("lay,epi", TILED)
+def test_gemm_tiles_and_slices(lay, epi, tile, slices):
+    """The bf16 kernel on every tile height and number of reduction slices,
+    against float64: one row, a tile's height -1 / +0 / +1, ragged reduction
+    lengths for the weight gradient, and reductions of one stage, of fewer
+    stages than a tile's ring of slots and of many.  Stored bf16 rounds to
+    2^-9 of a value and the fp32 sums of K <= 1024 terms stay far below that:
+    5e-3 relative L2 (TOL / 4)."""
+    if lay == F.FL_GEMM_TN and slices > 1:
+        pytest.skip("weight gradients are not sliced")
+    part = torch.full((16 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
+    for M, N, K in ((1, 256, 64), (tile - 1, 256, 192), (tile, 512, 448), (tile + 1, 256, 1024), (300, 768, 512)):
+        if lay == F.FL_GEMM_TN:
+            M, K = (M + 7) // 8 * 8, K - 27
+        if slices > (K + 63) // 64:
+            continue
+        A, B, bias, R, C0, ref, second = _tiled_case(lay, epi, M, N, K)
+        acc = epi == F.FL_EPI_ACC_F32
+        C = dev(C0, "f32") if acc else torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        C2 = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        nb = (M + 255) // 256
+        cs = torch.full((nb, N), float("nan"), device="cuda") if epi == F.FL_EPI_GELU_BWD else None
+        F.fl_test_gemm(F.FL_BF16, lay, epi, dev(A, "bf16"), dev(B, "bf16"), C, M, N, K, A.shape[1], B.shape[1], N,
+                       bias=dev(bias, "bf16"), R=dev(R, "bf16"), ldr=N, C2=C2, ldc2=N, Z=dev(R, "bf16"), ldz=N,
+                       part=part, res_scale=1.5, colsum=cs, tile=tile, slices=slices)
+        sync()
+        assert rel_l2(host(C), ref) < (1e-6 if acc else TOL["bf16"] / 4), (M, N, K)
+        if second is not None:
+            assert rel_l2(host(C2), second) < TOL["bf16"] / 4, (M, N, K)
+        if cs is not None:
+            c = host(C)
+            for blk in range(nb):
+                rows = c[256 * blk:256 * (blk + 1)]
+                assert np.all(np.abs(host(cs)[blk] - rows.sum(0)) <= 1e-6 * (np.abs(rows).sum(0) + 1e-30)), (M, blk)
+
+
+@pytest.mark.parametrize("lay,epi", [t for t in TILED if t[0] != F.FL_GEMM_TN])
+def test_gemm_rows_in_two_launches(lay, epi):
+    """Row counts just past whole rounds of large tiles: the product runs as
+    two launches (the whole rounds, then the remaining rows on another tile
+    shape), and the second starts in the right row of every operand."""
+    part = torch.empty(64 << 20 >> 2, dtype=torch.float32, device="cuda")
+    N, K = 4096, 128
+    for M in (4096 + 1, 4096 + 300):
+        A, B, bias, R, C0, ref, second = _tiled_case(lay, epi, M, N, K)
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        C2 = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        nb = (M + 255) // 256
+        cs = torch.full((nb, N), float("nan"), device="cuda") if epi == F.FL_EPI_GELU_BWD else None
+        F.fl_test_gemm(F.FL_BF16, lay, epi, dev(A, "bf16"), dev(B, "bf16"), C, M, N, K, A.shape[1], B.shape[1], N,
+                       bias=dev(bias, "bf16"), R=dev(R, "bf16"), ldr=N, C2=C2, ldc2=N, Z=dev(R, "bf16"), ldz=N,
+                       part=part, res_scale=1.5, colsum=cs)
+        sync()
+        c = host(C)
+        assert rel_l2(c[:4096], ref[:4096]) < TOL["bf16"] / 4 and rel_l2(c[4096:], ref[4096:]) < TOL["bf16"] / 4
+        if second is not None:
+            c2 = host(C2)
+            assert rel_l2(c2[4096:], second[4096:]) < TOL["bf16"] / 4
+        if cs is not None:
+            for blk in range(nb):
+                rows = c[256 * blk:256 * (blk + 1)]
+                assert np.all(np.abs(host(cs)[blk] - rows.sum(0)) <= 1e-6 * (np.abs(rows).sum(0) + 1e-30)), (M, blk)
+
+
 @pytest.mark.parametrize("M", [700, 256, 1])
 def test_gemm_gelu_bwd_column_sums(M):
     """The GeLU' input-gradient GEMM also writes, per 256-row block, the
