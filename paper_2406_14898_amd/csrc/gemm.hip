@@ -18,6 +18,7 @@
 // up with four consecutive output columns of one row, which the epilogue
 // stores as one 8- or 16-byte vector.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -144,6 +145,50 @@ struct TileLoader<T, ROWS, NT, false> {
   }
 };
 
+// Epilogue of four consecutive columns n .. n + 3 of row m.
+template <typename T, int EPI>
+__device__ __forceinline__ void store_outputs(const GemmArgs& p, int m, int n, const float (&acc)[4]) {
+  float v[4] = {acc[0], acc[1], acc[2], acc[3]};
+  if constexpr (EPI == EPI_ACC_F32) {
+    float* C = static_cast<float*>(p.C) + (long)m * p.ldc + n;
+    Vec4<float> c;
+    c.load(C);
+    float o[4] = {c.get(0) + v[0], c.get(1) + v[1], c.get(2) + v[2], c.get(3) + v[3]};
+    c.set(o);
+    c.store(C);
+  } else {
+    if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU) {
+      Vec4<T> b;
+      b.load(static_cast<const T*>(p.bias) + n);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] += b.get(r);
+    }
+    if constexpr (EPI == EPI_BIAS_RES || EPI == EPI_RES) {
+      Vec4<T> rr;
+      rr.load(static_cast<const T*>(p.R) + (long)m * p.ldr + n);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] += p.res_scale * rr.get(r);
+    }
+    if constexpr (EPI == EPI_GELU_BWD) {
+      Vec4<T> z;
+      z.load(static_cast<const T*>(p.Z) + (long)m * p.ldz + n);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] *= gelu_grad_f(z.get(r));
+    }
+    Vec4<T> o;
+    o.set(v);
+    if (EPI != EPI_BIAS_GELU || p.C) o.store(static_cast<T*>(p.C) + (long)m * p.ldc + n);
+    if constexpr (EPI == EPI_BIAS_GELU) {
+      float g[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) g[r] = gelu_f(v[r]);
+      Vec4<T> og;
+      og.set(g);
+      og.store(static_cast<T*>(p.C2) + (long)m * p.ldc2 + n);
+    }
+  }
+}
+
 template <typename T, int BM, int BN, int WTM, int WTN, bool AK, bool BKc, int EPI>
 __global__ void __launch_bounds__(64 * (BM / (16 * WTM)) * (BN / (16 * WTN)))
 gemm_kernel(GemmArgs p) {
@@ -230,47 +275,126 @@ gemm_kernel(GemmArgs p) {
 #pragma unroll
     for (int i = 0; i < WTN; ++i) {
       const int n = n0 + wn * 16 * WTN + 16 * i + 4 * fg;
-      float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-      if constexpr (EPI == EPI_ACC_F32) {
-        float* C = static_cast<float*>(p.C) + (long)m * p.ldc + n;
-        Vec4<float> c;
-        c.load(C);
-        float o[4] = {c.get(0) + v[0], c.get(1) + v[1], c.get(2) + v[2], c.get(3) + v[3]};
-        c.set(o);
-        c.store(C);
-      } else {
-        if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU) {
-          Vec4<T> b;
-          b.load(static_cast<const T*>(p.bias) + n);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] += b.get(r);
-        }
-        if constexpr (EPI == EPI_BIAS_RES || EPI == EPI_RES) {
-          Vec4<T> rr;
-          rr.load(static_cast<const T*>(p.R) + (long)m * p.ldr + n);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] += p.res_scale * rr.get(r);
-        }
-        if constexpr (EPI == EPI_GELU_BWD) {
-          Vec4<T> z;
-          z.load(static_cast<const T*>(p.Z) + (long)m * p.ldz + n);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] *= gelu_grad_f(z.get(r));
-        }
-        Vec4<T> o;
-        o.set(v);
-        if (EPI != EPI_BIAS_GELU || p.C) o.store(static_cast<T*>(p.C) + (long)m * p.ldc + n);
-        if constexpr (EPI == EPI_BIAS_GELU) {
-          float g[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) g[r] = gelu_f(v[r]);
-          Vec4<T> og;
-          og.set(g);
-          og.store(static_cast<T*>(p.C2) + (long)m * p.ldc2 + n);
-        }
-      }
+      const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+      store_outputs<T, EPI>(p, m, n, v);
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// fp32 products with few 128 x 128 tiles: 32 x 32 (TT = 2) or 16 x 16 (TT =
+// 1) outputs per workgroup, the reduction dealt to its eight waves in chunks
+// of 32.  Such a product is bound by the length of one workgroup's serial
+// chain, not by the chip's arithmetic or bandwidth, so every wave covers the
+// whole tile for an eighth of the reduction, its operands go from memory to
+// registers with the next chunk's loads in flight (no LDS stage, no barrier
+// per chunk), and the partial sums meet in LDS once, added in wave order.
+// Against the 128 x 128 tiles' barrier-separated stages (us): 256 x 256 x 1024
+// 79 -> 6.9, 256 x 768 x 256 24 -> 5.4, 1024 x 1024 x 256 33 -> 14.
+// A K-contiguous operand lane reads its row's eight consecutive reduction
+// indices (8 g .. 8 g + 7); an MN-contiguous one reads, for each of them, TT
+// neighbouring rows, one for each 16-row matrix-core tile (row TT (lane % 16)
+// + t of tile t).
+// ---------------------------------------------------------------------------
+template <bool KC, int TT>
+struct SmallOperand {
+  Vec8<float> v[TT];  // per 16-row tile: eight reduction indices of this lane's row
+  // rows r0 .. r0 + 16 TT - 1 below rlim, reduction indices k .. k + 7 below klim
+  __device__ __forceinline__ void load(const float* P, long ld, int r0, int rlim, int k, int klim, int fr) {
+    if constexpr (KC) {
+#pragma unroll
+      for (int t = 0; t < TT; ++t) {
+        const int r = r0 + 16 * t + fr;
+        if (r < rlim && k < klim) v[t].load(P + (long)r * ld + k);
+        else v[t].zero();
+      }
+    } else {
+      const int r = r0 + TT * fr;
+      float a[TT][8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const bool ok = k + e < klim && r + TT - 1 < rlim;
+        const float* q = P + (long)(k + e) * ld + r;
+        if constexpr (TT == 2) {
+          u32x2 x = {0u, 0u};
+          if (ok) x = ld8(q);
+          a[0][e] = __uint_as_float(x[0]);
+          a[TT - 1][e] = __uint_as_float(x[1]);
+        } else {
+          a[0][e] = ok ? *q : 0.f;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < TT; ++t) v[t].set(a[t]);
+    }
+  }
+  // tile row of matrix-core row idx of 16-row tile t
+  __device__ static __forceinline__ int row(int t, int idx) { return KC ? 16 * t + idx : TT * idx + t; }
+};
+
+template <bool AK, bool BKc, int EPI, int TT>
+__global__ void __launch_bounds__(512) gemm_f32_small_kernel(GemmArgs p) {
+  constexpr int NW = 8, BT = 16 * TT, PAD = BT + 4;
+  __shared__ __attribute__((aligned(16))) float red[NW][BT * PAD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int fr = lane & 15, fg = lane >> 4;
+  const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
+  const float* A = static_cast<const float*>(p.A);
+  const float* B = static_cast<const float*>(p.B);
+  // rows and reduction indices that exist (a K-contiguous row is read in whole
+  // groups of eight: K is a multiple of 64 there; M and N are even)
+  const int bnlim = BKc ? p.nb : p.N, bklim = BKc ? p.K : p.nb;
+  f32x4 acc[TT][TT];
+#pragma unroll
+  for (int i = 0; i < TT; ++i)
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  SmallOperand<AK, TT> a[2];
+  SmallOperand<BKc, TT> b[2];
+  auto load = [&](auto slot, int k0) {
+    constexpr int S = decltype(slot)::value;
+    a[S].load(A, p.lda, m0, p.M, k0 + 8 * fg, p.K, fr);
+    b[S].load(B, p.ldb, n0, bnlim, k0 + 8 * fg, bklim, fr);
+  };
+  auto mma = [&](auto slot) {
+    constexpr int S = decltype(slot)::value;
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TT; ++j) acc[i][j] = mma16(b[S].v[i].frag(), a[S].v[j].frag(), acc[i][j]);
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  // this wave's chunks: 32 wave, 32 (wave + NW), ...
+  constexpr int STEP = 32 * NW;
+  load(S0{}, 32 * wave);
+  for (int k0 = 32 * wave; k0 < p.K; k0 += 2 * STEP) {
+    load(S1{}, k0 + STEP);  // past the end: reads nothing
+    mma(S0{});
+    if (k0 + STEP >= p.K) break;
+    load(S0{}, k0 + 2 * STEP);
+    mma(S1{});
+  }
+#pragma unroll
+  for (int j = 0; j < TT; ++j)
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        red[wave][SmallOperand<AK, TT>::row(j, fr) * PAD + SmallOperand<BKc, TT>::row(i, 4 * fg + e)] = acc[i][j][e];
+  __syncthreads();
+  const int r = tid / (BT / 4), c = tid % (BT / 4) * 4;
+  const int m = m0 + r, n = n0 + c;
+  if (r >= BT || m >= p.M) return;
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    Vec4<float> x;
+    x.load(&red[w][r * PAD + c]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += x.get(e);
+  }
+  store_outputs<float, EPI>(p, m, n, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -281,17 +405,31 @@ template <typename T, int BM, int BN, int WTM, int WTN, bool AK, bool BKc, int E
 static hipError_t launch_cfg(const GemmArgs& a, hipStream_t st) {
   using Cfg = GemmCfg<T, BM, BN, WTM, WTN, AK, BKc, EPI>;
   int tiles = ((a.M + BM - 1) / BM) * (a.N / BN);
-  if (tiles == 0) return hipSuccess;
   hipLaunchKernelGGL((gemm_kernel<T, BM, BN, WTM, WTN, AK, BKc, EPI>), dim3(tiles), dim3(Cfg::NT), 0, st, a);
   return hipGetLastError();
 }
 
 template <typename T, bool AK, bool BKc, int EPI>
 static hipError_t launch_layout(const GemmArgs& a, hipStream_t st) {
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if constexpr (sizeof(T) == 2) {
     if (a.N % 256 == 0) return launch_cfg<T, 256, 256, 8, 8, AK, BKc, EPI>(a, st);
     return launch_cfg<T, 256, 128, 8, 4, AK, BKc, EPI>(a, st);
   } else {
+    // Too few 128 x 128 tiles to fill the chip.  Measured (us): 128 tiles
+    // (2048 x 1024 x 256) 25 on 32 x 32 against 35 on 128 x 128, 248 tiles
+    // (3900 x 1024 x 256) 35 against 37; 64 tiles of 32 x 32 (256 x 256 x 1024)
+    // 11 against 6.9 on 16 x 16, 192 of them (256 x 768 x 256) 5.4 against 5.9.
+    const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
+    const long tiles32 = (long)((a.M + 31) / 32) * (a.N / 32);
+    if (tiles32 <= 128) {
+      hipLaunchKernelGGL((gemm_f32_small_kernel<AK, BKc, EPI, 1>), dim3(a.N / 16, (a.M + 15) / 16), dim3(512), 0, st, a);
+      return hipGetLastError();
+    }
+    if (tiles < 192) {
+      hipLaunchKernelGGL((gemm_f32_small_kernel<AK, BKc, EPI, 2>), dim3(a.N / 32, (a.M + 31) / 32), dim3(512), 0, st, a);
+      return hipGetLastError();
+    }
     if (a.N % 128 == 0) return launch_cfg<T, 128, 128, 4, 4, AK, BKc, EPI>(a, st);
     return launch_cfg<T, 128, 64, 4, 2, AK, BKc, EPI>(a, st);
   }

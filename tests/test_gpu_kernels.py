@@ -69,12 +69,12 @@ def test_gemm_nn(dt, epi, N):
     assert rel_l2(host(C), ref) < TOL[dt] / 4
 
 
-def _tiled_case(lay, epi, M, N, K, seed=31):
+def _tiled_case(lay, epi, M, N, K, seed=31, dt="bf16"):
     """Operands and the fp64 reference (C, second output or None) of one
-    product of the bf16 kernel, every epilogue's extra input included."""
+    product, every epilogue's extra input included."""
     ka, kb = ((K, M) if lay == F.FL_GEMM_TN else (M, K)), ((N, K) if lay == F.FL_GEMM_NT else (K, N))
-    A, B = rnd(ka, seed), rnd(kb, seed + 1, 0.1)
-    bias, R, C0 = rnd((N,), seed + 2), rnd((M, N), seed + 3), rnd((M, N), seed + 4, dt="f32")
+    A, B = rnd(ka, seed, dt=dt), rnd(kb, seed + 1, 0.1, dt=dt)
+    bias, R, C0 = rnd((N,), seed + 2, dt=dt), rnd((M, N), seed + 3, dt=dt), rnd((M, N), seed + 4, dt="f32")
     a = A.T if lay == F.FL_GEMM_TN else A
     b = B.T if lay == F.FL_GEMM_NT else B
     ref, second = a.astype(np.float64) @ b.astype(np.float64), None
@@ -133,6 +133,38 @@ def test_gemm_tiles_and_slices(lay, epi, tile, slices):
             for blk in range(nb):
                 rows = c[256 * blk:256 * (blk + 1)]
                 assert np.all(np.abs(host(cs)[blk] - rows.sum(0)) <= 1e-6 * (np.abs(rows).sum(0) + 1e-30)), (M, blk)
+
+
+@pytest.mark.parametrize("lay,epi", TILED)
+def test_gemm_f32_few_tiles(lay, epi):
+    """fp32 products of few tiles, on both small tile sizes: one row, row
+    counts around 16 and 32, reductions shorter than the eight waves' first
+    chunks and past a whole round of them, ragged for the weight gradient, and
+    B with fewer rows than the shape (they read as zero and are not touched).
+    fp32 sums of K <= 1024 terms: 1e-6 relative L2."""
+    for M, N, K in ((1, 64, 64), (15, 256, 192), (17, 64, 576), (33, 128, 1024), (260, 768, 320)):
+        if lay == F.FL_GEMM_TN:
+            M, K = (M + 7) // 8 * 8, K - 27
+        A, B, bias, R, C0, ref, second = _tiled_case(lay, epi, M, N, K, dt="f32")
+        C = dev(C0, "f32") if epi == F.FL_EPI_ACC_F32 else torch.full((M, N), float("nan"), device="cuda")
+        C2 = torch.full((M, N), float("nan"), device="cuda")
+        args = (A.shape[1], B.shape[1], N)
+        kw = dict(bias=dev(bias, "f32"), R=dev(R, "f32"), ldr=N, C2=C2, ldc2=N, Z=dev(R, "f32"), ldz=N, res_scale=1.5)
+        F.fl_test_gemm(F.FL_F32, lay, epi, dev(A, "f32"), dev(B, "f32"), C, M, N, K, *args, **kw)
+        sync()
+        assert rel_l2(host(C), ref) < 1e-6, (M, N, K)
+        if second is not None:
+            assert rel_l2(host(C2), second) < 1e-6, (M, N, K)
+        if epi == F.FL_EPI_STORE:
+            nb = B.shape[0] - 24  # the rows past it hold NaN
+            cut = B.copy()
+            cut[nb:] = 0
+            full = A.astype(np.float64) @ (cut.T if lay == F.FL_GEMM_NT else cut).astype(np.float64)
+            poison = cut.copy()
+            poison[nb:] = np.nan
+            F.fl_test_gemm(F.FL_F32, lay, epi, dev(A, "f32"), dev(poison, "f32"), C, M, N, K, *args, b_rows=nb)
+            sync()
+            assert rel_l2(host(C), full) < 1e-6, (M, N, K)
 
 
 @pytest.mark.parametrize("lay,epi", [t for t in TILED if t[0] != F.FL_GEMM_TN])
