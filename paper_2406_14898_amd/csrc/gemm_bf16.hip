@@ -185,9 +185,9 @@ __device__ __forceinline__ float gelu2_grad(float z) {
 
 // Work order: workgroup wg runs on XCD wg % 8, and each XCD takes a contiguous
 // range of work items.  Items walk bands of kBand tile rows column by column
-// (kAlongN: bands of tile columns row by row); a tile's reduction slices lie
-// between the band's rows and the next column, so the workgroups of an XCD
-// that run together read the same reduction range of the same rows.
+// (kAlongN: bands of tile columns row by row), one reduction slice of the
+// whole product after another, so that an XCD reads few slices of A (1295
+// tokens x 4096 x 130560: SLICEFIG).
 template <int kBand, bool kAlongN>
 __device__ __forceinline__ void work_coords(int wg, int nwg, int tiles_m, int tiles_n, int slices, int& tm, int& tn,
                                             int& slice) {
@@ -196,14 +196,14 @@ __device__ __forceinline__ void work_coords(int wg, int nwg, int tiles_m, int ti
   const int x = wg % kXcd, j = wg / kXcd;
   const int id = (x < r) ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
   const int ta = kAlongN ? tiles_n : tiles_m, tb = kAlongN ? tiles_m : tiles_n;
-  const int per_band = kBand * tb * slices;
-  const int band = id / per_band;
+  slice = id / (ta * tb);
+  const int tile = id - slice * (ta * tb);
+  const int per_band = kBand * tb;
+  const int band = tile / per_band;
   const int first = band * kBand;
   const int size = min(ta - first, kBand);
-  const int in_band = id % per_band;
-  const int a = first + in_band % size, rest = in_band / size;
-  slice = rest % slices;
-  const int b = rest / slices;
+  const int in_band = tile - band * per_band;
+  const int a = first + in_band % size, b = in_band / size;
   tm = kAlongN ? b : a;
   tn = kAlongN ? a : b;
 }
@@ -368,7 +368,7 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
 // 4096 x 4096 output projection than 4), 4 elsewhere (8 measured no faster),
 // 2 for the fp32 accumulator.
 template <int EPI>
-constexpr int epi_steps() { return (EPI == EPI_BIAS_RES || EPI == EPI_RES) ? 8 : EPI == EPI_ACC_F32 ? 2 : 4; }
+constexpr int epi_steps() { return (EPI == EPI_BIAS_RES || EPI == EPI_RES) ? 8 : EPI == EPI_ACC_F32 ? 8 : 4; }
 
 template <bool AK, bool BKc, int EPI, class TL>
 __global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16_kernel(G2Args p) {
@@ -740,7 +740,9 @@ int plan_rows(const GemmDesc& d, GemmPart (&parts)[2]) {
       if (m1 <= 0 || m1 >= d.M || (s > 1 && ((size_t)s * m1 * d.N * 4 > pb || 2 * s > d.K / kBK))) continue;
       GemmPart rest;
       const double t = part_us(m1, d.N, d.K, tile, s) + best_part(d.M - m1, d.N, d.K, pb, false, &rest);
-      if (t < best) {
+      // (5 % for what the estimate does not see; also keeps the choice of rows
+      // that are close to whole rounds anyway)
+      if (t < 0.95 * best) {
         best = t;
         parts[0] = GemmPart{m1, tile, s};
         parts[1] = rest;
@@ -828,7 +830,7 @@ hipError_t launch_wgrad(const GemmDesc& d, hipStream_t st) {
   // 113 at 509; too few 256-row tiles to fill the chip, 3840 x 1280: 64-row 22
   // against 37 at 1024, 128-row 48 against 71 at 3072)
   const bool few = tiles256 < 256;
-  if (!tile) tile = tiles64 <= 512 || d.K <= (few ? 1536 : 640) ? 64 : few || d.K < 768 ? 128 : 256;
+  if (!tile) tile = tiles64 <= 512 || d.K <= (few ? 1536 : 300) ? 64 : few || d.K <= 600 ? 128 : 256;
   if (tile == 256) return launch_tile<false, false, EPI_ACC_F32, Tile256>(a, st);
   if (tile == 128) return launch_tile<false, false, EPI_ACC_F32, Tile128w>(a, st);
   if (tiles64 <= 512) return launch_tile<false, false, EPI_ACC_F32, Tile64>(a, st);
