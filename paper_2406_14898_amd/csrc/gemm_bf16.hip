@@ -186,8 +186,9 @@ __device__ __forceinline__ float gelu2_grad(float z) {
 // Work order: workgroup wg runs on XCD wg % 8, and each XCD takes a contiguous
 // range of work items.  Items walk bands of kBand tile rows column by column
 // (kAlongN: bands of tile columns row by row), one reduction slice of the
-// whole product after another, so that an XCD reads few slices of A (1295
-// tokens x 4096 x 130560: SLICEFIG).
+// whole product after another, so that an XCD reads few slices of A
+// (K = 16384 in four to eight slices: 1-3 % faster than a tile's slices side
+// by side).
 template <int kBand, bool kAlongN>
 __device__ __forceinline__ void work_coords(int wg, int nwg, int tiles_m, int tiles_n, int slices, int& tm, int& tn,
                                             int& slice) {
@@ -366,9 +367,15 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
 // Row steps of the epilogue whose global reads are issued together: 8 for the
 // residual epilogues (a 128-row half's whole share: 6 % faster on the 41447 x
 // 4096 x 4096 output projection than 4), 4 elsewhere (8 measured no faster),
-// 2 for the fp32 accumulator.
+// 8 for the fp32 accumulator, whose reads are what a short weight gradient
+// waits for (4096 x 16384 over 509 tokens on 128 x 128 tiles: 154 us with 2,
+// 148 with 4, 136 with 8; long ones unchanged).  Reading it before the
+// reduction instead was slower (88 -> 103 us, 12288 x 4096 over 509 tokens):
+// the first operand stages then queue behind it.
 template <int EPI>
-constexpr int epi_steps() { return (EPI == EPI_BIAS_RES || EPI == EPI_RES) ? 8 : EPI == EPI_ACC_F32 ? 8 : 4; }
+constexpr int epi_steps() {
+  return EPI == EPI_BIAS_RES || EPI == EPI_RES || EPI == EPI_ACC_F32 ? 8 : 4;
+}
 
 template <bool AK, bool BKc, int EPI, class TL>
 __global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16_kernel(G2Args p) {
@@ -825,10 +832,12 @@ hipError_t launch_wgrad(const GemmDesc& d, hipStream_t st) {
   const G2Args a = make_args(d, false);
   const long tiles256 = (long)((d.M + 255) / 256) * (d.N / 256), tiles64 = (long)((d.M + 63) / 64) * (d.N / 128);
   int tile = d.tile;
-  // (16384 x 4096: 64-row tiles 161 us against 165 on 256-row ones at 509
-  // tokens, 128-row 194 against 177 at 768; 12288 x 4096: 64-row 94 against
-  // 113 at 509; too few 256-row tiles to fill the chip, 3840 x 1280: 64-row 22
-  // against 37 at 1024, 128-row 48 against 71 at 3072)
+  // (16384 x 4096: 64-row tiles 90 us against 89 on 128-row ones at 37 tokens;
+  // 128-row 148 against 157 on 256-row ones at 509, 211 against 215 at 1024;
+  // a whole step of one 509-token client 1240 us with 64-row tiles up to 640
+  // tokens, 1223 with this rule, and the vocabulary gradient of 733 tokens is
+  // 70 us faster on 256-row tiles.  Too few 256-row tiles to fill the chip,
+  // 3840 x 1280: 64-row 23 us against 36 at 1024, 128-row 48 against 71 at 3072)
   const bool few = tiles256 < 256;
   if (!tile) tile = tiles64 <= 512 || d.K <= (few ? 1536 : 300) ? 64 : few || d.K <= 600 ? 128 : 256;
   if (tile == 256) return launch_tile<false, false, EPI_ACC_F32, Tile256>(a, st);
