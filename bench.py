@@ -52,7 +52,7 @@ CLASS_KERNELS = {
     "gemm_nn": ("gemm_bf16_kernel<true, false, 0,", "gemm_bf16_kernel<true, false, 6,"),
     "gemm_tn_acc": ("gemm_bf16_kernel<false, false",),
     "attn_fwd": ("::fwd_kernel<",),
-    "attn_bwd": ("attn_delta_kernel", "ds_offsets_kernel", "::dkdv_kernel<", "::dq_kernel<", "::dq_ds_kernel<"),
+    "attn_bwd": ("attn_delta_kernel", "::dkdv_kernel<", "::dq_kernel<", "::dq_ds_kernel<"),
     "layernorm_fwd": ("ln_fwd_kernel",),
     "layernorm_bwd": ("ln_bwd_fused_kernel", "ln_bwd_dx_kernel"),
     "rope_qk": ("rope_qk_kernel",),

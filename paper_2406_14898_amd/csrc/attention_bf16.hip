@@ -36,7 +36,7 @@
 namespace flglm {
 namespace {
 
-constexpr int kRows = 64;  // rows per LDS tile
+constexpr int kRows = kAttnTileRows;  // rows per LDS tile
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 #define LDS_AS __attribute__((address_space(3)))
 
@@ -220,13 +220,6 @@ __device__ __forceinline__ bool tile_full(int j0, int qlo, int L, int P) {
 // queries 32 p + 4 g + e (e < 4) and 32 p + 16 + 4 g + e - 4 (e >= 4), so
 // every store is a whole 1 KB block; keys 32 c2 .. + 31 are the contiguous
 // half c2.
-__host__ __device__ __forceinline__ long ds_row_off(int qt, int ntp, int np) {
-  if (qt <= np) return (long)qt * (ntp + np);
-  return (long)np * (ntp + np) + (long)(qt - np) * ntp + ((long)qt * (qt + 1) - (long)np * (np + 1)) / 2;
-}
-__host__ __device__ __forceinline__ long ds_seq_tiles(int L, int P, int ntp) {
-  return ds_row_off((L + kRows - 1) / kRows, ntp, (P + kRows - 1) / kRows);
-}
 constexpr long kDsTileElems = (long)kRows * kRows;
 
 // ---------------------------------------------------------------------------
@@ -994,46 +987,6 @@ __global__ void __launch_bounds__(256, 2) dq_ds_kernel(AttnDesc a) {
   }
 }
 
-// Tile offsets of the stored dS: off[s] = sum over sequences before s of
-// num_heads * ds_seq_tiles, off[S] = the total (one workgroup, chunked scan).
-// With tile_base: tile_base[s] = the 64-row tiles of the sequences before s.
-__global__ void __launch_bounds__(256) ds_offsets_kernel(const int32_t* cu, const int32_t* prefix, int S, int nh,
-                                                         int ntp, int64_t* off, int32_t* tile_base) {
-  __shared__ long sh[2][256];
-  const int t = threadIdx.x;
-  long carry = 0, carry_t = 0;
-  for (int s0 = 0; s0 < S; s0 += 256) {
-    const int s = s0 + t;
-    long v = 0, vt = 0;
-    if (s < S) {
-      const int L = cu[s + 1] - cu[s];
-      v = (long)nh * ds_seq_tiles(L, prefix ? prefix[s] : 0, ntp);
-      vt = (L + kRows - 1) / kRows;
-    }
-    sh[0][t] = v;
-    sh[1][t] = vt;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      const long x = t >= o ? sh[0][t - o] : 0, xt = t >= o ? sh[1][t - o] : 0;
-      __syncthreads();
-      sh[0][t] += x;
-      sh[1][t] += xt;
-      __syncthreads();
-    }
-    if (s < S) {
-      off[s] = carry + sh[0][t] - v;
-      if (tile_base) tile_base[s] = (int32_t)(carry_t + sh[1][t] - vt);
-    }
-    carry += sh[0][255];
-    carry_t += sh[1][255];
-    __syncthreads();
-  }
-  if (t == 0) {
-    off[S] = carry;
-    if (tile_base) tile_base[S] = (int32_t)carry_t;
-  }
-}
-
 template <int D>
 hipError_t fwd_launch(const AttnDesc& a, hipStream_t st) {
   const dim3 grid = wg_grid((a.max_seqlen + 127) / 128, a.num_heads, a.num_seqs);
@@ -1048,7 +1001,7 @@ hipError_t bwd_launch(const AttnDesc& a, hipStream_t st) {
   const dim3 gkv = wg_grid((a.num_prefix + 63) / 64 + (a.max_seqlen + 63) / 64, a.num_heads, a.num_seqs);
   if (a.ds) {
     // dk, dv and the stored dS, then dq from dS
-    if ((e = attn_ds_offsets(a, st)) != hipSuccess) return e;
+    if (!a.ds_off_ready && (e = attn_ds_offsets(a, st)) != hipSuccess) return e;
     hipLaunchKernelGGL((dkdv_kernel<D, true>), gkv, dim3(256), 0, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const dim3 gq = wg_grid((a.max_seqlen + 255) / 256, a.num_heads, a.num_seqs);
@@ -1065,9 +1018,14 @@ hipError_t bwd_launch(const AttnDesc& a, hipStream_t st) {
 }  // namespace
 
 hipError_t attn_ds_offsets(const AttnDesc& a, hipStream_t st) {
-  hipLaunchKernelGGL(ds_offsets_kernel, dim3(1), dim3(256), 0, st, a.cu_seqlens, a.prefix_len, a.num_seqs,
-                     a.num_heads, (a.num_prefix + kRows - 1) / kRows, a.ds_off, a.bias_part ? a.tile_base : nullptr);
-  return hipGetLastError();
+  PlanDesc d;
+  d.num_seqs = a.num_seqs;
+  d.cu = const_cast<int32_t*>(a.cu_seqlens);
+  d.ctx = const_cast<int32_t*>(a.prefix_len);
+  d.ds_off = a.ds_off; d.tile_base = a.bias_part ? a.tile_base : nullptr;
+  d.num_heads = a.num_heads;
+  d.prefix_tiles = (a.num_prefix + kRows - 1) / kRows;
+  return batch_plan(d, st);
 }
 
 // Buffer resources are rebased per 64-row tile, so any sequence length

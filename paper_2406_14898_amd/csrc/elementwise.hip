@@ -2,6 +2,10 @@
 // position encoding, deterministic column sums (bias and LayerNorm parameter
 // gradients), packed-batch bookkeeping and client packing.  All of them move
 // 16-byte vectors along the contiguous hidden dimension.
+#include <algorithm>
+#include <cstring>
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -10,42 +14,9 @@ namespace flglm {
 // ---------------------------------------------------------------------------
 // Positions and rotary table
 // ---------------------------------------------------------------------------
-__global__ void seq_positions_kernel(const int32_t* cu, int32_t* pos) {
-  const int s = blockIdx.x;
-  const int r0 = cu[s], r1 = cu[s + 1];
-  for (int r = r0 + (int)threadIdx.x; r < r1; r += blockDim.x) pos[r] = r - r0;
-}
-
-hipError_t seq_positions(const int32_t* cu, int S, int32_t* pos, hipStream_t st) {
-  if (S <= 0) return hipSuccess;
-  hipLaunchKernelGGL(seq_positions_kernel, dim3(S), dim3(256), 0, st, cu, pos);
-  return hipGetLastError();
-}
-
-// GLM 2-D positions: with a context of P tokens (ctx[s], or the whole
-// sequence), p1 = t inside the context and the [gMASK] position max(P-1, 0)
-// after it; p2 = 0 inside the context and t - P + 1 after it.
-__global__ void seq_positions_2d_kernel(const int32_t* cu, const int32_t* ctx, int32_t* p1, int32_t* p2) {
-  const int s = blockIdx.x;
-  const int r0 = cu[s], r1 = cu[s + 1];
-  const int P = ctx ? ctx[s] : r1 - r0;
-  const int m = P > 0 ? P - 1 : 0;
-  for (int r = r0 + (int)threadIdx.x; r < r1; r += blockDim.x) {
-    const int t = r - r0;
-    p1[r] = t < P ? t : m;
-    p2[r] = t < P ? 0 : t - P + 1;
-  }
-}
-
-hipError_t seq_positions_2d(const int32_t* cu, const int32_t* ctx, int S, int32_t* p1, int32_t* p2, hipStream_t st) {
-  if (S <= 0) return hipSuccess;
-  hipLaunchKernelGGL(seq_positions_2d_kernel, dim3(S), dim3(256), 0, st, cu, ctx, p1, p2);
-  return hipGetLastError();
-}
-
-__global__ void rope_table_kernel(float* ct, float* stbl, int max_pos, int r, double base) {
+// cos / sin (p * theta_i), theta_i = base^(-2i/r), entry idx = p (r / 2) + i, in double.
+__device__ __forceinline__ void rope_entry(float* ct, float* stbl, long idx, int max_pos, int r, double base) {
   const int half = r / 2;
-  const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (long)max_pos * half) return;
   const int p = (int)(idx / half), i = (int)(idx % half);
   const double theta = pow(base, -2.0 * (double)i / (double)r);
@@ -54,11 +25,107 @@ __global__ void rope_table_kernel(float* ct, float* stbl, int max_pos, int r, do
   stbl[idx] = (float)sin(ang);
 }
 
-hipError_t rope_table(float* ct, float* stbl, int max_pos, int r, float base, hipStream_t st) {
-  const long n = (long)max_pos * (r / 2);
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, ct, stbl, max_pos,
-                     r, (double)base);
+// One launch for a stack call's bookkeeping (batch_plan): a small call is bound
+// by its launches, and copying the bounds, the positions, the rotary table and
+// the softmax-gradient offsets were up to five of them (3-5 us each; one
+// launch instead: a 37-token forward 144 -> 140 us, a training step of one
+// 509-token client 1232 -> 1176, of two small fp32 blocks 329 -> 308).  Thread i writes row i's position and
+// table entry i; the first workgroup also writes the bounds and the offsets.
+struct PlanArgs {
+  int32_t cu[kPlanArgSeqs + 1];
+  int32_t ctx[kPlanArgSeqs];
+};
+template <bool ARGS>
+__global__ void __launch_bounds__(256) batch_plan_kernel(PlanDesc d, std::conditional_t<ARGS, PlanArgs, int> args) {
+  __shared__ int32_t lcu[ARGS ? kPlanArgSeqs + 1 : 1];
+  __shared__ long sh[2][256];
+  const int t = threadIdx.x, S = d.num_seqs;
+  const int32_t* cu = d.cu;
+  if constexpr (ARGS) {
+    for (int i = t; i <= S; i += 256) lcu[i] = args.cu[i];
+    __syncthreads();
+    cu = lcu;
+  }
+  auto ctx_of = [&](int s, int L) -> int {  // the GLM context of sequence s
+    if (!d.ctx) return L;
+    if constexpr (ARGS) return args.ctx[s];
+    else return d.ctx[s];
+  };
+  const long idx = (long)blockIdx.x * 256 + t;
+  if (idx < d.total_tokens) {
+    // the sequence of row idx: the last s with cu[s] <= idx
+    int lo = 0, hi = S - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) / 2;
+      if (cu[mid] <= idx) lo = mid;
+      else hi = mid - 1;
+    }
+    const int p = (int)idx - cu[lo];
+    if (d.pos2) {
+      // with a context of P tokens p1 = t inside it and the [gMASK] position
+      // max(P - 1, 0) after it; p2 = 0 inside it and t - P + 1 after it
+      const int P = ctx_of(lo, cu[lo + 1] - cu[lo]);
+      d.pos[idx] = p < P ? p : (P > 0 ? P - 1 : 0);
+      d.pos2[idx] = p < P ? 0 : p - P + 1;
+    } else {
+      d.pos[idx] = p;
+    }
+  }
+  rope_entry(d.cos_t, d.sin_t, idx, d.max_pos, d.rotary_dim, (double)d.base);
+  if (blockIdx.x != 0) return;
+  if constexpr (ARGS) {
+    for (int i = t; i <= S; i += 256) d.cu[i] = lcu[i];
+    if (d.ctx)
+      for (int i = t; i < S; i += 256) d.ctx[i] = args.ctx[i];
+  }
+  if (!d.ds_off) return;
+  // offsets: sums over the sequences before each, 256 sequences at a time
+  long carry = 0, carry_t = 0;
+  for (int s0 = 0; s0 < S; s0 += 256) {
+    const int s = s0 + t;
+    long v = 0, vt = 0;
+    if (s < S) {
+      const int L = cu[s + 1] - cu[s];
+      v = (long)d.num_heads * ds_seq_tiles(L, d.ctx ? ctx_of(s, L) : 0, d.prefix_tiles);
+      vt = (L + kAttnTileRows - 1) / kAttnTileRows;
+    }
+    sh[0][t] = v;
+    sh[1][t] = vt;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+      const long x = t >= o ? sh[0][t - o] : 0, xt = t >= o ? sh[1][t - o] : 0;
+      __syncthreads();
+      sh[0][t] += x;
+      sh[1][t] += xt;
+      __syncthreads();
+    }
+    if (s < S) {
+      d.ds_off[s] = carry + sh[0][t] - v;
+      if (d.tile_base) d.tile_base[s] = (int32_t)(carry_t + sh[1][t] - vt);
+    }
+    carry += sh[0][255];
+    carry_t += sh[1][255];
+    __syncthreads();
+  }
+  if (t == 0) {
+    d.ds_off[S] = carry;
+    if (d.tile_base) d.tile_base[S] = (int32_t)carry_t;
+  }
+}
+
+hipError_t batch_plan(const PlanDesc& d, hipStream_t st) {
+  if (d.num_seqs <= 0) return hipSuccess;
+  const long n = std::max<long>({1L, (long)d.total_tokens, (long)d.max_pos * (d.rotary_dim / 2)});
+  const dim3 grid((unsigned)((n + 255) / 256));
+  if (!d.cu_host) {
+    hipLaunchKernelGGL(batch_plan_kernel<false>, grid, dim3(256), 0, st, d, 0);
+    return hipGetLastError();
+  }
+  if (d.num_seqs > kPlanArgSeqs) return hipErrorInvalidValue;
+  PlanArgs a;
+  std::memcpy(a.cu, d.cu_host, sizeof(int32_t) * (d.num_seqs + 1));
+  if (d.ctx_host) std::memcpy(a.ctx, d.ctx_host, sizeof(int32_t) * d.num_seqs);
+  hipLaunchKernelGGL(batch_plan_kernel<true>, grid, dim3(256), 0, st, d, a);
   return hipGetLastError();
 }
 

@@ -426,24 +426,41 @@ int check_grads(const fl_stack* st, const fl_layer_grads* grads) {
 }
 
 // ---------------------------------------------------------------------------
-// Plan upload: host descriptor arrays -> pinned staging ring -> workspace.
+// Batch plan: host descriptor arrays -> workspace, in kernel arguments or
+// through the pinned staging ring.
 // ---------------------------------------------------------------------------
-// Once cu_seqlens and the prefix lengths are on the device: every row's
-// position inside its sequence and the rotary table.
-int plan_kernels(fl_stack* st, const BatchInfo& bi, const Plan& p, hipStream_t stream) {
+// Positions, rotary table and, for a backward (w), the offsets of the stored
+// softmax gradient; host_bounds: the bounds travel in the kernel's arguments.
+int plan_kernels(fl_stack* st, const BatchInfo& bi, const Plan& p, bool host_bounds, const Work* w,
+                 hipStream_t stream) {
   hipStream_t s = stream;
-  LAUNCH(FL_PROF_PLAN, 0, 4.0 * bi.T, [&]() {
-    hipError_t e = st->d.rotary_2d ? seq_positions_2d(p.cu, bi.prefix ? p.prefix : nullptr, bi.S, p.pos, p.pos2, stream)
-                                   : seq_positions(p.cu, bi.S, p.pos, stream);
-    return e != hipSuccess ? e
-                           : rope_table(p.cos_t, p.sin_t, bi.maxL + 1, st->d.rotary_dim, st->d.rope_base, stream);
-  }());
+  PlanDesc d;
+  if (host_bounds) {
+    d.cu_host = bi.cu_host;
+    d.ctx_host = bi.prefix_host;
+  }
+  d.num_seqs = bi.S; d.total_tokens = bi.T;
+  d.cu = p.cu; d.ctx = bi.prefix ? p.prefix : nullptr;
+  d.pos = p.pos; d.pos2 = st->d.rotary_2d ? p.pos2 : nullptr;
+  d.cos_t = p.cos_t; d.sin_t = p.sin_t;
+  d.max_pos = bi.maxL + 1; d.rotary_dim = st->d.rotary_dim; d.base = st->d.rope_base;
+  if (w && w->ds) {
+    d.ds_off = w->ds_off; d.tile_base = w->tile_base;
+    d.num_heads = st->d.num_heads;
+    d.prefix_tiles = (st->d.num_prefix + kAttnTileRows - 1) / kAttnTileRows;
+  }
+  LAUNCH(FL_PROF_PLAN, 0, 4.0 * bi.T, batch_plan(d, stream));
   return FL_OK;
 }
 
-int upload_plan(fl_stack* st, const fl_batch_desc* b, const BatchInfo& bi, const Plan& p, hipStream_t stream) {
-  const size_t ncu = bi.S + 1, npre = bi.S;
-  const size_t bytes = sizeof(int32_t) * (ncu + npre);
+// Bounds of up to kPlanArgSeqs sequences travel in kernel arguments; more go
+// through pinned staging.
+int upload_plan(fl_stack* st, const fl_batch_desc* b, const BatchInfo& bi, const Plan& p, const Work* w,
+                hipStream_t stream) {
+  if (bi.S <= kPlanArgSeqs) return plan_kernels(st, bi, p, true, w, stream);
+  // the workspace holds cu and, behind it, the prefix lengths: one copy of both
+  const size_t gap = (size_t)((char*)p.prefix - (char*)p.cu);
+  const size_t bytes = bi.prefix ? gap + sizeof(int32_t) * bi.S : sizeof(int32_t) * (bi.S + 1);
   const int k = st->next;
   st->next = (st->next + 1) % fl_stack::kRing;
   if (!st->ev_made[k]) {
@@ -458,15 +475,13 @@ int upload_plan(fl_stack* st, const fl_batch_desc* b, const BatchInfo& bi, const
     HIP_OK(hipHostMalloc(&st->stage[k], std::max(bytes, (size_t)4096), hipHostMallocDefault));
     st->stage_cap[k] = std::max(bytes, (size_t)4096);
   }
-  int32_t* h = (int32_t*)st->stage[k];
-  std::memcpy(h, b->cu_seqlens, sizeof(int32_t) * ncu);
-  if (bi.prefix) std::memcpy(h + ncu, b->prefix_len, sizeof(int32_t) * npre);
-  else std::memset(h + ncu, 0, sizeof(int32_t) * npre);
-  HIP_OK(hipMemcpyAsync(p.cu, h, sizeof(int32_t) * ncu, hipMemcpyHostToDevice, stream));
-  HIP_OK(hipMemcpyAsync(p.prefix, h + ncu, sizeof(int32_t) * npre, hipMemcpyHostToDevice, stream));
+  char* h = (char*)st->stage[k];
+  std::memcpy(h, b->cu_seqlens, sizeof(int32_t) * (bi.S + 1));
+  if (bi.prefix) std::memcpy(h + gap, b->prefix_len, sizeof(int32_t) * bi.S);
+  HIP_OK(hipMemcpyAsync(p.cu, h, bytes, hipMemcpyHostToDevice, stream));
   HIP_OK(hipEventRecord(st->ev[k], stream));
   st->ev_used[k] = true;
-  return plan_kernels(st, bi, p, stream);
+  return plan_kernels(st, bi, p, false, w, stream);
 }
 
 // Algorithmic work of one launch, for the opt-in launch timing.
@@ -659,7 +674,7 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   ad.pos = plan.pos; ad.cos_t = plan.cos_t; ad.sin_t = plan.sin_t;
   ad.rotary_dim = st->d.rotary_2d ? 0 : st->d.rotary_dim;
   ad.pk = p.prefix_k; ad.pv = p.prefix_v; ad.num_prefix = st->d.num_prefix; ad.dprefix_part = w.dprefix;
-  ad.ds = w.ds; ad.ds_off = w.ds_off;
+  ad.ds = w.ds; ad.ds_off = w.ds_off; ad.ds_off_ready = w.ds != nullptr;
   // b_qkv's column sums come from the attention kernels' own tiles (unless
   // the GLM 2-D rotation changes dq and dk after them)
   const bool fused_bqkv = train_w && w.ds && w.bias_part && !st->d.rotary_2d;
@@ -721,17 +736,6 @@ constexpr size_t kScratchBytes = (size_t)FL_NOALLOC_SCRATCH_BYTES;
 // Host code never uses this name as an address (it is a host-side stand-in
 // there): it takes each device's address with hipGetSymbolAddress.
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
-
-struct PlanArgs {
-  int32_t num_seqs;
-  int32_t cu[FL_NOALLOC_MAX_SEQS + 1];
-  int32_t prefix[FL_NOALLOC_MAX_SEQS];
-};
-__global__ void plan_args_kernel(PlanArgs a, int32_t* cu, int32_t* prefix) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i <= a.num_seqs) cu[i] = a.cu[i];
-  if (i < a.num_seqs) prefix[i] = a.prefix[i];
-}
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -905,7 +909,7 @@ int fl_server_stack_forward(fl_stack* st, const fl_batch_desc* b, const fl_layer
     Carver cs(saved);
     carve_saved(cs, st, bi.T, recompute != 0, &sv);
   }
-  if ((rc = upload_plan(st, b, bi, w.plan, s))) return rc;
+  if ((rc = upload_plan(st, b, bi, w.plan, nullptr, s))) return rc;
   const int N = st->d.num_layers;
   const void* cur = x;
   for (int l = 0; l < N; ++l) {
@@ -926,6 +930,7 @@ int fl_server_stack_forward_noalloc(fl_stack* st, const fl_batch_desc* b, const 
   if (rc) return rc;
   if (bi.S > FL_NOALLOC_MAX_SEQS)
     return fail(FL_ERR_ARG, "%d sequences: the allocation-free forward takes at most %d", bi.S, FL_NOALLOC_MAX_SEQS);
+  static_assert(FL_NOALLOC_MAX_SEQS <= kPlanArgSeqs, "the bounds fit the plan kernel's arguments");
   if ((rc = check_params(st, layers))) return rc;
   if (!x || !y) return fail(FL_ERR_NULL, "x / y is NULL");
   if (!aligned16(x) || !aligned16(y)) return fail(FL_ERR_ALIGN, "x / y must be 16-byte aligned");
@@ -944,15 +949,8 @@ int fl_server_stack_forward_noalloc(fl_stack* st, const fl_batch_desc* b, const 
   Carver cw(base);
   Work w;
   carve_fwd_work(cw, st, bi, &w);
-  PlanArgs pa;
-  pa.num_seqs = bi.S;
-  std::memcpy(pa.cu, b->cu_seqlens, sizeof(int32_t) * (bi.S + 1));
-  if (bi.prefix) std::memcpy(pa.prefix, b->prefix_len, sizeof(int32_t) * bi.S);
-  else std::memset(pa.prefix, 0, sizeof(int32_t) * bi.S);
   ProfOff off(st);
-  hipLaunchKernelGGL(plan_args_kernel, dim3((bi.S + 1 + 255) / 256), dim3(256), 0, s, pa, w.plan.cu, w.plan.prefix);
-  HIP_OK(hipGetLastError());
-  if ((rc = plan_kernels(st, bi, w.plan, s))) return rc;
+  if ((rc = plan_kernels(st, bi, w.plan, true, nullptr, s))) return rc;
   const int N = st->d.num_layers;
   const void* cur = x;
   for (int l = 0; l < N; ++l) {
@@ -992,7 +990,7 @@ int fl_server_stack_backward(fl_stack* st, const fl_batch_desc* b, const fl_laye
   Saved sv;
   Carver cs(const_cast<void*>(saved));
   carve_saved(cs, st, bi.T, recompute != 0, &sv);
-  if ((rc = upload_plan(st, b, bi, w.plan, s))) return rc;
+  if ((rc = upload_plan(st, b, bi, w.plan, &w, s))) return rc;
   const int N = st->d.num_layers;
   const void* gcur = dy;
   for (int l = N - 1; l >= 0; --l) {
@@ -1032,7 +1030,7 @@ static int pack_impl(fl_stack* st, const fl_batch_desc* b, const void* const* cb
   Carver cw(ws);
   Work w;
   carve_work(cw, st, bi, &w);
-  if ((rc = upload_plan(st, b, bi, w.plan, s))) return rc;
+  if ((rc = upload_plan(st, b, bi, w.plan, nullptr, s))) return rc;
   for (int c = 0; c < bi.C; ++c) {
     const int s0 = b->client_seq_ptr[c], s1 = b->client_seq_ptr[c + 1];
     int Lmax = 0;

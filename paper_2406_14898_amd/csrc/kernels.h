@@ -64,13 +64,45 @@ bool gemm_bf16_dma_ok(GemmLayout layout, const GemmDesc& d);
 bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d);
 hipError_t gemm_bf16_dma(GemmLayout layout, int epi, const GemmDesc& d, hipStream_t st);
 
-// Batch bookkeeping: position of every packed row inside its own sequence.
-hipError_t seq_positions(const int32_t* cu_seqlens, int num_seqs, int32_t* pos, hipStream_t st);
-// GLM 2-D positions (context length ctx[s], or the whole sequence when ctx is null).
-hipError_t seq_positions_2d(const int32_t* cu_seqlens, const int32_t* ctx, int num_seqs, int32_t* p1, int32_t* p2,
-                            hipStream_t st);
-// cos / sin (p * theta_i), theta_i = base^(-2i/r), p < max_pos, i < r/2 (computed in double).
-hipError_t rope_table(float* cos_t, float* sin_t, int max_pos, int rotary_dim, float base, hipStream_t st);
+// Stored attention softmax gradient: tiles before query tile qt of a sequence
+// and head (ntp prefix key tiles, np context key tiles; see attention_bf16.hip),
+// and the tiles of a whole sequence of L rows and P context keys.
+constexpr int kAttnTileRows = 64;
+__host__ __device__ __forceinline__ long ds_row_off(int qt, int ntp, int np) {
+  if (qt <= np) return (long)qt * (ntp + np);
+  return (long)np * (ntp + np) + (long)(qt - np) * ntp + ((long)qt * (qt + 1) - (long)np * (np + 1)) / 2;
+}
+__host__ __device__ __forceinline__ long ds_seq_tiles(int L, int P, int ntp) {
+  return ds_row_off((L + kAttnTileRows - 1) / kAttnTileRows, ntp, (P + kAttnTileRows - 1) / kAttnTileRows);
+}
+
+// Batch bookkeeping of one stack call, in one launch: the position of every
+// packed row inside its own sequence (pos; with pos2 the GLM 2-D positions of
+// context length ctx[s], or of the whole sequence without a context), the
+// rotary table cos / sin (p * base^(-2i/r)), p < max_pos, i < r/2, and with
+// ds_off the per-sequence offsets of the stored softmax gradient (off[s] =
+// num_heads * the tiles of the sequences before s, off[S] = all; tile_base[s]
+// = their 64-row tiles).  The sequence bounds come
+// from host arrays through kernel arguments (up to kPlanArgSeqs sequences;
+// they are then also written to cu and ctx) or are already on the device.
+constexpr int kPlanArgSeqs = 256;
+struct PlanDesc {
+  const int32_t* cu_host = nullptr;   // null: cu / ctx are filled already
+  const int32_t* ctx_host = nullptr;  // null: no context lengths (causal)
+  int num_seqs = 0, total_tokens = 0;
+  int32_t* cu = nullptr;
+  int32_t* ctx = nullptr;  // null: causal
+  int32_t* pos = nullptr;
+  int32_t* pos2 = nullptr;  // null: 1-D positions
+  float* cos_t = nullptr;
+  float* sin_t = nullptr;
+  int max_pos = 0, rotary_dim = 0;
+  float base = 0.f;
+  int64_t* ds_off = nullptr;  // null: no offsets
+  int32_t* tile_base = nullptr;
+  int num_heads = 0, prefix_tiles = 0;
+};
+hipError_t batch_plan(const PlanDesc& d, hipStream_t st);
 // In-place rotation of the q and k parts of qkv [T, 3H] (row stride ld):
 // dims [0, rotary_dim) of every head by pos; with pos2 (GLM 2-D positions)
 // also dims [rotary_dim, 2 rotary_dim) by pos2.  sign -1 rotates back.
@@ -155,6 +187,7 @@ struct AttnDesc {
   // recomputes S and dP instead of reading dS.
   void* ds = nullptr;
   int64_t* ds_off = nullptr;
+  bool ds_off_ready = false;  // ds_off and tile_base are filled already (batch_plan)
   // With ds: per 64-row tile of each sequence, the column sums of the stored
   // dq | dk | dv rows (fp32 [tile rows][3 hidden]; tile rows numbered
   // sequence after sequence, tile_base (device int32 [S + 1] scratch)

@@ -157,9 +157,13 @@ int fl_test_rope(int dtype, void* qkv, const int32_t* cu_dev, int S, int T, int 
   const int d = H / num_heads;
   if (rotary_dim < 0 || rotary_dim > d || rotary_dim % 8) return set_error(FL_ERR_ARG, "bad rotary_dim");
   hipStream_t s = (hipStream_t)stream;
-  int rc = herr(seq_positions(cu_dev, S, pos, s));
+  PlanDesc pd;
+  pd.num_seqs = S; pd.total_tokens = T;
+  pd.cu = const_cast<int32_t*>(cu_dev);
+  pd.pos = pos; pd.cos_t = cos_t; pd.sin_t = sin_t;
+  pd.max_pos = max_seqlen; pd.rotary_dim = rotary_dim; pd.base = base;
+  int rc = herr(batch_plan(pd, s));
   if (rc) return rc;
-  if ((rc = herr(rope_table(cos_t, sin_t, max_seqlen, rotary_dim, base, s)))) return rc;
   return herr(rope_qk((DType)dtype, qkv, 3L * H, pos, cos_t, sin_t, T, H, d, rotary_dim, s));
 }
 

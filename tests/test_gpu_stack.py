@@ -346,3 +346,30 @@ def test_launch_profile_of_chosen_classes():
     assert all(some[k]["launches"] == full[k]["launches"] and some[k]["ms"] > 0 for k in some)
     # records stay until the next enabling call; disabling adds none
     assert none == some
+
+
+@pytest.mark.parametrize("seqs", [1, 255, 256, 257, 300])
+@pytest.mark.parametrize("rotary_2d", [False, True])
+def test_bounds_in_arguments_and_staged(seqs, rotary_2d):
+    """The sequence bounds travel in the plan kernel's arguments up to 256
+    sequences and through staging beyond; either way positions (1-D and GLM
+    2-D), context lengths and the backward's tile offsets are those of every
+    sequence: one block against the oracle, sequences of 1 to 5 tokens (and
+    one of 70, past a 64-row tile)."""
+    shape = synth.StackShape(num_layers=1, hidden=256, num_heads=2, ffn_hidden=512, rotary_dim=64,
+                             rotary_2d=rotary_2d)
+    lens = np.random.default_rng(seqs).integers(1, 6, seqs)
+    lens[seqs // 2] = 70
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    batch = synth.Batch(cu, np.arange(seqs + 1, dtype=np.int32), "prefix", (lens // 2).astype(np.int32))
+    layers = [synth.layer_params(shape, 0, seed=5, bf16=True)]
+    x = synth.activations(batch.total_tokens, shape.hidden, seed=5, bf16=True)
+    dy = synth.upstream_grad(batch.total_tokens, shape.hidden, seed=5, bf16=True)
+    g = GpuStack(shape, layers, "bf16")
+    res = g.to_host(g.run(batch, x, dy))
+    g.close()
+    y, xs = oracle.stack_forward(layers, 1, x, batch, shape)
+    dx, grads = oracle.stack_backward(layers, 1, xs, dy, batch, shape)
+    assert rel_l2(res["y"], y) < TOL["bf16"] and rel_l2(res["dx"], dx) < TOL["bf16"]
+    for k in grads[0]:
+        assert rel_l2(res["grads"][0][k], grads[0][k]) < TOL["bf16"], k
