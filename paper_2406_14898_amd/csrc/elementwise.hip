@@ -243,6 +243,56 @@ __global__ void __launch_bounds__(256) ln_fwd_kernel(const T* x, const T* g, con
   if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
 }
 
+// LayerNorm of few rows: one workgroup per row (one 8-element chunk per lane,
+// H <= 8 NT), gain and shift loaded with the row.  One wave per row leaves most
+// of the chip idle there and is a chain of eight chunks and two passes (H
+// 4096: 37 rows 5.1 -> 3.2 us, 509 rows 5.6 -> 4.0).
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT) ln_fwd_row_kernel(const T* x, const T* g, const T* b, T* y, float* mean,
+                                                        float* rstd, int H, float eps) {
+  __shared__ float red[2][NT / 64];
+  const int row = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = threadIdx.x * 8;
+  const bool on = c < H;
+  Vec8<T> v, gg, bb;
+  if (on) {
+    v.load(x + (long)row * H + c);
+    gg.load(g + c);
+    bb.load(b + c);
+  } else {
+    v.zero();
+    gg.zero();
+    bb.zero();
+  }
+  auto total = [&](float s, int k) {  // sum over the workgroup, waves in order
+    s = wave_sum(s);
+    if (lane == 0) red[k][w] = s;
+    __syncthreads();
+    float t = red[k][0];
+#pragma unroll
+    for (int i = 1; i < NT / 64; ++i) t += red[k][i];
+    return t;
+  };
+  float s = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s += v.get(e);
+  const float mu = total(s, 0) / (float)H;
+  float ss = 0.f;
+  if (on) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { const float dlt = v.get(e) - mu; ss += dlt * dlt; }
+  }
+  const float rs = 1.0f / sqrtf(total(ss, 1) / (float)H + eps);
+  if (on) {
+    Vec8<T> o;
+    float out[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) out[e] = (v.get(e) - mu) * rs * gg.get(e) + bb.get(e);
+    o.set(out);
+    o.store(y + (long)row * H + c);
+  }
+  if (threadIdx.x == 0) { mean[row] = mu; rstd[row] = rs; }
+}
+
 template <typename T, int MAXC>
 __global__ void __launch_bounds__(256) ln_bwd_dx_kernel(const T* dy, const T* x, const float* mean,
                                                         const float* rstd, const T* g, const T* dres, T* dx, int T_,
@@ -297,6 +347,17 @@ static hipError_t ln_fwd_t(const void* x, const void* g, const void* b, void* y,
                            int H, float eps, hipStream_t st) {
   dim3 grid((T_ + 3) / 4), blk(256);
   const int nch = H / 8;
+  // (H 4096, us: 1024 rows 5.4 against 6.3 with a wave per row, 2048 rows 8.8
+  // against 8.3; H 1280 3.5 / 3.9 and 4.6 / 4.5)
+  if (nch > 64 && nch <= 512 && T_ <= 1536) {
+    if (nch <= 256)
+      hipLaunchKernelGGL((ln_fwd_row_kernel<T, 256>), dim3(T_), dim3(256), 0, st, (const T*)x, (const T*)g,
+                         (const T*)b, (T*)y, mean, rstd, H, eps);
+    else
+      hipLaunchKernelGGL((ln_fwd_row_kernel<T, 512>), dim3(T_), dim3(512), 0, st, (const T*)x, (const T*)g,
+                         (const T*)b, (T*)y, mean, rstd, H, eps);
+    return hipGetLastError();
+  }
   if (nch <= 64)
     hipLaunchKernelGGL((ln_fwd_kernel<T, 1>), grid, blk, 0, st, (const T*)x, (const T*)g, (const T*)b, (T*)y, mean,
                        rstd, T_, H, eps);
@@ -346,8 +407,11 @@ hipError_t layernorm_bwd_dx(DType dt, const void* dy, const void* x, const float
 
 // ---------------------------------------------------------------------------
 // LayerNorm backward fused with the column sums that follow it.  Workgroup b
-// of kLnBlocks takes rows [T b / kLnBlocks, T (b + 1) / kLnBlocks) (an even
-// share, so the grid is one balanced round) across all H columns: wave w
+// of B = ln_blocks(T) takes rows [T b / B, T (b + 1) / B) (an even share, so
+// the grid is one balanced round; below 2048 rows four rows each, so that the
+// B rows of partial sums stay a fraction of the data: with 512 workgroups a
+// 509-row call wrote and read 25 MB of them: 27 us with its three finishes, now
+// 16) across all H columns: wave w
 // owns columns [512 w, 512 w + 512), eight per lane, so each row read is one
 // contiguous 1 KB segment per wave.  Rows go four at a time; a row's two
 // sums (of dxh and dxh * xh) are combined over the waves through LDS in wave
@@ -368,7 +432,7 @@ __global__ void __launch_bounds__(512, sizeof(T) == 2 ? 4 : 2)
   const int col = w * 512 + lane * 8;
   const bool on = col < H;
   const int nw = (H + 511) / 512;  // waves holding columns
-  const int r0 = (int)((long)T_ * blockIdx.x / kLnBlocks), r1 = (int)((long)T_ * (blockIdx.x + 1) / kLnBlocks);
+  const int r0 = (int)((long)T_ * blockIdx.x / gridDim.x), r1 = (int)((long)T_ * (blockIdx.x + 1) / gridDim.x);
   float gv[8], ag[8], ab[8], ao[8];
   {
     Vec8<T> gg;
@@ -479,7 +543,7 @@ hipError_t layernorm_bwd_fused(DType dt, const void* dy, const void* x, const fl
                                float* pout, hipStream_t st) {
   if (T_ <= 0) return hipSuccess;
   if (H > 4096 || H % 8 != 0 || (pg == nullptr) != (pb == nullptr)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)kLnBlocks), blk(512);
+  const dim3 grid((unsigned)ln_blocks(T_)), blk(512);
   if (dt == DT_BF16) {
     hipLaunchKernelGGL((ln_bwd_fused_kernel<bf16, 2>), grid, blk, 0, st, (const bf16*)dy, (const bf16*)x, mean, rstd,
                        (const bf16*)g, (const bf16*)dres, (bf16*)dx, T_, H, pg, pb, pout);
@@ -577,6 +641,58 @@ hipError_t colsum_partial(DType dt, int mode, const void* X, long ldx, const voi
       hipLaunchKernelGGL((colsum_partial_kernel<float, 1>), grid, blk, 0, st, (const float*)X, ldx,
                          (const float*)Y, mean, rstd, T_, N, part, part2);
   }
+  return hipGetLastError();
+}
+
+// Column sums of few rows in one launch: out[n] += sum_t X[t][n].  A workgroup
+// takes 64 columns (eight lanes of eight columns, 128 rows at a time); a lane's
+// rows in order, then the eight rows of a wave, then the waves in order.  The
+// two-stage form above is a chain of 64 rows per wave and a second launch (N
+// 4096: 256 rows 7.0 -> 3.4 us, 1024 rows 7.0 -> 3.9).
+template <typename T>
+__global__ void __launch_bounds__(1024) colsum_direct_kernel(const T* X, long ldx, int T_, float* out) {
+  __shared__ float sh[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int col = blockIdx.x * 64 + (lane & 7) * 8;
+  float a[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] = 0.f;
+  for (int r = w * 8 + (lane >> 3); r < T_; r += 512) {
+    Vec8<T> v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (r + 128 * u < T_) v[u].load(X + (long)(r + 128 * u) * ldx + col);
+      else v[u].zero();
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e] += v[u].get(e);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) a[e] += __shfl_xor(a[e], o, 64);
+  }
+  if (lane < 8) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sh[w][lane * 8 + e] = a[e];
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    float t = sh[0][threadIdx.x];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) t += sh[v][threadIdx.x];
+    out[(long)blockIdx.x * 64 + threadIdx.x] += t;
+  }
+}
+
+hipError_t colsum_direct(DType dt, const void* X, long ldx, int T_, int N, float* out, hipStream_t st) {
+  if (T_ <= 0 || N <= 0) return hipSuccess;
+  if (N % 64 != 0) return hipErrorInvalidValue;
+  if (dt == DT_BF16)
+    hipLaunchKernelGGL((colsum_direct_kernel<bf16>), dim3(N / 64), dim3(1024), 0, st, (const bf16*)X, ldx, T_, out);
+  else
+    hipLaunchKernelGGL((colsum_direct_kernel<float>), dim3(N / 64), dim3(1024), 0, st, (const float*)X, ldx, T_, out);
   return hipGetLastError();
 }
 

@@ -556,10 +556,12 @@ int block_forward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const fl_
   return FL_OK;
 }
 
-// out[n] += sum_t X[t][n] (two-stage, deterministic).
+// out[n] += sum_t X[t][n] (deterministic; two stages from kColsumDirectRows
+// rows on).
 int colsum_into(fl_stack* st, DType dt, const void* X, long ldx, int T, int N, float* out, const Work& w,
                 hipStream_t s) {
   LAUNCH(FL_PROF_COLSUM, 0, (double)T * N * st->E, [&]() {
+    if (T <= kColsumDirectRows) return colsum_direct(dt, X, ldx, T, N, out, s);
     hipError_t e = colsum_partial(dt, 0, X, ldx, nullptr, nullptr, nullptr, T, N, w.part, nullptr, s);
     return e != hipSuccess ? e : colsum_finish(w.part, colsum_blocks(T), N, out, s);
   }());
@@ -578,7 +580,8 @@ int ln_backward(fl_stack* st, DType dt, const void* dy, const void* xin, const f
          layernorm_bwd_fused(dt, dy, xin, mean, rstd, gamma, dres, dx, T, H, dgamma ? w.lnp[0] : nullptr,
                              dgamma ? w.lnp[1] : nullptr, dsum ? w.lnp[2] : nullptr, s));
   if (!dgamma && !dsum) return FL_OK;
-  LAUNCH(FL_PROF_COLSUM, 0, 4.0 * kLnBlocks * H * ((dgamma ? 2 : 0) + (dsum ? 1 : 0)), [&]() {
+  const int nblk = ln_blocks(T);
+  LAUNCH(FL_PROF_COLSUM, 0, 4.0 * nblk * H * ((dgamma ? 2 : 0) + (dsum ? 1 : 0)), [&]() {
     const float* parts[3];
     float* outs[3];
     int n = 0;
@@ -587,7 +590,7 @@ int ln_backward(fl_stack* st, DType dt, const void* dy, const void* xin, const f
       parts[n] = w.lnp[1]; outs[n++] = dbeta;
     }
     if (dsum) { parts[n] = w.lnp[2]; outs[n++] = dsum; }
-    return colsum_finish_n(parts, outs, n, kLnBlocks, H, s);
+    return colsum_finish_n(parts, outs, n, nblk, H, s);
   }());
   return FL_OK;
 }
@@ -623,10 +626,13 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   g.Z = a.z; g.ldz = F;
   // db_1 = column sums of dz: formed per 256-row tile in the GEMM's epilogue
   // where the kernel supports it (no second pass over dz), else below
-  const bool b1_fused = train_w && gemm_fuses_colsum(dt, GEMM_NN, EPI_GELU_BWD, g);
+  // (few rows: only where that costs no pass of its own)
+  with_part(g, plan);
+  const bool b1_fused = train_w && gemm_fuses_colsum(dt, GEMM_NN, EPI_GELU_BWD, g) &&
+                        (T > kColsumDirectRows || gemm_epilogue_colsum(g));
   if (b1_fused) g.colsum = w.part;
   LAUNCH(FL_PROF_GEMM_NN_GELU_BWD, gemm_flops(T, F, H), gemm_bytes(T, F, H, E, 2 * E),
-         gemm(dt, GEMM_NN, EPI_GELU_BWD, with_part(g, plan), s));
+         gemm(dt, GEMM_NN, EPI_GELU_BWD, g, s));
   // z = w W_1^T + b_1
   if (train_w) {
     if (b1_fused) {

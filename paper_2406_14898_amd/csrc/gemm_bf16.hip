@@ -870,6 +870,11 @@ bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d) 
          gemm_bf16_dma_ok(layout, d);
 }
 
+bool gemm_epilogue_colsum(const GemmDesc& d) {
+  GemmPart parts[2];
+  return plan_rows(d, parts) == 1 && parts[0].tile == 256 && parts[0].slices == 1;
+}
+
 hipError_t gemm_bf16_dma(GemmLayout layout, int epi, const GemmDesc& d, hipStream_t st) {
   switch (layout) {
     case GEMM_NT:

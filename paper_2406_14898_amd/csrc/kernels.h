@@ -62,6 +62,8 @@ bool gemm_bf16_dma_ok(GemmLayout layout, const GemmDesc& d);
 // Whether gemm() fills d.colsum for this call (bf16 GeLU' input-gradient
 // GEMMs on the LDS-DMA kernel); otherwise the caller sums the columns itself.
 bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d);
+// Whether it does so in the product's own epilogue, without another pass.
+bool gemm_epilogue_colsum(const GemmDesc& d);
 hipError_t gemm_bf16_dma(GemmLayout layout, int epi, const GemmDesc& d, hipStream_t st);
 
 // Stored attention softmax gradient: tiles before query tile qt of a sequence
@@ -119,11 +121,12 @@ hipError_t layernorm_bwd_dx(DType dt, const void* dy, const void* x, const float
                             const void* g, const void* dres, void* dx, int T, int H, hipStream_t st);
 
 // LayerNorm backward fused with its column sums: dx as layernorm_bwd_dx, and
-// per block of rows (kLnBlocks blocks of T / kLnBlocks rows; partials
-// [kLnBlocks][H] fp32, completed by colsum_finish): pg, pb = the gain / shift
+// per block of rows (ln_blocks(T) blocks of an even share of the rows;
+// partials [ln_blocks(T)][H] fp32, completed by colsum_finish): pg, pb = the gain / shift
 // gradient sums (sum dy * xh, sum dy; both or neither), pout = the sum of
 // the stored dx (or null).  H <= 4096.
-constexpr int kLnBlocks = 512;
+constexpr int kLnBlocks = 512;  // at most
+inline int ln_blocks(int T) { return T >= 4 * kLnBlocks ? kLnBlocks : (T + 3) / 4; }
 hipError_t layernorm_bwd_fused(DType dt, const void* dy, const void* x, const float* mean, const float* rstd,
                                const void* g, const void* dres, void* dx, int T, int H, float* pg, float* pb,
                                float* pout, hipStream_t st);
@@ -139,6 +142,10 @@ inline int colsum_blocks(int T) { return (T + kColsumRows - 1) / kColsumRows; }
 hipError_t colsum_partial(DType dt, int mode, const void* X, long ldx, const void* Y, const float* mean,
                           const float* rstd, int T, int N, float* partial, float* partial2, hipStream_t st);
 hipError_t colsum_finish(const float* partial, int nblk, int N, float* out, hipStream_t st);
+// The column sums of X in one launch, for up to kColsumDirectRows rows (N a
+// multiple of 64): out[n] += sum_t X[t][n].
+constexpr int kColsumDirectRows = 2048;
+hipError_t colsum_direct(DType dt, const void* X, long ldx, int T, int N, float* out, hipStream_t st);
 // colsum_finish of up to three partial arrays of one shape in one launch.
 hipError_t colsum_finish_n(const float* const* partials, float* const* outs, int count, int nblk, int N,
                            hipStream_t st);

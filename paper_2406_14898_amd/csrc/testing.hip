@@ -127,9 +127,9 @@ int fl_test_layernorm_bwd_fused(int dtype, const void* dy, const void* x, const 
   float* pb = dgamma ? partial + (size_t)kLnBlocks * H : nullptr;
   float* po = dsum ? partial + (size_t)2 * kLnBlocks * H : nullptr;
   int rc = herr(layernorm_bwd_fused((DType)dtype, dy, x, mean, rstd, g, dres, dx, T, H, pg, pb, po, s));
-  if (!rc && dgamma) rc = herr(colsum_finish(pg, kLnBlocks, H, dgamma, s));
-  if (!rc && dgamma) rc = herr(colsum_finish(pb, kLnBlocks, H, dbeta, s));
-  if (!rc && dsum) rc = herr(colsum_finish(po, kLnBlocks, H, dsum, s));
+  if (!rc && dgamma) rc = herr(colsum_finish(pg, ln_blocks(T), H, dgamma, s));
+  if (!rc && dgamma) rc = herr(colsum_finish(pb, ln_blocks(T), H, dbeta, s));
+  if (!rc && dsum) rc = herr(colsum_finish(po, ln_blocks(T), H, dsum, s));
   return rc;
 }
 
@@ -142,6 +142,8 @@ int fl_test_colsum(int dtype, int mode, const void* X, const void* Y, const floa
   hipStream_t s = (hipStream_t)stream;
   const int nb = colsum_blocks(T);
   float* p2 = partial + (size_t)nb * N;
+  if (mode == 0 && T <= kColsumDirectRows && N % 64 == 0)  // as the stack does
+    return herr(colsum_direct((DType)dtype, X, N, T, N, out, s));
   int rc = herr(colsum_partial((DType)dtype, mode, X, N, Y, mean, rstd, T, N, partial, p2, s));
   if (rc) return rc;
   if ((rc = herr(colsum_finish(partial, nb, N, out, s)))) return rc;

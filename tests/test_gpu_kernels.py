@@ -423,6 +423,70 @@ def test_colsum_many_blocks(dt):
     assert rel_l2(host(out), 2 * X.astype(np.float64).sum(0)) < 1e-5
 
 
+@pytest.mark.parametrize("dt", DT)
+@pytest.mark.parametrize("T,H", [(1, 768), (3, 2048), (1535, 768), (1536, 4096), (1537, 768)])
+def test_layernorm_fwd_row_per_workgroup(dt, T, H):
+    """LayerNorm forward around the row count where it changes from one
+    workgroup to one wave per row, at widths below, at and past 256 lanes'
+    chunks.  Error bounds as for any row count: a bf16 output rounds to 2^-9,
+    fp32 sums of H <= 4096 terms stay below 1e-5."""
+    code, tdt = DTYPES[dt]
+    x = rnd((T, H), 41, 2.0, dt=dt)
+    g, b = rnd((H,), 42, dt=dt), rnd((H,), 43, dt=dt)
+    ref, _, rstd = oracle.layer_norm(x.astype(np.float64), g, b, 1e-5)
+    y = torch.full((T, H), float("nan"), dtype=tdt, device="cuda")
+    mean, rs = torch.empty(T, device="cuda"), torch.empty(T, device="cuda")
+    F.fl_test_layernorm_fwd(code, dev(x, dt), dev(g, dt), dev(b, dt), y, mean, rs, T, H, 1e-5)
+    sync()
+    assert rel_l2(host(y), ref) < TOL[dt] / 4
+    assert rel_l2(host(rs), rstd[:, 0]) < 1e-5
+    assert np.abs(host(mean) - x.astype(np.float64).mean(1)).max() < 1e-5
+
+
+@pytest.mark.parametrize("dt", DT)
+@pytest.mark.parametrize("T", [1, 4, 5, 2047, 2048, 2049])
+def test_layernorm_bwd_row_blocks(dt, T):
+    """LayerNorm backward sums where the number of row blocks changes: one
+    block, two, and around the 2048 rows from which it is constant; the
+    scratch past them (NaN) must not be read."""
+    code, tdt = DTYPES[dt]
+    H = 512
+    x, g = rnd((T, H), 44, 2.0, dt=dt), rnd((H,), 45, dt=dt)
+    _, xhat, rstd = oracle.layer_norm(x.astype(np.float64), g, g, 1e-5)
+    mean = torch.from_numpy(x.astype(np.float64).mean(1).astype(np.float32)).cuda()
+    rs = torch.from_numpy(rstd[:, 0].astype(np.float32)).cuda()
+    dy = rnd((T, H), 46, dt=dt)
+    dxr, dgr, dbr = oracle.layer_norm_backward(dy.astype(np.float64), xhat, rstd, g.astype(np.float64))
+    out = torch.full((T, H), float("nan"), dtype=tdt, device="cuda")
+    og, ob, osum = (torch.zeros(H, device="cuda") for _ in range(3))
+    part = torch.full((3 * 512 * H,), float("nan"), dtype=torch.float32, device="cuda")
+    F.fl_test_layernorm_bwd_fused(code, dev(dy, dt), dev(x, dt), mean, rs, dev(g, dt), None, out, T, H, og, ob, osum,
+                                  part)
+    sync()
+    got = host(out)
+    assert rel_l2(got, dxr) < TOL[dt] / 4
+    assert rel_l2(host(og), dgr) < 1e-4 and rel_l2(host(ob), dbr) < 1e-5
+    scale = np.abs(got).sum(0) + 1e-30
+    assert np.all(np.abs(host(osum) - got.sum(0)) <= 1e-5 * scale)
+
+
+@pytest.mark.parametrize("dt", DT)
+@pytest.mark.parametrize("T", [1, 7, 128, 513, 2048, 2049, 5000])
+def test_colsum_one_and_two_stages(dt, T):
+    """Column sums around the row count where they change from one launch to
+    two stages, with fewer rows than a workgroup's lanes and ragged ends;
+    accumulated onto what is there."""
+    code, _ = DTYPES[dt]
+    N = 320
+    X = rnd((T, N), 47, dt=dt)
+    out = torch.full((N,), 3.0, dtype=torch.float32, device="cuda")
+    part = torch.empty(2 * N * ((T + 255) // 256), dtype=torch.float32, device="cuda")
+    F.fl_test_colsum(code, 0, dev(X, dt), None, None, None, T, N, out, None, part)
+    sync()
+    scale = np.abs(X.astype(np.float64)).sum(0) + 3.0
+    assert np.all(np.abs(host(out) - (X.astype(np.float64).sum(0) + 3.0)) <= 1e-5 * scale)
+
+
 # ---------------------------------------------------------------------------
 # Rotary and attention
 # ---------------------------------------------------------------------------
