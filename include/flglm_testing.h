@@ -58,6 +58,17 @@ int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void
                        int64_t ldc2, const void* Z, int64_t ldz, float* part, int64_t part_bytes, int b_rows,
                        float res_scale, float* colsum, int tile, int slices, void* stream);
 
+/* The backward of one linear layer in one launch (few rows): dX[T][in] =
+ * dY W (times gelu_tanh'(Z) where Z is given), dW[out][in] (fp32) += dY^T X
+ * and, where db is given, db[out] (fp32) += the column sums of dY.  All arrays
+ * are dense; out and in are multiples of 256 (bf16) or 64 (fp32).  tile_d, slices and
+ * tile_w force the bf16 kernel's tile heights (64 or 128) and the slices of
+ * dX's reduction (0: chosen from the shape); FL_ERR_ARG where the products do
+ * not run as one launch. */
+int fl_test_linear_backward(int dtype, const void* dY, const void* W, const void* X, const void* Z, void* dX,
+                            float* dW, float* db, int T, int out, int in, float* part, int64_t part_bytes,
+                            int tile_d, int slices, int tile_w, void* stream);
+
 /* LayerNorm over rows of x [T, H] (H % 256 == 0, H <= 4096). */
 int fl_test_layernorm_fwd(int dtype, const void* x, const void* g, const void* b, void* y, float* mean, float* rstd,
                           int T, int H, float eps, void* stream);

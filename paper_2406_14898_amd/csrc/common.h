@@ -221,4 +221,44 @@ __device__ __forceinline__ void settle(T& v) {
 // writes) access patterns over distinct banks.
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row ^ (row >> 3)) & 7); }
 
+// out[n] += sum_t X[t][n] for the 64 columns from col0 on, by a workgroup of NW
+// waves (eight lanes of eight columns, 8 NW rows at a time); sh: 64 NW floats
+// of LDS.  A lane's rows in order, then the eight rows of a wave, then the
+// waves in order.
+template <typename T, int NW>
+__device__ __forceinline__ void colsum_cols(const T* X, long ldx, int rows, int col0, float* out, float* sh) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int col = col0 + (lane & 7) * 8;
+  float a[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a[e] = 0.f;
+  for (int r = w * 8 + (lane >> 3); r < rows; r += 32 * NW) {
+    Vec8<T> v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (r + 8 * NW * u < rows) v[u].load(X + (long)(r + 8 * NW * u) * ldx + col);
+      else v[u].zero();
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e] += v[u].get(e);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) a[e] += __shfl_xor(a[e], o, 64);
+  }
+  if (lane < 8) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sh[w * 64 + lane * 8 + e] = a[e];
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    float t = sh[threadIdx.x];
+#pragma unroll
+    for (int v = 1; v < NW; ++v) t += sh[v * 64 + threadIdx.x];
+    out[col0 + threadIdx.x] += t;
+  }
+}
+
 }  // namespace flglm

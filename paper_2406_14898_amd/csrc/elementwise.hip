@@ -644,46 +644,13 @@ hipError_t colsum_partial(DType dt, int mode, const void* X, long ldx, const voi
   return hipGetLastError();
 }
 
-// Column sums of few rows in one launch: out[n] += sum_t X[t][n].  A workgroup
-// takes 64 columns (eight lanes of eight columns, 128 rows at a time); a lane's
-// rows in order, then the eight rows of a wave, then the waves in order.  The
-// two-stage form above is a chain of 64 rows per wave and a second launch (N
-// 4096: 256 rows 7.0 -> 3.4 us, 1024 rows 7.0 -> 3.9).
+// Column sums of few rows in one launch (N 4096: 256 rows 7.0 -> 3.4 us, 1024
+// rows 7.0 -> 3.9, against the two-stage form above: a chain of 64 rows per
+// wave and a second launch).
 template <typename T>
 __global__ void __launch_bounds__(1024) colsum_direct_kernel(const T* X, long ldx, int T_, float* out) {
-  __shared__ float sh[16][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int col = blockIdx.x * 64 + (lane & 7) * 8;
-  float a[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) a[e] = 0.f;
-  for (int r = w * 8 + (lane >> 3); r < T_; r += 512) {
-    Vec8<T> v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (r + 128 * u < T_) v[u].load(X + (long)(r + 128 * u) * ldx + col);
-      else v[u].zero();
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] += v[u].get(e);
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-#pragma unroll
-    for (int o = 8; o < 64; o <<= 1) a[e] += __shfl_xor(a[e], o, 64);
-  }
-  if (lane < 8) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sh[w][lane * 8 + e] = a[e];
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    float t = sh[0][threadIdx.x];
-#pragma unroll
-    for (int v = 1; v < 16; ++v) t += sh[v][threadIdx.x];
-    out[(long)blockIdx.x * 64 + threadIdx.x] += t;
-  }
+  __shared__ float sh[16 * 64];
+  colsum_cols<T, 16>(X, ldx, T_, blockIdx.x * 64, out, sh);
 }
 
 hipError_t colsum_direct(DType dt, const void* X, long ldx, int T_, int N, float* out, hipStream_t st) {

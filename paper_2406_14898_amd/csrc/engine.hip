@@ -613,60 +613,71 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   // input-gradient GEMMs' epilogues) instead of passing straight through
   const float alpha = st->d.residual_alpha;
   int rc;
+  // A linear layer's input gradient gd and weight gradient gw, with the bias
+  // gradient `bias` += the column sums of the output gradient (NULL: formed
+  // elsewhere).  Few rows: one launch, unless launch timing tells the classes
+  // apart.
+  constexpr uint32_t kPairClasses = 1u << FL_PROF_GEMM_TN_ACC | 1u << FL_PROF_GEMM_NN |
+                                    1u << FL_PROF_GEMM_NN_GELU_BWD | 1u << FL_PROF_COLSUM;
+  const bool may_pair = train_w && !(st->prof_mask & kPairClasses);
+  auto linear = [&](int cls, int epi, GemmDesc& gd, GemmDesc& gw, float* bias) -> int {
+    with_part(gd, plan);
+    if (may_pair && gemm_pair_ok(dt, epi, gd, gw)) {
+      HIP_OK(gemm_pair(dt, epi, gd, gw, bias, s));
+      return FL_OK;
+    }
+    const int n_out = gd.K, n_in = gd.N;
+    if (train_w) {
+      int r;
+      if (bias && (r = colsum_into(st, dt, gd.A, n_out, T, n_out, bias, w, s))) return r;
+      LAUNCH(FL_PROF_GEMM_TN_ACC, gemm_flops(n_out, n_in, T), gemm_bytes(n_out, n_in, T, E, 8),
+             gemm(dt, GEMM_TN, EPI_ACC_F32, with_part(gw, plan), s));
+    }
+    LAUNCH(cls, gemm_flops(T, n_in, n_out), gemm_bytes(T, n_in, n_out, E, epi == EPI_GELU_BWD ? 2 * E : E),
+           gemm(dt, GEMM_NN, epi, gd, s));
+    return FL_OK;
+  };
+  auto grad_in = [&](const void* dout, const void* weight, void* din, int n_out, int n_in) {
+    GemmDesc g;
+    g.A = dout; g.B = weight; g.C = din; g.M = T; g.N = n_in; g.K = n_out; g.lda = n_out; g.ldb = n_in; g.ldc = n_in;
+    return g;
+  };
+  auto grad_w = [&](const void* dout, const void* in, float* dw, int n_out, int n_in) {
+    GemmDesc g;
+    g.A = dout; g.B = in; g.C = dw; g.M = n_out; g.N = n_in; g.K = T; g.lda = n_out; g.ldb = n_in; g.ldc = n_in;
+    return g;
+  };
   // y = h + g W_2^T + b_2
-  GemmDesc g;
-  if (train_w) {
-    if (!b2_done && (rc = colsum_into(st, dt, dy, H, T, H, gr.b_2, w, s))) return rc;
-    g.A = dy; g.B = a.g; g.C = gr.w_2; g.M = H; g.N = F; g.K = T; g.lda = H; g.ldb = F; g.ldc = F;
-    LAUNCH(FL_PROF_GEMM_TN_ACC, gemm_flops(H, F, T), gemm_bytes(H, F, T, E, 8),
-           gemm(dt, GEMM_TN, EPI_ACC_F32, with_part(g, plan), s));
-  }
-  g = GemmDesc();
-  g.A = dy; g.B = p.w_2; g.C = w.dz; g.M = T; g.N = F; g.K = H; g.lda = H; g.ldb = F; g.ldc = F;
-  g.Z = a.z; g.ldz = F;
+  GemmDesc gd = grad_in(dy, p.w_2, w.dz, H, F), gw = grad_w(dy, a.g, gr.w_2, H, F);
+  gd.Z = a.z; gd.ldz = F;
   // db_1 = column sums of dz: formed per 256-row tile in the GEMM's epilogue
   // where the kernel supports it (no second pass over dz), else below
   // (few rows: only where that costs no pass of its own)
-  with_part(g, plan);
-  const bool b1_fused = train_w && gemm_fuses_colsum(dt, GEMM_NN, EPI_GELU_BWD, g) &&
-                        (T > kColsumDirectRows || gemm_epilogue_colsum(g));
-  if (b1_fused) g.colsum = w.part;
-  LAUNCH(FL_PROF_GEMM_NN_GELU_BWD, gemm_flops(T, F, H), gemm_bytes(T, F, H, E, 2 * E),
-         gemm(dt, GEMM_NN, EPI_GELU_BWD, g, s));
+  with_part(gd, plan);
+  const bool b1_fused = train_w && !(may_pair && gemm_pair_ok(dt, EPI_GELU_BWD, gd, gw)) &&
+                        gemm_fuses_colsum(dt, GEMM_NN, EPI_GELU_BWD, gd) &&
+                        (T > kColsumDirectRows || gemm_epilogue_colsum(gd));
+  if (b1_fused) gd.colsum = w.part;
+  if ((rc = linear(FL_PROF_GEMM_NN_GELU_BWD, EPI_GELU_BWD, gd, gw, b2_done ? nullptr : gr.b_2))) return rc;
   // z = w W_1^T + b_1
-  if (train_w) {
-    if (b1_fused) {
-      LAUNCH(FL_PROF_COLSUM, 0, 4.0 * colsum_blocks(T) * F, colsum_finish(w.part, colsum_blocks(T), F, gr.b_1, s));
-    } else if ((rc = colsum_into(st, dt, w.dz, F, T, F, gr.b_1, w, s))) {
-      return rc;
-    }
-    g = GemmDesc();
-    g.A = w.dz; g.B = a.w; g.C = gr.w_1; g.M = F; g.N = H; g.K = T; g.lda = F; g.ldb = H; g.ldc = H;
-    LAUNCH(FL_PROF_GEMM_TN_ACC, gemm_flops(F, H, T), gemm_bytes(F, H, T, E, 8),
-           gemm(dt, GEMM_TN, EPI_ACC_F32, with_part(g, plan), s));
-  }
-  g = GemmDesc();
-  g.A = w.dz; g.B = p.w_1; g.C = w.tmp; g.M = T; g.N = H; g.K = F; g.lda = F; g.ldb = H; g.ldc = H;
+  if (b1_fused)
+    LAUNCH(FL_PROF_COLSUM, 0, 4.0 * colsum_blocks(T) * F, colsum_finish(w.part, colsum_blocks(T), F, gr.b_1, s));
+  gd = grad_in(w.dz, p.w_1, w.tmp, F, H);
+  gw = grad_w(w.dz, a.w, gr.w_1, F, H);
   if (alpha > 0.f) {
-    g.R = dy; g.ldr = H; g.res_scale = alpha;
+    gd.R = dy; gd.ldr = H; gd.res_scale = alpha;
   }
-  LAUNCH(FL_PROF_GEMM_NN, gemm_flops(T, H, F), gemm_bytes(T, H, F, E, E),
-         gemm(dt, GEMM_NN, alpha > 0.f ? EPI_RES : EPI_STORE, with_part(g, plan), s));
+  if ((rc = linear(FL_PROF_GEMM_NN, alpha > 0.f ? EPI_RES : EPI_STORE, gd, gw, b1_fused ? nullptr : gr.b_1)))
+    return rc;
   // w = LN2(h); h also feeds y directly (plain residual).  db_o = the column
   // sums of dh, formed in the same pass.
   if ((rc = ln_backward(st, dt, w.tmp, a.h, a.mean2, a.rstd2, p.ln2_g, alpha > 0.f ? nullptr : dy, w.dh, gr.ln2_g,
                         gr.ln2_b, train_w ? gr.b_o : nullptr, T, H, w, s)))
     return rc;
   // h = x + o W_o^T + b_o
-  if (train_w) {
-    g = GemmDesc();
-    g.A = w.dh; g.B = a.o; g.C = gr.w_o; g.M = H; g.N = H; g.K = T; g.lda = H; g.ldb = H; g.ldc = H;
-    LAUNCH(FL_PROF_GEMM_TN_ACC, gemm_flops(H, H, T), gemm_bytes(H, H, T, E, 8),
-           gemm(dt, GEMM_TN, EPI_ACC_F32, with_part(g, plan), s));
-  }
-  g = GemmDesc();
-  g.A = w.dh; g.B = p.w_o; g.C = w.tmp; g.M = T; g.N = H; g.K = H; g.lda = H; g.ldb = H; g.ldc = H;
-  LAUNCH(FL_PROF_GEMM_NN, gemm_flops(T, H, H), gemm_bytes(T, H, H, E, E), gemm(dt, GEMM_NN, EPI_STORE, with_part(g, plan), s));
+  gd = grad_in(w.dh, p.w_o, w.tmp, H, H);
+  gw = grad_w(w.dh, a.o, gr.w_o, H, H);
+  if ((rc = linear(FL_PROF_GEMM_NN, EPI_STORE, gd, gw, nullptr))) return rc;
   // attention (dq, dk, dv with the inverse rotation applied)
   AttnDesc ad;
   ad.qkv = a.qkv; ad.ld_qkv = 3 * H; ad.o = a.o; ad.ld_o = H; ad.lse = a.lse;
@@ -701,24 +712,16 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
            prefix_grad_reduce(w.dprefix, bi.S, n, gr.prefix_k, gr.prefix_v, s));
   }
   // qkv = u W_qkv^T + b_qkv
-  if (train_w) {
-    if (fused_bqkv)
-      LAUNCH(FL_PROF_COLSUM, 0, 4.0 * w.bias_rows * 3 * H,
-             colsum_finish(w.bias_part, w.bias_rows, 3 * H, gr.b_qkv, s));
-    else if ((rc = colsum_into(st, dt, w.dqkv, 3 * H, T, 3 * H, gr.b_qkv, w, s)))
-      return rc;
-    g = GemmDesc();
-    g.A = w.dqkv; g.B = a.u; g.C = gr.w_qkv; g.M = 3 * H; g.N = H; g.K = T; g.lda = 3 * H; g.ldb = H; g.ldc = H;
-    LAUNCH(FL_PROF_GEMM_TN_ACC, gemm_flops(3 * H, H, T), gemm_bytes(3 * H, H, T, E, 8),
-           gemm(dt, GEMM_TN, EPI_ACC_F32, with_part(g, plan), s));
-  }
-  g = GemmDesc();
-  g.A = w.dqkv; g.B = p.w_qkv; g.C = w.tmp; g.M = T; g.N = H; g.K = 3 * H; g.lda = 3 * H; g.ldb = H; g.ldc = H;
+  if (fused_bqkv)
+    LAUNCH(FL_PROF_COLSUM, 0, 4.0 * w.bias_rows * 3 * H,
+           colsum_finish(w.bias_part, w.bias_rows, 3 * H, gr.b_qkv, s));
+  gd = grad_in(w.dqkv, p.w_qkv, w.tmp, 3 * H, H);
+  gw = grad_w(w.dqkv, a.u, gr.w_qkv, 3 * H, H);
   if (alpha > 0.f) {
-    g.R = w.dh; g.ldr = H; g.res_scale = alpha;
+    gd.R = w.dh; gd.ldr = H; gd.res_scale = alpha;
   }
-  LAUNCH(FL_PROF_GEMM_NN, gemm_flops(T, H, 3 * H), gemm_bytes(T, H, 3 * H, E, E),
-         gemm(dt, GEMM_NN, alpha > 0.f ? EPI_RES : EPI_STORE, with_part(g, plan), s));
+  if ((rc = linear(FL_PROF_GEMM_NN, alpha > 0.f ? EPI_RES : EPI_STORE, gd, gw, fused_bqkv ? nullptr : gr.b_qkv)))
+    return rc;
   // u = LN1(x); x also feeds h directly (plain residual)
   return ln_backward(st, dt, w.tmp, x, a.mean1, a.rstd1, p.ln1_g, alpha > 0.f ? nullptr : w.dh, dx, gr.ln1_g,
                      gr.ln1_b, dx_sum, T, H, w, s);

@@ -332,13 +332,16 @@ struct SmallOperand {
   __device__ static __forceinline__ int row(int t, int idx) { return KC ? 16 * t + idx : TT * idx + t; }
 };
 
+// LDS floats of one wave's partial tile
+template <int TT>
+constexpr int kSmallRed = 16 * TT * (16 * TT + 4);
+
+// The tile at row m0, column n0; red: 8 partial tiles of LDS.
 template <bool AK, bool BKc, int EPI, int TT>
-__global__ void __launch_bounds__(512) gemm_f32_small_kernel(GemmArgs p) {
-  constexpr int NW = 8, BT = 16 * TT, PAD = BT + 4;
-  __shared__ __attribute__((aligned(16))) float red[NW][BT * PAD];
+__device__ __forceinline__ void gemm_f32_small_tile(const GemmArgs& p, float* red, int m0, int n0) {
+  constexpr int NW = 8, BT = 16 * TT, PAD = BT + 4, RED = kSmallRed<TT>;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int fr = lane & 15, fg = lane >> 4;
-  const int m0 = blockIdx.y * BT, n0 = blockIdx.x * BT;
   const float* A = static_cast<const float*>(p.A);
   const float* B = static_cast<const float*>(p.B);
   // rows and reduction indices that exist (a K-contiguous row is read in whole
@@ -381,7 +384,7 @@ __global__ void __launch_bounds__(512) gemm_f32_small_kernel(GemmArgs p) {
     for (int i = 0; i < TT; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        red[wave][SmallOperand<AK, TT>::row(j, fr) * PAD + SmallOperand<BKc, TT>::row(i, 4 * fg + e)] = acc[i][j][e];
+        red[wave * RED + SmallOperand<AK, TT>::row(j, fr) * PAD + SmallOperand<BKc, TT>::row(i, 4 * fg + e)] = acc[i][j][e];
   __syncthreads();
   const int r = tid / (BT / 4), c = tid % (BT / 4) * 4;
   const int m = m0 + r, n = n0 + c;
@@ -390,16 +393,57 @@ __global__ void __launch_bounds__(512) gemm_f32_small_kernel(GemmArgs p) {
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     Vec4<float> x;
-    x.load(&red[w][r * PAD + c]);
+    x.load(red + w * RED + r * PAD + c);
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] += x.get(e);
   }
   store_outputs<float, EPI>(p, m, n, v);
 }
 
+template <bool AK, bool BKc, int EPI, int TT>
+__global__ void __launch_bounds__(512) gemm_f32_small_kernel(GemmArgs p) {
+  __shared__ __attribute__((aligned(16))) float red[8 * kSmallRed<TT>];
+  gemm_f32_small_tile<AK, BKc, EPI, TT>(p, red, blockIdx.y * 16 * TT, blockIdx.x * 16 * TT);
+}
+
+// The input gradient d (NN), the weight gradient w (TN) and, with `bias`, the
+// bias gradient (+= the column sums of the layer's output gradient) of one
+// linear layer in one launch: each is a few microseconds of a few hundred
+// workgroups, most of it launch and ramp.
+struct SmallPairArgs {
+  GemmArgs d, w;
+  float* bias;
+};
+template <int EPI, int TD, int TW>
+__global__ void __launch_bounds__(512) gemm_f32_pair_kernel(SmallPairArgs p) {
+  __shared__ __attribute__((aligned(16))) float red[8 * kSmallRed<(TD > TW ? TD : TW)>];
+  const int nd = (p.d.M + 16 * TD - 1) / (16 * TD) * (p.d.N / (16 * TD));
+  const int nw = (p.w.M + 16 * TW - 1) / (16 * TW) * (p.w.N / (16 * TW));
+  int b = blockIdx.x;
+  if (b < nd) {
+    const int tn = p.d.N / (16 * TD);
+    gemm_f32_small_tile<true, false, EPI, TD>(p.d, red, b / tn * 16 * TD, b % tn * 16 * TD);
+  } else if ((b -= nd) < nw) {
+    const int tn = p.w.N / (16 * TW);
+    gemm_f32_small_tile<false, false, EPI_ACC_F32, TW>(p.w, red, b / tn * 16 * TW, b % tn * 16 * TW);
+  } else {
+    colsum_cols<float, 8>(static_cast<const float*>(p.w.A), p.w.lda, p.w.K, (b - nw) * 64, p.bias, red);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+
+// 16-row tiles along each side of the small kernel's tile for an fp32 product,
+// or 0: enough 128 x 128 tiles to fill the chip.  Measured (us): 128 tiles
+// (2048 x 1024 x 256) 25 on 32 x 32 against 35 on 128 x 128, 248 tiles (3900 x
+// 1024 x 256) 35 against 37; 64 tiles of 32 x 32 (256 x 256 x 1024) 11 against
+// 6.9 on 16 x 16, 192 of them (256 x 768 x 256) 5.4 against 5.9.
+static int small_tiles(int M, int N) {
+  if ((long)((M + 31) / 32) * (N / 32) <= 128) return 1;
+  return (long)((M + 127) / 128) * ((N + 127) / 128) < 192 ? 2 : 0;
+}
 
 template <typename T, int BM, int BN, int WTM, int WTN, bool AK, bool BKc, int EPI>
 static hipError_t launch_cfg(const GemmArgs& a, hipStream_t st) {
@@ -416,17 +460,12 @@ static hipError_t launch_layout(const GemmArgs& a, hipStream_t st) {
     if (a.N % 256 == 0) return launch_cfg<T, 256, 256, 8, 8, AK, BKc, EPI>(a, st);
     return launch_cfg<T, 256, 128, 8, 4, AK, BKc, EPI>(a, st);
   } else {
-    // Too few 128 x 128 tiles to fill the chip.  Measured (us): 128 tiles
-    // (2048 x 1024 x 256) 25 on 32 x 32 against 35 on 128 x 128, 248 tiles
-    // (3900 x 1024 x 256) 35 against 37; 64 tiles of 32 x 32 (256 x 256 x 1024)
-    // 11 against 6.9 on 16 x 16, 192 of them (256 x 768 x 256) 5.4 against 5.9.
-    const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-    const long tiles32 = (long)((a.M + 31) / 32) * (a.N / 32);
-    if (tiles32 <= 128) {
+    const int tt = small_tiles(a.M, a.N);
+    if (tt == 1) {
       hipLaunchKernelGGL((gemm_f32_small_kernel<AK, BKc, EPI, 1>), dim3(a.N / 16, (a.M + 15) / 16), dim3(512), 0, st, a);
       return hipGetLastError();
     }
-    if (tiles < 192) {
+    if (tt == 2) {
       hipLaunchKernelGGL((gemm_f32_small_kernel<AK, BKc, EPI, 2>), dim3(a.N / 32, (a.M + 31) / 32), dim3(512), 0, st, a);
       return hipGetLastError();
     }
@@ -456,6 +495,17 @@ static hipError_t dispatch_layout(int epi, const GemmArgs& a, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
+static GemmArgs make_args(GemmLayout layout, const GemmDesc& d) {
+  GemmArgs a;
+  a.A = d.A; a.B = d.B; a.C = d.C;
+  a.M = d.M; a.N = d.N; a.K = d.K;
+  a.lda = d.lda; a.ldb = d.ldb; a.ldc = d.ldc;
+  a.bias = d.bias; a.R = d.R; a.ldr = d.ldr; a.C2 = d.C2; a.ldc2 = d.ldc2; a.Z = d.Z; a.ldz = d.ldz;
+  a.nb = gemm_b_rows(layout == GEMM_NT, d);
+  a.res_scale = d.res_scale;
+  return a;
+}
+
 hipError_t gemm(DType dt, GemmLayout layout, int epi, const GemmDesc& d, hipStream_t st) {
   if (dt == DT_BF16 && gemm_bf16_dma_ok(layout, d)) return gemm_bf16_dma(layout, epi, d, st);
   // A weight-gradient GEMM whose operands span 2^31 bytes or more along the
@@ -482,13 +532,7 @@ hipError_t gemm(DType dt, GemmLayout layout, int epi, const GemmDesc& d, hipStre
       }
     }
   }
-  GemmArgs a;
-  a.A = d.A; a.B = d.B; a.C = d.C;
-  a.M = d.M; a.N = d.N; a.K = d.K;
-  a.lda = d.lda; a.ldb = d.ldb; a.ldc = d.ldc;
-  a.bias = d.bias; a.R = d.R; a.ldr = d.ldr; a.C2 = d.C2; a.ldc2 = d.ldc2; a.Z = d.Z; a.ldz = d.ldz;
-  a.nb = gemm_b_rows(layout == GEMM_NT, d);
-  a.res_scale = d.res_scale;
+  const GemmArgs a = make_args(layout, d);
   if (dt == DT_BF16) {
     switch (layout) {
       case GEMM_NT: return dispatch_layout<bf16, GEMM_NT>(epi, a, st);
@@ -503,6 +547,35 @@ hipError_t gemm(DType dt, GemmLayout layout, int epi, const GemmDesc& d, hipStre
     }
   }
   return hipErrorInvalidValue;
+}
+
+template <int EPI>
+static hipError_t launch_pair(const SmallPairArgs& a, int td, int tw, hipStream_t st) {
+  const long nd = (long)((a.d.M + 16 * td - 1) / (16 * td)) * (a.d.N / (16 * td));
+  const long nw = (long)((a.w.M + 16 * tw - 1) / (16 * tw)) * (a.w.N / (16 * tw));
+  const dim3 grid((unsigned)(nd + nw + (a.bias ? a.w.M / 64 : 0))), blk(512);
+  if (td == 1 && tw == 1) hipLaunchKernelGGL((gemm_f32_pair_kernel<EPI, 1, 1>), grid, blk, 0, st, a);
+  else if (td == 1) hipLaunchKernelGGL((gemm_f32_pair_kernel<EPI, 1, 2>), grid, blk, 0, st, a);
+  else if (tw == 1) hipLaunchKernelGGL((gemm_f32_pair_kernel<EPI, 2, 1>), grid, blk, 0, st, a);
+  else hipLaunchKernelGGL((gemm_f32_pair_kernel<EPI, 2, 2>), grid, blk, 0, st, a);
+  return hipGetLastError();
+}
+
+bool gemm_pair_ok(DType dt, int epi, const GemmDesc& d, const GemmDesc& w) {
+  // one output gradient: d's A is w's A
+  if (d.A != w.A || d.lda != w.lda || d.M != w.K || d.K != w.M || w.M % 64 != 0) return false;
+  if (dt == DT_BF16) return gemm_bf16_pair_ok(epi, d, w);
+  return (epi == EPI_STORE || epi == EPI_GELU_BWD) && d.M > 0 && w.M > 0 && d.M <= kColsumDirectRows &&
+         small_tiles(d.M, d.N) && small_tiles(w.M, w.N);
+}
+
+hipError_t gemm_pair(DType dt, int epi, const GemmDesc& d, const GemmDesc& w, float* bias, hipStream_t st) {
+  if (!gemm_pair_ok(dt, epi, d, w)) return hipErrorInvalidValue;
+  if (dt == DT_BF16) return gemm_bf16_pair(epi, d, w, bias, st);
+  SmallPairArgs a;
+  a.d = make_args(GEMM_NN, d); a.w = make_args(GEMM_TN, w); a.bias = bias;
+  const int td = small_tiles(d.M, d.N), tw = small_tiles(w.M, w.N);
+  return epi == EPI_STORE ? launch_pair<EPI_STORE>(a, td, tw, st) : launch_pair<EPI_GELU_BWD>(a, td, tw, st);
 }
 
 }  // namespace flglm

@@ -377,20 +377,14 @@ constexpr int epi_steps() {
   return EPI == EPI_BIAS_RES || EPI == EPI_RES || EPI == EPI_ACC_F32 ? 8 : 4;
 }
 
+// One work item (output tile, reduction slice) of a product; smem holds at
+// least TL's operand slots and every thread of the workgroup takes part.
 template <bool AK, bool BKc, int EPI, class TL>
-__global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16_kernel(G2Args p) {
+__device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, int nwork) {
   constexpr int kBM = TL::kBM, kBN = TL::kBN, kThr = TL::kThr, kWaves = TL::kWaves;
   constexpr int kWTM = TL::kWTM, kWTN = TL::kWTN, kSlot = TL::kSlot, kStages = TL::kStages;
-  __shared__ __attribute__((aligned(1024))) bf16 smem[kStages * kSlot];  // [slot][A | B]
-
   const int tiles_m = (p.M + kBM - 1) / kBM, tiles_n = p.N / kBN;
-  const int ntiles = tiles_m * tiles_n;
   const int nk = (p.K + kBK - 1) / kBK;
-  const int nwork = ntiles * p.slices;
-  // Persistent where the grid is smaller than the work (256 x 256 tiles: one
-  // workgroup per CU); a tile's epilogue stores drain while the next item's
-  // first stages load.
-  for (int wi = blockIdx.x; wi < nwork; wi += gridDim.x) {
   int tm, tn, slice;
   // Bands of 4 tile rows for the forward and dgrad products on 256 x 256
   // tiles (the 32 tiles one XCD holds span 4 row panels of A and 8 column
@@ -597,6 +591,45 @@ __global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16
   } else {
     tile_epilogue<TL, EPI, epi_steps<EPI>()>(p, acc, reinterpret_cast<float*>(&smem[0]), tm, m0, n0, tid);
   }
+}
+
+template <bool AK, bool BKc, int EPI, class TL>
+__global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16_kernel(G2Args p) {
+  __shared__ __attribute__((aligned(1024))) bf16 smem[TL::kStages * TL::kSlot];  // [slot][A | B]
+  const int nwork = ((p.M + TL::kBM - 1) / TL::kBM) * (p.N / TL::kBN) * p.slices;
+  // Persistent where the grid is smaller than the work (256 x 256 tiles: one
+  // workgroup per CU); a tile's epilogue stores drain while the next item's
+  // first stages load.
+  for (int wi = blockIdx.x; wi < nwork; wi += gridDim.x) gemm_item<AK, BKc, EPI, TL>(p, smem, wi, nwork);
+}
+
+// The input gradient d (NN) and the weight gradient w (TN) of one linear layer
+// and, with `bias`, its bias gradient (+= the column sums of the layer's output
+// gradient) in one launch.  All three only read that gradient.
+struct PairArgs {
+  G2Args d, w;
+  int nd, nw;        // their work items
+  int chunk, share;  // of each segment of workgroups: items of d, then of w
+  float* bias;       // [w.M], or null
+};
+template <int EPI, class TD, class TW>
+__global__ void __launch_bounds__(256, TD::kOcc < TW::kOcc ? TD::kOcc : TW::kOcc) gemm_pair_kernel(PairArgs p) {
+  static_assert(TD::kThr == 256 && TW::kThr == 256, "workgroup");
+  constexpr int kD = TD::kStages * TD::kSlot, kW = TW::kStages * TW::kSlot;
+  __shared__ __attribute__((aligned(1024))) bf16 smem[kD > kW ? kD : kW];
+  const int seg = p.chunk + p.share, nseg = (p.nd + p.chunk - 1) / p.chunk;
+  const int b = blockIdx.x;
+  if (b < nseg * seg) {
+    const int s = b / seg, r = b - s * seg;
+    if (r < p.chunk) {
+      const int wi = s * p.chunk + r;
+      if (wi < p.nd) gemm_item<true, false, EPI, TD>(p.d, smem, wi, p.nd);
+    } else {
+      const int wi = s * p.share + r - p.chunk;
+      if (wi < p.nw) gemm_item<false, false, EPI_ACC_F32, TW>(p.w, smem, wi, p.nw);
+    }
+  } else {
+    colsum_cols<bf16, 4>(p.w.A, p.w.lda, p.w.K, (b - nseg * seg) * 64, p.bias, reinterpret_cast<float*>(smem));
   }
 }
 
@@ -768,14 +801,18 @@ hipError_t launch_tile(const G2Args& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int EPI>
+hipError_t launch_slices(const G2Args& a, hipStream_t st) {
+  const long groups = (long)a.M * (a.N / 8);
+  hipLaunchKernelGGL((gemm_slices_kernel<EPI>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
 template <bool AK, bool BKc, int EPI, class TL>
 hipError_t launch_rows(const G2Args& a, hipStream_t st) {
   if (a.slices == 1) return launch_tile<AK, BKc, EPI, TL>(a, st);
   hipError_t e = launch_tile<AK, BKc, EPI_PART, TL>(a, st);
-  if (e != hipSuccess) return e;
-  const long groups = (long)a.M * (a.N / 8);
-  hipLaunchKernelGGL((gemm_slices_kernel<EPI>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, a);
-  return hipGetLastError();
+  return e != hipSuccess ? e : launch_slices<EPI>(a, st);
 }
 
 G2Args make_args(const GemmDesc& d, bool bk) {
@@ -846,7 +883,84 @@ hipError_t launch_wgrad(const GemmDesc& d, hipStream_t st) {
   return launch_tile<false, false, EPI_ACC_F32, Tile64w>(a, st);
 }
 
+// The pair kernel's tile heights for both products and slices for d.
+struct PairPlan {
+  int tile_d, slices, tile_w;
+};
+
+template <int EPI, class TD, class TW>
+hipError_t launch_pair_tiles(const G2Args& d, const G2Args& w, float* bias, hipStream_t st) {
+  PairArgs a;
+  a.d = d; a.w = w; a.bias = bias;
+  a.nd = ((d.M + TD::kBM - 1) / TD::kBM) * (d.N / TD::kBN) * d.slices;
+  a.nw = ((w.M + TW::kBM - 1) / TW::kBM) * (w.N / TW::kBN);
+  a.chunk = std::min(num_cus(), (a.nd + 7) / 8 * 8);
+  const int nseg = (a.nd + a.chunk - 1) / a.chunk;
+  a.share = ((a.nw + nseg - 1) / nseg + 7) / 8 * 8;
+  const int grid = nseg * (a.chunk + a.share) + (bias ? w.M / 64 : 0);
+  hipLaunchKernelGGL((gemm_pair_kernel<EPI, TD, TW>), dim3(grid), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+template <int EPI>
+hipError_t launch_pair(const PairPlan& pl, const G2Args& d, const G2Args& w, float* bias, hipStream_t st) {
+  if (pl.tile_d == 64)
+    return pl.tile_w == 64 ? launch_pair_tiles<EPI, Tile64w, Tile64w>(d, w, bias, st)
+                           : launch_pair_tiles<EPI, Tile64w, Tile128w>(d, w, bias, st);
+  return pl.tile_w == 64 ? launch_pair_tiles<EPI, Tile128w, Tile64w>(d, w, bias, st)
+                         : launch_pair_tiles<EPI, Tile128w, Tile128w>(d, w, bias, st);
+}
+
+// Tile heights, slices and whether one launch is the faster form, from a sweep
+// of every choice on MI355X (rows 9 .. 2048; hidden 256 to 4096, FFN 3.25 and 4
+// times as wide).  The input gradient wants about as many items as there are
+// CUs, each of six stages or more; the weight gradient's items fill in behind.
+// Two launches against one (us): hidden 1280, FFN 3328, 1458 rows FFN-down 51
+// -> 45, FFN-up 50 -> 38, 1024 rows QKV 45 -> 35; hidden 4096 output projection
+// 509 rows 65 -> 55, 1024 rows 104 -> 80; 64 rows FFN-down 140 -> 128.
+// Wide layers of more rows are bound by the matrix cores and by the weight
+// gradient's traffic, where the large tiles of the separate launches win (4096
+// x 16384: 400 rows 199 against 206, 1458 rows 436 against 473) except where
+// their 256-row tiles would be mostly padding (640 rows 291 against 256, 733
+// rows 310 against 278, 820 rows 314 against 310).
+bool plan_pair(const GemmDesc& d, const GemmDesc& w, PairPlan* pl) {
+  if (d.tile) {
+    *pl = PairPlan{d.tile, d.slices, w.tile};
+    return true;
+  }
+  const long n64 = (long)((d.M + 63) / 64) * (d.N / 128), n128 = (long)((d.M + 127) / 128) * (d.N / 128);
+  const long w128 = (long)((w.M + 127) / 128) * (w.N / 128);
+  const int stages = d.K / kBK;
+  pl->tile_d = d.M < 200 || (n64 < 256 && (stages < 32 || n64 >= 200)) ? 64 : 128;
+  const long n = pl->tile_d == 64 ? n64 : n128;
+  pl->slices = (int)std::max(1L, std::min({8L, (long)stages / 6, 256 / n}));
+  while (pl->slices > 1 && (!d.part || (size_t)pl->slices * d.M * d.N * 4 > d.part_bytes)) --pl->slices;
+  pl->tile_w = (w128 > 512 && d.M < 200) || (w128 < 200 && d.M > 900) ? 64 : 128;
+  if (w128 <= 1024) return d.M <= kColsumDirectRows;
+  return d.M <= 340 || (d.M > 600 && d.M <= 820);
+}
+
 }  // namespace
+
+bool gemm_bf16_pair_ok(int epi, const GemmDesc& d, const GemmDesc& w) {
+  PairPlan pl;
+  return (epi == EPI_STORE || epi == EPI_GELU_BWD) && d.M > 0 && w.M > 0 && gemm_bf16_dma_ok(GEMM_NN, d) &&
+         gemm_bf16_dma_ok(GEMM_TN, w) && plan_pair(d, w, &pl);
+}
+
+hipError_t gemm_bf16_pair(int epi, const GemmDesc& d, const GemmDesc& w, float* bias, hipStream_t st) {
+  PairPlan pl;
+  if (!gemm_bf16_pair_ok(epi, d, w) || !plan_pair(d, w, &pl) || (bias && w.M % 64 != 0)) return hipErrorInvalidValue;
+  G2Args a = make_args(d, false);
+  a.slices = pl.slices;
+  const G2Args b = make_args(w, false);
+  if (pl.slices > 1) {
+    hipError_t e = launch_pair<EPI_PART>(pl, a, b, bias, st);
+    if (e != hipSuccess) return e;
+    return epi == EPI_STORE ? launch_slices<EPI_STORE>(a, st) : launch_slices<EPI_GELU_BWD>(a, st);
+  }
+  return epi == EPI_STORE ? launch_pair<EPI_STORE>(pl, a, b, bias, st) : launch_pair<EPI_GELU_BWD>(pl, a, b, bias, st);
+}
 
 size_t gemm_part_bytes() { return (size_t)64 << 20; }
 

@@ -65,6 +65,15 @@ bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d);
 // Whether it does so in the product's own epilogue, without another pass.
 bool gemm_epilogue_colsum(const GemmDesc& d);
 hipError_t gemm_bf16_dma(GemmLayout layout, int epi, const GemmDesc& d, hipStream_t st);
+// The backward of one linear layer with few rows in one launch: the input
+// gradient d (NN, EPI_STORE or EPI_GELU_BWD), the weight gradient w (TN,
+// EPI_ACC_F32; d.A == w.A is the layer's output gradient) and, where bias is
+// given, bias[m] += the column sums of that gradient.  gemm_pair_ok: whether
+// it takes these products and is the faster form.
+bool gemm_pair_ok(DType dt, int epi, const GemmDesc& d, const GemmDesc& w);
+hipError_t gemm_pair(DType dt, int epi, const GemmDesc& d, const GemmDesc& w, float* bias, hipStream_t st);
+bool gemm_bf16_pair_ok(int epi, const GemmDesc& d, const GemmDesc& w);
+hipError_t gemm_bf16_pair(int epi, const GemmDesc& d, const GemmDesc& w, float* bias, hipStream_t st);
 
 // Stored attention softmax gradient: tiles before query tile qt of a sequence
 // and head (ntp prefix key tiles, np context key tiles; see attention_bf16.hip),

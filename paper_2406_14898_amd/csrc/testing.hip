@@ -98,6 +98,34 @@ int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void
   return herr(gemm((DType)dtype, (GemmLayout)layout, epi, d, (hipStream_t)stream));
 }
 
+int fl_test_linear_backward(int dtype, const void* dY, const void* W, const void* X, const void* Z, void* dX,
+                            float* dW, float* db, int T, int out, int in, float* part, int64_t part_bytes,
+                            int tile_d, int slices, int tile_w, void* stream) {
+  if (!dtype_ok(dtype)) return set_error(FL_ERR_ARG, "bad dtype");
+  if (!dY || !W || !X || !dX || !dW) return set_error(FL_ERR_NULL, "NULL argument");
+  if (!al16(dY) || !al16(W) || !al16(X) || !al16(Z) || !al16(dX) || !al16(dW) || !al16(db) || !al16(part))
+    return set_error(FL_ERR_ALIGN, "an array is not 16-byte aligned");
+  const int mult = dtype == FL_BF16 ? 256 : 64;
+  if (T < 1 || out < 1 || in < 1 || out % mult || in % mult) return set_error(FL_ERR_ARG, "bad T / out / in");
+  GemmDesc d, w;
+  d.A = dY; d.B = W; d.C = dX; d.M = T; d.N = in; d.K = out; d.lda = out; d.ldb = in; d.ldc = in;
+  d.Z = Z; d.ldz = in;
+  d.part = part_bytes > 0 ? part : nullptr;
+  d.part_bytes = d.part ? (size_t)part_bytes : 0;
+  w.A = dY; w.B = X; w.C = dW; w.M = out; w.N = in; w.K = T; w.lda = out; w.ldb = in; w.ldc = in;
+  if (tile_d || tile_w) {
+    if (dtype != FL_BF16 || (tile_d != 64 && tile_d != 128) || (tile_w != 64 && tile_w != 128))
+      return set_error(FL_ERR_ARG, "tile heights are 64 or 128 (bf16)");
+    if (slices < 1 || slices > out / 64) return set_error(FL_ERR_ARG, "slices outside [1, reduction stages]");
+    if (slices > 1 && d.part_bytes / 4 / slices < (size_t)T * in)
+      return set_error(FL_ERR_WORKSPACE, "part too small for the slices");
+    d.tile = tile_d; d.slices = slices; w.tile = tile_w;
+  }
+  const int epi = Z ? EPI_GELU_BWD : EPI_STORE;
+  if (!gemm_pair_ok((DType)dtype, epi, d, w)) return set_error(FL_ERR_ARG, "these products run as separate launches");
+  return herr(gemm_pair((DType)dtype, epi, d, w, db, (hipStream_t)stream));
+}
+
 int fl_test_layernorm_fwd(int dtype, const void* x, const void* g, const void* b, void* y, float* mean, float* rstd,
                           int T, int H, float eps, void* stream) {
   if (!dtype_ok(dtype)) return set_error(FL_ERR_ARG, "bad dtype");

@@ -195,6 +195,39 @@ def test_gemm_rows_in_two_launches(lay, epi):
                 assert np.all(np.abs(host(cs)[blk] - rows.sum(0)) <= 1e-6 * (np.abs(rows).sum(0) + 1e-30)), (M, blk)
 
 
+@pytest.mark.parametrize("dt,tile_d,slices,tile_w", [("f32", 0, 1, 0), ("bf16", 0, 1, 0), ("bf16", 64, 1, 64),
+                                                     ("bf16", 64, 3, 128), ("bf16", 128, 1, 128), ("bf16", 128, 2, 64)])
+@pytest.mark.parametrize("gelu", [False, True])
+def test_linear_backward_in_one_launch(dt, tile_d, slices, tile_w, gelu):
+    """Input, weight and bias gradient of a linear layer from one launch, on
+    every pair of tiles, against float64: one row, rows around the tile
+    heights and past several, more input-gradient items than CUs (they run in
+    segments, the weight gradient's items between them) and fewer.  Bounds as
+    for the separate products: a stored bf16 rounds to 2^-9; fp32 sums of at
+    most 2048 terms stay below 1e-6 of the terms' norm."""
+    code, tdt = DTYPES[dt]
+    part = torch.full((64 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
+    shapes = [(1, 256, 512), (63, 512, 256), (129, 768, 512), (300, 256, 1024), (650, 256, 8192)]
+    if dt == "f32":
+        shapes = [(1, 64, 192), (33, 128, 64), (260, 768, 256), (2048, 256, 1024)]
+    for T, n_out, n_in in shapes:
+        dy, W, X = rnd((T, n_out), 51, dt=dt), rnd((n_out, n_in), 52, 0.1, dt=dt), rnd((T, n_in), 53, dt=dt)
+        Z, dw0, db0 = rnd((T, n_in), 54, dt=dt), rnd((n_out, n_in), 55, dt="f32"), rnd((n_out,), 56, dt="f32")
+        y64 = dy.astype(np.float64)
+        ref = y64 @ W.astype(np.float64)
+        if gelu:
+            ref = ref * oracle.gelu_grad(Z.astype(np.float64))
+        dX = torch.full((T, n_in), float("nan"), dtype=tdt, device="cuda")
+        dW, db = dev(dw0, "f32"), dev(db0, "f32")
+        F.fl_test_linear_backward(code, dev(dy, dt), dev(W, dt), dev(X, dt), dev(Z, dt) if gelu else None, dX, dW,
+                                  db if T != 63 else None, T, n_out, n_in, part, tile_d, slices, tile_w)
+        sync()
+        assert rel_l2(host(dX), ref) < (1e-6 if dt == "f32" else TOL[dt] / 4), (T, n_out, n_in)
+        assert rel_l2(host(dW), y64.T @ X.astype(np.float64) + dw0) < 1e-6, (T, n_out, n_in)
+        want = db0 + (y64.sum(0) if T != 63 else 0)
+        assert np.all(np.abs(host(db) - want) <= 1e-6 * (np.abs(y64).sum(0) + np.abs(db0))), (T, n_out, n_in)
+
+
 @pytest.mark.parametrize("M", [700, 256, 1])
 def test_gemm_gelu_bwd_column_sums(M):
     """The GeLU' input-gradient GEMM also writes, per 256-row block, the
