@@ -57,12 +57,13 @@ struct Tile {
   static constexpr int kWTM = BM / (16 * WM), kWTN = BN / (16 * WN);
   static constexpr int kRegA = BM * 66, kRegB = BN * 66;  // elements, room for either layout's padding
   static constexpr int kSlot = kRegA + kRegB;
-  static constexpr bool kBig = BM == 256;
+  static constexpr bool kBig = BM >= 192;  // one workgroup per CU, persistent
   // epilogue staging: the whole tile as fp32 where it fits, else one wave row at a time
   static constexpr int kPasses = BM * BN * 4 <= S * kSlot * 2 ? 1 : WM;
   static_assert(BM / kPasses * BN * 4 <= S * kSlot * 2, "staging");
 };
 using Tile256 = Tile<256, 256, 2, 4, 2, 1>;   // 132 KB
+using Tile192 = Tile<192, 256, 2, 4, 2, 1>;   // 116 KB
 using Tile128 = Tile<128, 256, 2, 4, 3, 1>;   // 149 KB
 using Tile64 = Tile<64, 128, 1, 4, 3, 2>;     // 74 KB
 // weight gradients: more workgroups per CU, so that one's fp32 read-modify-
@@ -115,9 +116,15 @@ __device__ __forceinline__ void dma16(i32x4 rs, uint32_t lds_inst_base, uint32_t
 // 2-4, for which these reads are 2-way conflicted; a placement free of that
 // (1056-byte blocks, row parities 512 bytes apart) measured no faster.
 // Instruction inst fills block inst.
+// ROWS = 192: a wave's six 16-row groups would straddle the 64-row sets, so
+// the two wave rows' groups alternate instead (group place 2 j + w holds group
+// 6 w + j): every fragment is again a wave base plus a constant.
+template <int ROWS>
 __device__ __forceinline__ uint32_t k_src(long ld, int inst, int lane) {
   const int slot = lane >> 3;
-  const int row = 16 * (4 * (inst >> 3) + (slot >> 1)) + (inst & 7) + 8 * (slot & 1);
+  int q = 4 * (inst >> 3) + (slot >> 1);
+  if constexpr (ROWS == 192) q = 6 * (q & 1) + (q >> 1);
+  const int row = 16 * q + (inst & 7) + 8 * (slot & 1);
   return (uint32_t)(row * ld + (lane & 7) * 8) * 2u;
 }
 // MN-contiguous tile: 4 column blocks of 64 columns (kMCol elements each),
@@ -156,8 +163,14 @@ __device__ __forceinline__ int frag_m_base(int col0, int fr, int fg) {
   return (col0 >> 6) * kMCol + 16 * ((col0 >> 4) & 3) + (fr >> 2) * kMBlock + ((fg & 1) + 4 * (fg >> 1)) * 64 +
          4 * (fr & 3);
 }
+template <int ROWS>
+__device__ __forceinline__ int frag_k_base(int w, int rows, int fr, int fg) {
+  return ROWS == 192 ? frag_k_base(16 * w, fr, fg) : frag_k_base(w * rows, fr, fg);
+}
+template <int ROWS>
 __device__ __forceinline__ bf16x8 frag_k(const bf16* tile, int base, int c, int j) {
-  return __builtin_bit_cast(bf16x8, ld16(tile + base + 8 * kKBlock * (j >> 2) + 128 * (j & 3) + 32 * c));
+  const int off = ROWS == 192 ? 8 * kKBlock * (j >> 1) + 256 * (j & 1) : 8 * kKBlock * (j >> 2) + 128 * (j & 3);
+  return __builtin_bit_cast(bf16x8, ld16(tile + base + off + 32 * c));
 }
 __device__ __forceinline__ bf16x8 frag_m(const bf16* tile, int base, int c, int j) {
   const bf16* p = tile + base + 16 * (j & 3) + kMCol * (j >> 2) + 4 * kMBlock * c;
@@ -273,7 +286,8 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
     wg_barrier();
     // Rows wave + kWaves q, q = kRpi t + sh (t = 0 .. kSteps - 1), in batches
     // of steps whose global loads are issued together before their first use.
-    constexpr int kB = STEPS < kSteps ? STEPS : kSteps;
+    constexpr int kB = kSteps % STEPS == 0 ? STEPS : kSteps < STEPS ? kSteps : kSteps / 2;
+    static_assert(kSteps % kB == 0, "whole batches");
 #pragma unroll
     for (int t0 = 0; t0 < kSteps; t0 += kB) {
       Vec8<bf16> ext[kB];
@@ -342,7 +356,7 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     wg_barrier();
   }
-  if constexpr (EPI == EPI_GELU_BWD && TL::kBig) {
+  if constexpr (EPI == EPI_GELU_BWD && TL::kBM == kColsumRows) {
     if (p.colsum) {
       // the sixteen half-waves' partial column sums, added in (wave, half)
       // order (the operand tiles are free: every wave passed the barrier)
@@ -452,10 +466,10 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
   uint32_t voa[kDmaA], vob[kDmaB];
 #pragma unroll
   for (int i = 0; i < kDmaA; ++i)
-    voa[i] = AK ? k_src(p.lda, i * kDmaStride + wq, lane) : m_src(p.lda, i * kDmaStride + wq, lane);
+    voa[i] = AK ? k_src<kBM>(p.lda, i * kDmaStride + wq, lane) : m_src(p.lda, i * kDmaStride + wq, lane);
 #pragma unroll
   for (int i = 0; i < kDmaB; ++i)
-    vob[i] = BKc ? k_src(p.ldb, i * kDmaStride + wq, lane) : m_src(p.ldb, i * kDmaStride + wq, lane);
+    vob[i] = BKc ? k_src<kBN>(p.ldb, i * kDmaStride + wq, lane) : m_src(p.ldb, i * kDmaStride + wq, lane);
   // byte offset of reduction index k0 along each operand
   auto kstep_a = [&](int k0) { return AK ? (uint32_t)k0 * 2u : (uint32_t)((long)k0 * p.lda * 2); };
   auto kstep_b = [&](int k0) { return BKc ? (uint32_t)k0 * 2u : (uint32_t)((long)k0 * p.ldb * 2); };
@@ -476,8 +490,8 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
       for (int g = 0; g < kDma; ++g) dma_one(kt, slot, g);
     }
   };
-  const int abase = AK ? frag_k_base(wm * 16 * kWTM, fr, fg) : frag_m_base(wm * 16 * kWTM, fr, fg);
-  const int bbase = BKc ? frag_k_base(wn * 16 * kWTN, fr, fg) : frag_m_base(wn * 16 * kWTN, fr, fg);
+  const int abase = AK ? frag_k_base<kBM>(wm, 16 * kWTM, fr, fg) : frag_m_base(wm * 16 * kWTM, fr, fg);
+  const int bbase = BKc ? frag_k_base<kBN>(wn, 16 * kWTN, fr, fg) : frag_m_base(wn * 16 * kWTN, fr, fg);
 
   f32x4 acc[kWTN][kWTM];
 #pragma unroll
@@ -487,11 +501,11 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
 
   auto rd_a = [&](int slot, int c, int j) {
     const bf16* as = smem + slot * kSlot;
-    return AK ? frag_k(as, abase, c, j) : frag_m(as, abase, c, j);
+    return AK ? frag_k<kBM>(as, abase, c, j) : frag_m(as, abase, c, j);
   };
   auto rd_b = [&](int slot, int c, int i) {
     const bf16* bs = smem + slot * kSlot + TL::kRegA;
-    return BKc ? frag_k(bs, bbase, c, i) : frag_m(bs, bbase, c, i);
+    return BKc ? frag_k<kBN>(bs, bbase, c, i) : frag_m(bs, bbase, c, i);
   };
   // fragments of reduction half c of the stage in slot `slot`
   auto load_frags = [&](int slot, int c, bf16x8 (&af)[kWTM], bf16x8 (&bf)[kWTN]) {
@@ -718,25 +732,28 @@ struct GemmPart {
   int rows, tile, slices;
 };
 
-// Estimated time (us) of an NT or NN product of M rows on 64-, 128- or 256-row
-// tiles with its reduction in s slices, fitted to a sweep on MI355X (M 16 ..
-// 4409, N and K of hidden 1280 and 4096, every tile and slice count): a
-// 64-wide stage takes 0.45 us with one 64-row workgroup on a CU and 0.72 with
+// Estimated time (us) of an NT or NN product of M rows on 64-, 128-, 192- or
+// 256-row tiles with its reduction in s slices, fitted to a sweep on MI355X (M
+// 16 .. 6000, N and K of hidden 1280 and 4096, every tile and slice count): a
+// 64-wide stage takes 0.45 us with one 64-row workgroup on a CU and 0.64 with
 // two, 0.79 for a 128-row one and 1.31 for a 256-row one; slices cost the
 // round trip of their fp32 sums and a launch.  Choosing by it comes within 1 %
-// (geometric mean) of the fastest choice of each product.
+// (geometric mean) of the fastest choice of each product.  192-row tiles are
+// taken as 0.79 of a 256-row one, as measured on long products, where the
+// clock falls as more CUs are busy (1295 x 130560 x 4096: 1244 us against
+// 1375); short ones reach 0.77.
 double part_us(int M, int N, int K, int tile, int s) {
   const double n = (double)(K / kBK) / s;
+  const long items = (long)((M + tile - 1) / tile) * (N / (tile == 64 ? 128 : 256)) * s;
+  const double rounds = (double)((items + 255) / 256);
   double t;
   if (tile == 64) {
-    const long items = (long)((M + 63) / 64) * (N / 128) * s, full = items / 512, rem = items % 512;
-    t = 2.0 + 0.97 * (full + (rem > 0)) + n * (0.723 * full + (rem > 256 ? 0.723 : rem > 0 ? 0.449 : 0.0));
+    const long full = items / 512, rem = items % 512;
+    t = 2.0 + 0.97 * (full + (rem > 0)) + n * (0.64 * full + (rem > 256 ? 0.64 : rem > 0 ? 0.449 : 0.0));
   } else if (tile == 128) {
-    const long items = (long)((M + 127) / 128) * (N / 256) * s;
-    t = 2.4 + (double)((items + 255) / 256) * (4.5 + 0.791 * n);
+    t = 2.4 + rounds * (4.5 + 0.791 * n);
   } else {
-    const long items = (long)((M + 255) / 256) * (N / 256) * s;
-    t = 3.7 + (double)((items + 255) / 256) * (11.9 + 1.31 * n);
+    t = 3.7 + rounds * (tile == 192 ? 9.4 + 1.035 * n : 11.9 + 1.31 * n);
   }
   t = std::max(t, 4.5 + 2.0 * N * (double)K / 7.03e6);
   if (s > 1) {
@@ -746,16 +763,31 @@ double part_us(int M, int N, int K, int tile, int s) {
   return t;
 }
 
+// The same with the column sums of C where they are asked for: whole 256-row
+// tiles form them in their epilogue, the others in another pass over C.
+double part_us(const GemmDesc& d, int M, int tile, int s) {
+  const bool pass = d.colsum && (tile != kColsumRows || s > 1);
+  return part_us(M, d.N, d.K, tile, s) + (pass ? 4.0 + 2.0 * M * (double)d.N / 4.5e6 : 0.0);
+}
+
+constexpr int kTiles[] = {64, 128, 192, 256};
 constexpr int kSlices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
 
-// Best single launch for M rows (slices only as far as the scratch allows and
-// at least two stages each).
-double best_part(int M, int N, int K, size_t part_bytes, bool big, GemmPart* out) {
+// Whether M rows may run in s slices: as far as the scratch allows, of at
+// least two stages each.  192-row tiles are not sliced (1295 x 4096 x 130560 in
+// two slices 1346 us, on 256- and 128-row tiles in four and five 1208).
+bool slices_fit(const GemmDesc& d, int M, int tile, int s) {
+  const size_t bytes = d.part ? d.part_bytes : 0;
+  return s == 1 || (tile != 192 && (size_t)s * M * d.N * 4 <= bytes && 2 * s <= d.K / kBK);
+}
+
+// Best single launch for M rows on tiles of at most `most` rows.
+double best_part(const GemmDesc& d, int M, int most, GemmPart* out) {
   double best = 1e30;
-  for (int tile = 64; tile <= (big ? 256 : 128); tile *= 2)
+  for (int tile : kTiles)
     for (int s : kSlices) {
-      if (s > 1 && ((size_t)s * M * N * 4 > part_bytes || 2 * s > K / kBK)) break;
-      const double t = part_us(M, N, K, tile, s);
+      if (tile > most || !slices_fit(d, M, tile, s)) break;
+      const double t = part_us(d, M, tile, s);
       if (t < best) {
         best = t;
         *out = GemmPart{M, tile, s};
@@ -767,19 +799,19 @@ double best_part(int M, int N, int K, size_t part_bytes, bool big, GemmPart* out
 // NT / NN: one launch over all rows, or two: as many whole rounds of large
 // tiles as fill every CU, and the remaining rows on the shape that suits them.
 int plan_rows(const GemmDesc& d, GemmPart (&parts)[2]) {
-  const size_t pb = d.part ? d.part_bytes : 0;
-  double best = best_part(d.M, d.N, d.K, pb, true, &parts[0]);
+  double best = best_part(d, d.M, 256, &parts[0]);
   int n = 1;
   if (d.M <= 256) return n;
   const int nt = d.N / 256;
-  for (int tile = 128; tile <= 256; tile *= 2)
-    for (int s = 1; s <= 4; ++s) {
+  for (int tile : kTiles)
+    for (int s = 1; tile > 64 && s <= 4; ++s) {
       const long rows_t = d.M / tile;  // whole tile rows
-      long k = rows_t * nt * s / 256 * 256 / ((long)nt * s);
-      const int m1 = (int)(k * tile) / 256 * 256;
-      if (m1 <= 0 || m1 >= d.M || (s > 1 && ((size_t)s * m1 * d.N * 4 > pb || 2 * s > d.K / kBK))) continue;
+      const long k = rows_t * nt * s / 256 * 256 / ((long)nt * s);
+      int m1 = (int)(k * tile);
+      if (d.colsum) m1 = m1 / kColsumRows * kColsumRows;  // the second launch starts a block of column sums
+      if (m1 <= 0 || m1 >= d.M || !slices_fit(d, m1, tile, s)) continue;
       GemmPart rest;
-      const double t = part_us(m1, d.N, d.K, tile, s) + best_part(d.M - m1, d.N, d.K, pb, false, &rest);
+      const double t = part_us(d, m1, tile, s) + best_part(d, d.M - m1, 128, &rest);
       // (5 % for what the estimate does not see; also keeps the choice of rows
       // that are close to whole rounds anyway)
       if (t < 0.95 * best) {
@@ -852,6 +884,7 @@ hipError_t launch_tokens(const GemmDesc& d, hipStream_t st) {
     const bool fused = parts[i].tile == 256 && parts[i].slices == 1;
     if (fused) a.colsum = colsum;
     hipError_t e = parts[i].tile == 256   ? launch_rows<true, BKc, EPI, Tile256>(a, st)
+                   : parts[i].tile == 192 ? launch_rows<true, BKc, EPI, Tile192>(a, st)
                    : parts[i].tile == 128 ? launch_rows<true, BKc, EPI, Tile128>(a, st)
                                           : launch_rows<true, BKc, EPI, Tile64>(a, st);
     if (e == hipSuccess && colsum && !fused)

@@ -36,7 +36,7 @@ struct GemmDesc {
   // receives, per 256-row block, the column sums of the stored C (the
   // layout colsum_partial writes, so colsum_finish completes them).
   float* colsum = nullptr;
-  // bf16 LDS-DMA kernel: tile height (256, 128 or 64) and reduction slices
+  // bf16 LDS-DMA kernel: tile height (256, 192, 128 or 64) and reduction slices
   // (NT and NN, with scratch) to use for all rows; 0: chosen from the shape.
   int tile = 0, slices = 1;
 };

@@ -79,7 +79,8 @@ int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void
   d.b_rows = b_rows;
   d.res_scale = res_scale;
   if (tile) {
-    if (tile != 64 && tile != 128 && tile != 256) return set_error(FL_ERR_ARG, "tile must be 0, 64, 128 or 256");
+    if (tile != 64 && tile != 128 && tile != 256 && (tile != 192 || layout == FL_GEMM_TN))
+      return set_error(FL_ERR_ARG, "tile must be 0, 64, 128, 192 (NT and NN) or 256");
     if (dtype != FL_BF16 || !gemm_bf16_dma_ok((GemmLayout)layout, d))
       return set_error(FL_ERR_ARG, "a forced tile needs a product the LDS-DMA kernel takes");
     if (slices < 1 || (layout == FL_GEMM_TN && slices != 1) || slices > (K + 63) / 64)

@@ -98,7 +98,7 @@ TILED = [(F.FL_GEMM_NT, F.FL_EPI_STORE), (F.FL_GEMM_NT, F.FL_EPI_BIAS), (F.FL_GE
          (F.FL_GEMM_NN, F.FL_EPI_RES), (F.FL_GEMM_TN, F.FL_EPI_ACC_F32)]
 
 
-@pytest.mark.parametrize("tile,slices", [(64, 1), (64, 3), (64, 7), (128, 1), (128, 2), (128, 5), (256, 1), (256, 4)])
+@pytest.mark.parametrize("tile,slices", [(64, 1), (64, 3), (64, 7), (128, 1), (128, 2), (128, 5), (192, 1), (192, 3), (256, 1), (256, 4)])
 @pytest.mark.parametrize("lay,epi", TILED)
 def test_gemm_tiles_and_slices(lay, epi, tile, slices):
     """The bf16 kernel on every tile height and number of reduction slices,
@@ -107,8 +107,8 @@ def test_gemm_tiles_and_slices(lay, epi, tile, slices):
     stages than a tile's ring of slots and of many.  Stored bf16 rounds to
     2^-9 of a value and the fp32 sums of K <= 1024 terms stay far below that:
     5e-3 relative L2 (TOL / 4)."""
-    if lay == F.FL_GEMM_TN and slices > 1:
-        pytest.skip("weight gradients are not sliced")
+    if lay == F.FL_GEMM_TN and (slices > 1 or tile == 192):
+        pytest.skip("weight gradients are not sliced and have no 192-row tile")
     part = torch.full((16 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
     for M, N, K in ((1, 256, 64), (tile - 1, 256, 192), (tile, 512, 448), (tile + 1, 256, 1024), (300, 768, 512)):
         if lay == F.FL_GEMM_TN:
