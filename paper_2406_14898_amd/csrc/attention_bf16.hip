@@ -996,7 +996,7 @@ hipError_t fwd_launch(const AttnDesc& a, hipStream_t st) {
 
 template <int D>
 hipError_t bwd_launch(const AttnDesc& a, hipStream_t st) {
-  hipError_t e = attn_delta(DT_BF16, a, st);
+  hipError_t e = attn_delta(a, st);
   if (e != hipSuccess) return e;
   const dim3 gkv = wg_grid((a.num_prefix + 63) / 64 + (a.max_seqlen + 63) / 64, a.num_heads, a.num_seqs);
   if (a.ds) {

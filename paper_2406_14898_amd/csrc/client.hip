@@ -484,8 +484,8 @@ int fl_lm_head_backward(fl_client* c, const void* h, const void* ln_g, const voi
     if (dln_g) {
       const int nb = colsum_blocks((int)T);
       CK(colsum_partial(dt_of(c), 1, w.dhn, H, h, w.mean, w.rstd, (int)T, (int)H, w.ln_part, w.ln_part2, s));
-      CK(colsum_finish(w.ln_part, nb, (int)H, dln_g, s));
-      CK(colsum_finish(w.ln_part2, nb, (int)H, dln_b, s));
+      const ColsumJob jobs[2] = {{w.ln_part, dln_g, nb, (int)H}, {w.ln_part2, dln_b, nb, (int)H}};
+      CK(colsum_finish_n(jobs, 2, s));
     }
   }
   if (!dw_vocab) return FL_OK;

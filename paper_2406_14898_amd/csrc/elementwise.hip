@@ -666,18 +666,21 @@ hipError_t colsum_direct(DType dt, const void* X, long ldx, int T_, int N, float
 // out[n] += sum over the nblk partial rows.  A workgroup takes 64 columns;
 // its 16 waves sum contiguous sixteenths of the rows (eight loads in flight
 // per lane), and the sixteenths are added in order through LDS: a fixed
-// order, so the result is deterministic.  Up to three (partial, out) pairs
-// of one shape go in one launch (grid y).
+// order, so the result is deterministic.  Several jobs go in one launch (grid
+// y): a block's three finishes of a few hundred rows are launch and ramp only
+// (each 3 to 5 us).
 struct FinishSet {
-  const float* part[3];
-  float* out[3];
+  ColsumJob job[kColsumJobs];
 };
-__global__ void __launch_bounds__(1024) colsum_finish_kernel(FinishSet fs, int nblk, int N) {
+__global__ void __launch_bounds__(1024) colsum_finish_kernel(FinishSet fs) {
   constexpr int NW = 16;
   __shared__ float q[NW][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int n = blockIdx.x * 64 + lane;
-  const float* part = fs.part[blockIdx.y];
+  const ColsumJob job = fs.job[blockIdx.y];
+  const float* part = job.part;
+  const int nblk = job.nblk, N = job.N;
+  if (blockIdx.x * 64 >= N) return;
   const int per = (nblk + NW - 1) / NW;
   const int b0 = min(nblk, w * per), b1 = min(nblk, b0 + per);
   float s = 0.f;
@@ -698,22 +701,27 @@ __global__ void __launch_bounds__(1024) colsum_finish_kernel(FinishSet fs, int n
     float t = q[0][lane];
 #pragma unroll
     for (int v = 1; v < NW; ++v) t += q[v][lane];
-    fs.out[blockIdx.y][n] += t;
+    job.out[n] += t;
   }
 }
 
-hipError_t colsum_finish_n(const float* const* parts, float* const* outs, int count, int nblk, int N,
-                           hipStream_t st) {
-  if (N <= 0 || count <= 0) return hipSuccess;
-  if (count > 3) return hipErrorInvalidValue;
+hipError_t colsum_finish_n(const ColsumJob* jobs, int count, hipStream_t st) {
+  if (count <= 0) return hipSuccess;
+  if (count > kColsumJobs) return hipErrorInvalidValue;
   FinishSet fs{};
-  for (int i = 0; i < count; ++i) { fs.part[i] = parts[i]; fs.out[i] = outs[i]; }
-  hipLaunchKernelGGL(colsum_finish_kernel, dim3((N + 63) / 64, count), dim3(1024), 0, st, fs, nblk, N);
+  int N = 0;
+  for (int i = 0; i < count; ++i) {
+    fs.job[i] = jobs[i];
+    N = std::max(N, jobs[i].N);
+  }
+  if (N <= 0) return hipSuccess;
+  hipLaunchKernelGGL(colsum_finish_kernel, dim3((N + 63) / 64, count), dim3(1024), 0, st, fs);
   return hipGetLastError();
 }
 
 hipError_t colsum_finish(const float* part, int nblk, int N, float* out, hipStream_t st) {
-  return colsum_finish_n(&part, &out, 1, nblk, N, st);
+  const ColsumJob job{part, out, nblk, N};
+  return colsum_finish_n(&job, 1, st);
 }
 
 // ---------------------------------------------------------------------------

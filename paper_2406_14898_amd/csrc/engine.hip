@@ -286,7 +286,9 @@ struct Work {
   void *dz, *dh, *tmp, *dqkv;
   float* delta;
   float *part, *part2;
-  float* lnp[3];  // fused LayerNorm backward partials: gain, shift, output sums, [kLnBlocks][H] each
+  // fused LayerNorm backward partials of both LayerNorms: gain, shift, output
+  // sums, [ln_blocks(T)][H] each
+  float* lnp[2][3];
   float* dprefix;
   // stored attention softmax gradient (bf16, see attn_ds_tiles) and its
   // per-sequence offsets; null above kAttnDsMaxBytes (dq then recomputes it)
@@ -318,7 +320,7 @@ void carve_work(Carver& cv, const fl_stack* st, const BatchInfo& bi, Work* w) {
   const size_t nmax = std::max(F, 3 * H);
   w->part = (float*)cv.take(sizeof(float) * colsum_blocks(bi.T) * nmax);
   w->part2 = (float*)cv.take(sizeof(float) * colsum_blocks(bi.T) * nmax);
-  for (int i = 0; i < 3; ++i) w->lnp[i] = (float*)cv.take(sizeof(float) * kLnBlocks * H);
+  for (int i = 0; i < 6; ++i) w->lnp[i / 3][i % 3] = (float*)cv.take(sizeof(float) * ln_blocks(bi.T) * H);
   // per-sequence P-tuning v2 prefix gradients, [2][S][L_p][H] fp32
   const size_t np = st->d.num_prefix;
   w->dprefix = np ? (float*)cv.take(sizeof(float) * 2 * bi.S * np * H) : nullptr;
@@ -568,31 +570,43 @@ int colsum_into(fl_stack* st, DType dt, const void* X, long ldx, int T, int N, f
   return FL_OK;
 }
 
+// Column sums whose partials are complete: added to their outputs in one
+// launch at the block's end, or at once where launch timing counts each.
+struct Finishes {
+  ColsumJob job[kColsumJobs];
+  int n = 0;
+  void add(const float* part, float* out, int nblk, int N) { job[n++] = ColsumJob{part, out, nblk, N}; }
+};
+int flush(fl_stack* st, Finishes& f, hipStream_t s) {
+  if (f.n == 0) return FL_OK;
+  double bytes = 0;
+  for (int i = 0; i < f.n; ++i) bytes += 4.0 * f.job[i].nblk * f.job[i].N;
+  LAUNCH(FL_PROF_COLSUM, 0, bytes, colsum_finish_n(f.job, f.n, s));
+  f.n = 0;
+  return FL_OK;
+}
+int flush_if_timed(fl_stack* st, Finishes& f, hipStream_t s) {
+  return st->prof_mask >> FL_PROF_COLSUM & 1u ? flush(st, f, s) : FL_OK;
+}
+
 // LayerNorm backward: dx = dres + LN^T(dy); gain / shift gradients (NULL:
 // frozen) += their column sums and, with dsum, dsum += the column sums of dx
 // (the bias gradient of the projection that produced the LayerNorm's
 // input), all in the one pass over dy and x.
 int ln_backward(fl_stack* st, DType dt, const void* dy, const void* xin, const float* mean, const float* rstd,
                 const void* gamma, const void* dres, void* dx, float* dgamma, float* dbeta, float* dsum, int T, int H,
-                const Work& w, hipStream_t s) {
+                float* const (&lnp)[3], Finishes& fin, hipStream_t s) {
   const double TH = (double)T * H, E = st->E;
   LAUNCH(FL_PROF_LAYERNORM_BWD, 0, (dres ? 4 : 3) * TH * E + 8.0 * T,
-         layernorm_bwd_fused(dt, dy, xin, mean, rstd, gamma, dres, dx, T, H, dgamma ? w.lnp[0] : nullptr,
-                             dgamma ? w.lnp[1] : nullptr, dsum ? w.lnp[2] : nullptr, s));
-  if (!dgamma && !dsum) return FL_OK;
+         layernorm_bwd_fused(dt, dy, xin, mean, rstd, gamma, dres, dx, T, H, dgamma ? lnp[0] : nullptr,
+                             dgamma ? lnp[1] : nullptr, dsum ? lnp[2] : nullptr, s));
   const int nblk = ln_blocks(T);
-  LAUNCH(FL_PROF_COLSUM, 0, 4.0 * nblk * H * ((dgamma ? 2 : 0) + (dsum ? 1 : 0)), [&]() {
-    const float* parts[3];
-    float* outs[3];
-    int n = 0;
-    if (dgamma) {
-      parts[n] = w.lnp[0]; outs[n++] = dgamma;
-      parts[n] = w.lnp[1]; outs[n++] = dbeta;
-    }
-    if (dsum) { parts[n] = w.lnp[2]; outs[n++] = dsum; }
-    return colsum_finish_n(parts, outs, n, nblk, H, s);
-  }());
-  return FL_OK;
+  if (dgamma) {
+    fin.add(lnp[0], dgamma, nblk, H);
+    fin.add(lnp[1], dbeta, nblk, H);
+  }
+  if (dsum) fin.add(lnp[2], dsum, nblk, H);
+  return flush_if_timed(st, fin, s);
 }
 
 // One block backward: dy -> dx, gradients += .
@@ -612,6 +626,7 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   // feed y and h, so dy and dh join the LayerNorm inputs' gradients (in the
   // input-gradient GEMMs' epilogues) instead of passing straight through
   const float alpha = st->d.residual_alpha;
+  Finishes fin;
   int rc;
   // A linear layer's input gradient gd and weight gradient gw, with the bias
   // gradient `bias` += the column sums of the output gradient (NULL: formed
@@ -672,7 +687,7 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   // w = LN2(h); h also feeds y directly (plain residual).  db_o = the column
   // sums of dh, formed in the same pass.
   if ((rc = ln_backward(st, dt, w.tmp, a.h, a.mean2, a.rstd2, p.ln2_g, alpha > 0.f ? nullptr : dy, w.dh, gr.ln2_g,
-                        gr.ln2_b, train_w ? gr.b_o : nullptr, T, H, w, s)))
+                        gr.ln2_b, train_w ? gr.b_o : nullptr, T, H, w.lnp[1], fin, s)))
     return rc;
   // h = x + o W_o^T + b_o
   gd = grad_in(w.dh, p.w_o, w.tmp, H, H);
@@ -712,9 +727,10 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
            prefix_grad_reduce(w.dprefix, bi.S, n, gr.prefix_k, gr.prefix_v, s));
   }
   // qkv = u W_qkv^T + b_qkv
-  if (fused_bqkv)
-    LAUNCH(FL_PROF_COLSUM, 0, 4.0 * w.bias_rows * 3 * H,
-           colsum_finish(w.bias_part, w.bias_rows, 3 * H, gr.b_qkv, s));
+  if (fused_bqkv) {
+    fin.add(w.bias_part, gr.b_qkv, w.bias_rows, 3 * H);
+    if ((rc = flush_if_timed(st, fin, s))) return rc;
+  }
   gd = grad_in(w.dqkv, p.w_qkv, w.tmp, 3 * H, H);
   gw = grad_w(w.dqkv, a.u, gr.w_qkv, 3 * H, H);
   if (alpha > 0.f) {
@@ -723,8 +739,10 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   if ((rc = linear(FL_PROF_GEMM_NN, alpha > 0.f ? EPI_RES : EPI_STORE, gd, gw, fused_bqkv ? nullptr : gr.b_qkv)))
     return rc;
   // u = LN1(x); x also feeds h directly (plain residual)
-  return ln_backward(st, dt, w.tmp, x, a.mean1, a.rstd1, p.ln1_g, alpha > 0.f ? nullptr : w.dh, dx, gr.ln1_g,
-                     gr.ln1_b, dx_sum, T, H, w, s);
+  if ((rc = ln_backward(st, dt, w.tmp, x, a.mean1, a.rstd1, p.ln1_g, alpha > 0.f ? nullptr : w.dh, dx, gr.ln1_g,
+                        gr.ln1_b, dx_sum, T, H, w.lnp[0], fin, s)))
+    return rc;
+  return flush(st, fin, s);
 }
 
 }  // namespace

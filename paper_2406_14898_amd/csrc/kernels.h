@@ -155,9 +155,14 @@ hipError_t colsum_finish(const float* partial, int nblk, int N, float* out, hipS
 // multiple of 64): out[n] += sum_t X[t][n].
 constexpr int kColsumDirectRows = 2048;
 hipError_t colsum_direct(DType dt, const void* X, long ldx, int T, int N, float* out, hipStream_t st);
-// colsum_finish of up to three partial arrays of one shape in one launch.
-hipError_t colsum_finish_n(const float* const* partials, float* const* outs, int count, int nblk, int N,
-                           hipStream_t st);
+// Several of them (different out) in one launch.
+struct ColsumJob {
+  const float* part;
+  float* out;
+  int nblk, N;
+};
+constexpr int kColsumJobs = 8;
+hipError_t colsum_finish_n(const ColsumJob* jobs, int count, hipStream_t st);
 
 // P-tuning v2 prefix gradients: out_k += sum_s part[0][s], out_v += sum_s
 // part[1][s] over n = num_prefix * hidden elements (n % 4 == 0; fixed order).
@@ -177,7 +182,7 @@ struct AttnDesc {
   // backward
   const void* dout = nullptr;
   long ld_dout = 0;
-  float* delta = nullptr;  // [T, nh] scratch: rowsum(dO * O)
+  float* delta = nullptr;  // [T, nh] scratch of the bf16 kernels: rowsum(dO * O)
   void* dqkv = nullptr;    // [T, 3H]
   long ld_dqkv = 0;
   // Inverse rotary of dq, dk fused into the kernels' epilogues, over dims
@@ -223,8 +228,8 @@ hipError_t attn_ds_offsets(const AttnDesc& a, hipStream_t st);
 inline size_t attn_ds_off_bytes(int num_seqs) { return ((size_t)(num_seqs + 1) * 8 + 255) / 256 * 256; }
 hipError_t attn_fwd(DType dt, const AttnDesc& a, hipStream_t st);
 hipError_t attn_bwd(DType dt, const AttnDesc& a, hipStream_t st);
-// delta[t][h] = rowsum(dO * O), the backward pre-pass.
-hipError_t attn_delta(DType dt, const AttnDesc& a, hipStream_t st);
+// delta[t][h] = rowsum(dO * O), the bf16 backward's pre-pass.
+hipError_t attn_delta(const AttnDesc& a, hipStream_t st);
 // bf16 LDS-DMA kernels (attention_bf16.hip), used by attn_fwd / attn_bwd.
 bool attn_bf16_ok(const AttnDesc& a);
 hipError_t attn_fwd_bf16(const AttnDesc& a, hipStream_t st);

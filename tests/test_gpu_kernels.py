@@ -650,6 +650,27 @@ def test_attention_fwd_bwd(dt, heads, bname):
         assert rel_l2(g[:, 2 * H:], dv.reshape(T, H)) < tol, (r, stored)
 
 
+@pytest.mark.parametrize("seqs", [31, 32])
+def test_attention_f32_query_tiles(seqs):
+    """The fp32 forward around the workgroup count where its query tile grows
+    from 64 to 128 rows (two 128-row tiles, four heads: 248 and 256), lengths
+    from one row to just past both tiles.  fp32 bounds as for any batch."""
+    nh, d = 4, 64
+    H = nh * d
+    lens = np.asarray([(1, 63, 64, 65, 127, 128, 129, 130)[i % 8] for i in range(seqs)])
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T = int(cu[-1])
+    b = synth.Batch(cu, np.asarray([0, seqs], np.int32), "causal", None)
+    qkv = _qkv(T, H, 57, "f32")
+    q, k, v = (qkv[:, i * H:(i + 1) * H].astype(np.float64).reshape(T, nh, d) for i in range(3))
+    o = torch.full((T, H), float("nan"), device="cuda")
+    lse = torch.full((T, nh), float("nan"), device="cuda")
+    F.fl_test_attention_fwd(F.FL_F32, dev(qkv, "f32"), o, lse, dev_i32(cu), None, T, seqs, 130, H, nh)
+    sync()
+    assert rel_l2(host(o), oracle.attention_forward(q, k, v, b).reshape(T, H)) < TOL["f32"] / 2
+    assert rel_l2(host(lse), _lse_ref(q, k, b)) < 1e-5
+
+
 @pytest.mark.parametrize("stored", [False, True])
 @pytest.mark.parametrize("mask", ["causal", "prefix"])
 def test_attention_long_sequence(mask, stored):
