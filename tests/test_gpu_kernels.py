@@ -135,6 +135,29 @@ def test_gemm_tiles_and_slices(lay, epi, tile, slices):
                 assert np.all(np.abs(host(cs)[blk] - rows.sum(0)) <= 1e-6 * (np.abs(rows).sum(0) + 1e-30)), (M, blk)
 
 
+@pytest.mark.parametrize("slices", [1, 2])
+@pytest.mark.parametrize("lay,epi", [t for t in TILED if t[0] != F.FL_GEMM_TN])
+def test_gemm_64_rows_long_reduction(lay, epi, slices):
+    """64-row tiles of at most one workgroup per CU around the reduction
+    length (48 stages a slice) from which they keep six stages in flight, and
+    with more workgroups than CUs, which never do.  fp32 sums of K <= 6144
+    terms stay far below the bf16 rounding of the result."""
+    part = torch.full((16 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
+    for M, N, K in ((1, 256, 3008), (65, 256, 3072), (300, 256, 6144), (1200, 2048, 3072)):
+        A, B, bias, R, _, ref, second = _tiled_case(lay, epi, M, N, K)
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        C2 = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        if slices * M * N * 4 > 16 << 20:
+            continue
+        F.fl_test_gemm(F.FL_BF16, lay, epi, dev(A, "bf16"), dev(B, "bf16"), C, M, N, K, A.shape[1], B.shape[1], N,
+                       bias=dev(bias, "bf16"), R=dev(R, "bf16"), ldr=N, C2=C2, ldc2=N, Z=dev(R, "bf16"), ldz=N,
+                       part=part, res_scale=1.5, tile=64, slices=slices)
+        sync()
+        assert rel_l2(host(C), ref) < TOL["bf16"] / 4, (M, N, K)
+        if second is not None:
+            assert rel_l2(host(C2), second) < TOL["bf16"] / 4, (M, N, K)
+
+
 @pytest.mark.parametrize("lay,epi", TILED)
 def test_gemm_f32_few_tiles(lay, epi):
     """fp32 products of few tiles, on both small tile sizes: one row, row
