@@ -34,8 +34,8 @@ extern "C" {
  * STORE/BIAS/BIAS_RES/BIAS_GELU, NN with STORE/GELU_BWD/RES, TN with ACC_F32.
  * res_scale multiplies R in BIAS_RES and RES (1: plain residual).
  * part / part_bytes: optional device fp32 scratch (16-byte aligned) that
- * lets the bf16 kernel split the reduction of a last, partial round of
- * tiles over more compute units (NULL / 0: never split).
+ * lets the bf16 kernel cut the reduction of products with few tiles into
+ * slices over more compute units (NULL / 0: never cut).
  * b_rows > 0: B holds only that many rows (its N index for NT, its
  * reduction index for NN and TN); the rest read as zero and are never
  * touched (0: B is complete).
