@@ -340,8 +340,12 @@ int fl_average_replicas(int32_t num_replicas, float* const* params, void* const*
 /* Launch timing (off by default).  While enabled, every kernel launch the
  * handle enqueues is bracketed by two HIP events on the call's stream and
  * tagged with its class and its algorithmic work (flops of the contraction,
- * minimal HBM bytes).  Enabling clears earlier records.  The overhead is two
- * event records per launch. */
+ * minimal HBM bytes).  A launch that does the work of several classes (few
+ * rows: a linear layer's input, weight and bias gradients; a block's finishing
+ * column sums) counts as one launch of each piece of work, with the launch's
+ * time shared out by their bytes.  Timing adds events only: the launches and
+ * their results are those of an untimed call.  Enabling clears earlier
+ * records.  The overhead is two event records per launch. */
 #define FL_PROF_PLAN 0              /* positions + rotary table */
 #define FL_PROF_LAYERNORM_FWD 1
 #define FL_PROF_GEMM_NT_BIAS 2      /* QKV projection */

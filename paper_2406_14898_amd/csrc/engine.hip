@@ -78,11 +78,15 @@ struct fl_stack {
   bool ev_made[kRing] = {};
   bool ev_used[kRing] = {};
   int next = 0;
-  // opt-in launch timing (fl_stack_profile)
+  // opt-in launch timing (fl_stack_profile); a launch that does the work of
+  // several classes has one record for each, on the same pair of events, with
+  // the share of the launch's time that the class is given
   struct Rec {
     int cls;
     hipEvent_t a, b;
     double flops, bytes;
+    double share;
+    bool owner;  // returns the events to the pool
   };
   uint32_t prof_mask = 0;  // bit c: launches of class c are timed
   std::vector<Rec> recs;
@@ -105,12 +109,26 @@ hipError_t take_event(fl_stack* st, hipEvent_t* e) {
   return hipEventCreate(e);
 }
 
-// Runs `launch` (returning hipError_t); when profiling is on, brackets it
-// with two events on stream s and records the launch's algorithmic work.
+// What one launch does for one class.
+struct ClassWork {
+  int cls;
+  double flops, bytes;
+};
+
+// Runs `launch` (returning hipError_t), which does the work of n classes; when
+// any of them is timed, brackets it with two events on stream s and records
+// every timed class's algorithmic work, with the share of the time that its
+// bytes are of the launch's (launches of several classes are bound by memory).
 template <class Fn>
-hipError_t timed(fl_stack* st, hipStream_t s, int cls, double flops, double bytes, Fn&& launch) {
-  if (!((st->prof_mask >> cls) & 1u)) return launch();
-  fl_stack::Rec r{cls, nullptr, nullptr, flops, bytes};
+hipError_t timed(fl_stack* st, hipStream_t s, const ClassWork* work, int n, Fn&& launch) {
+  double bytes = 0;
+  bool on = false;
+  for (int i = 0; i < n; ++i) {
+    bytes += work[i].bytes;
+    on = on || ((st->prof_mask >> work[i].cls) & 1u);
+  }
+  if (!on) return launch();
+  fl_stack::Rec r{};
   hipError_t e = take_event(st, &r.a);
   if (e != hipSuccess) return e;
   if ((e = take_event(st, &r.b)) != hipSuccess) {
@@ -124,8 +142,22 @@ hipError_t timed(fl_stack* st, hipStream_t s, int cls, double flops, double byte
   }
   e = launch();
   hipError_t e2 = hipEventRecord(r.b, s);
-  st->recs.push_back(r);
+  r.owner = true;
+  for (int i = 0; i < n; ++i) {
+    if (!((st->prof_mask >> work[i].cls) & 1u)) continue;
+    r.cls = work[i].cls;
+    r.flops = work[i].flops;
+    r.bytes = work[i].bytes;
+    r.share = n == 1 || bytes <= 0 ? 1.0 / n : work[i].bytes / bytes;
+    st->recs.push_back(r);
+    r.owner = false;
+  }
   return e != hipSuccess ? e : e2;
+}
+template <class Fn>
+hipError_t timed(fl_stack* st, hipStream_t s, int cls, double flops, double bytes, Fn&& launch) {
+  const ClassWork w{cls, flops, bytes};
+  return timed(st, s, &w, 1, launch);
 }
 
 }  // namespace
@@ -571,22 +603,21 @@ int colsum_into(fl_stack* st, DType dt, const void* X, long ldx, int T, int N, f
 }
 
 // Column sums whose partials are complete: added to their outputs in one
-// launch at the block's end, or at once where launch timing counts each.
+// launch at the block's end.  Launch timing counts each pass that formed some
+// (begin) as one column-sum launch.
 struct Finishes {
   ColsumJob job[kColsumJobs];
-  int n = 0;
-  void add(const float* part, float* out, int nblk, int N) { job[n++] = ColsumJob{part, out, nblk, N}; }
+  ClassWork work[kColsumJobs];
+  int n = 0, groups = 0;
+  void begin() { work[groups++] = ClassWork{FL_PROF_COLSUM, 0, 0}; }
+  void add(const float* part, float* out, int nblk, int N) {
+    job[n++] = ColsumJob{part, out, nblk, N};
+    work[groups - 1].bytes += 4.0 * nblk * N;
+  }
 };
-int flush(fl_stack* st, Finishes& f, hipStream_t s) {
-  if (f.n == 0) return FL_OK;
-  double bytes = 0;
-  for (int i = 0; i < f.n; ++i) bytes += 4.0 * f.job[i].nblk * f.job[i].N;
-  LAUNCH(FL_PROF_COLSUM, 0, bytes, colsum_finish_n(f.job, f.n, s));
-  f.n = 0;
+int flush(fl_stack* st, const Finishes& f, hipStream_t s) {
+  if (f.n > 0) HIP_OK(timed(st, s, f.work, f.groups, [&]() { return colsum_finish_n(f.job, f.n, s); }));
   return FL_OK;
-}
-int flush_if_timed(fl_stack* st, Finishes& f, hipStream_t s) {
-  return st->prof_mask >> FL_PROF_COLSUM & 1u ? flush(st, f, s) : FL_OK;
 }
 
 // LayerNorm backward: dx = dres + LN^T(dy); gain / shift gradients (NULL:
@@ -601,12 +632,13 @@ int ln_backward(fl_stack* st, DType dt, const void* dy, const void* xin, const f
          layernorm_bwd_fused(dt, dy, xin, mean, rstd, gamma, dres, dx, T, H, dgamma ? lnp[0] : nullptr,
                              dgamma ? lnp[1] : nullptr, dsum ? lnp[2] : nullptr, s));
   const int nblk = ln_blocks(T);
+  if (dgamma || dsum) fin.begin();
   if (dgamma) {
     fin.add(lnp[0], dgamma, nblk, H);
     fin.add(lnp[1], dbeta, nblk, H);
   }
   if (dsum) fin.add(lnp[2], dsum, nblk, H);
-  return flush_if_timed(st, fin, s);
+  return FL_OK;
 }
 
 // One block backward: dy -> dx, gradients += .
@@ -630,26 +662,23 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   int rc;
   // A linear layer's input gradient gd and weight gradient gw, with the bias
   // gradient `bias` += the column sums of the output gradient (NULL: formed
-  // elsewhere).  Few rows: one launch, unless launch timing tells the classes
-  // apart.
-  constexpr uint32_t kPairClasses = 1u << FL_PROF_GEMM_TN_ACC | 1u << FL_PROF_GEMM_NN |
-                                    1u << FL_PROF_GEMM_NN_GELU_BWD | 1u << FL_PROF_COLSUM;
-  const bool may_pair = train_w && !(st->prof_mask & kPairClasses);
+  // elsewhere).  Few rows: one launch for all of them.
   auto linear = [&](int cls, int epi, GemmDesc& gd, GemmDesc& gw, float* bias) -> int {
     with_part(gd, plan);
-    if (may_pair && gemm_pair_ok(dt, epi, gd, gw)) {
-      HIP_OK(gemm_pair(dt, epi, gd, gw, bias, s));
+    const int n_out = gd.K, n_in = gd.N;
+    const ClassWork cd{cls, gemm_flops(T, n_in, n_out), gemm_bytes(T, n_in, n_out, E, epi == EPI_GELU_BWD ? 2 * E : E)};
+    const ClassWork cw{FL_PROF_GEMM_TN_ACC, gemm_flops(n_out, n_in, T), gemm_bytes(n_out, n_in, T, E, 8)};
+    if (train_w && gemm_pair_ok(dt, epi, gd, gw)) {
+      const ClassWork all[3] = {cd, cw, {FL_PROF_COLSUM, 0, (double)T * n_out * E}};
+      HIP_OK(timed(st, s, all, bias ? 3 : 2, [&]() { return gemm_pair(dt, epi, gd, gw, bias, s); }));
       return FL_OK;
     }
-    const int n_out = gd.K, n_in = gd.N;
     if (train_w) {
       int r;
       if (bias && (r = colsum_into(st, dt, gd.A, n_out, T, n_out, bias, w, s))) return r;
-      LAUNCH(FL_PROF_GEMM_TN_ACC, gemm_flops(n_out, n_in, T), gemm_bytes(n_out, n_in, T, E, 8),
-             gemm(dt, GEMM_TN, EPI_ACC_F32, with_part(gw, plan), s));
+      LAUNCH(cw.cls, cw.flops, cw.bytes, gemm(dt, GEMM_TN, EPI_ACC_F32, with_part(gw, plan), s));
     }
-    LAUNCH(cls, gemm_flops(T, n_in, n_out), gemm_bytes(T, n_in, n_out, E, epi == EPI_GELU_BWD ? 2 * E : E),
-           gemm(dt, GEMM_NN, epi, gd, s));
+    LAUNCH(cd.cls, cd.flops, cd.bytes, gemm(dt, GEMM_NN, epi, gd, s));
     return FL_OK;
   };
   auto grad_in = [&](const void* dout, const void* weight, void* din, int n_out, int n_in) {
@@ -669,7 +698,7 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   // where the kernel supports it (no second pass over dz), else below
   // (few rows: only where that costs no pass of its own)
   with_part(gd, plan);
-  const bool b1_fused = train_w && !(may_pair && gemm_pair_ok(dt, EPI_GELU_BWD, gd, gw)) &&
+  const bool b1_fused = train_w && !gemm_pair_ok(dt, EPI_GELU_BWD, gd, gw) &&
                         gemm_fuses_colsum(dt, GEMM_NN, EPI_GELU_BWD, gd) &&
                         (T > kColsumDirectRows || gemm_epilogue_colsum(gd));
   if (b1_fused) gd.colsum = w.part;
@@ -728,8 +757,8 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
   }
   // qkv = u W_qkv^T + b_qkv
   if (fused_bqkv) {
+    fin.begin();
     fin.add(w.bias_part, gr.b_qkv, w.bias_rows, 3 * H);
-    if ((rc = flush_if_timed(st, fin, s))) return rc;
   }
   gd = grad_in(w.dqkv, p.w_qkv, w.tmp, 3 * H, H);
   gw = grad_w(w.dqkv, a.u, gr.w_qkv, 3 * H, H);
@@ -822,6 +851,7 @@ int fl_stack_destroy(fl_stack* st) {
   if (!st) return FL_OK;
   int rc = FL_OK;
   for (auto& r : st->recs) {
+    if (!r.owner) continue;
     st->pool.push_back(r.a);
     st->pool.push_back(r.b);
   }
@@ -842,6 +872,7 @@ int fl_stack_profile_classes(fl_stack* st, uint32_t class_mask) {
   class_mask &= (1u << FL_PROF_NUM_CLASSES) - 1u;
   if (class_mask) {
     for (auto& r : st->recs) {
+      if (!r.owner) continue;
       st->pool.push_back(r.a);
       st->pool.push_back(r.b);
     }
@@ -866,7 +897,7 @@ int fl_stack_profile_read(fl_stack* st, int cls, int64_t* launches, double* ms, 
     float t = 0.f;
     HIP_OK(hipEventElapsedTime(&t, r.a, r.b));
     *launches += 1;
-    *ms += t;
+    *ms += t * r.share;
     *flops += r.flops;
     *bytes += r.bytes;
   }

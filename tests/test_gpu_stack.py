@@ -348,6 +348,32 @@ def test_launch_profile_of_chosen_classes():
     assert none == some
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_launch_timing_runs_the_same_launches(dt):
+    """Timing adds events and nothing else: with every class timed, and with
+    one class at a time, y, dx and all gradients are bit for bit those of an
+    untimed call, where a linear layer's gradients share one launch (few rows)
+    and a block's column sums are finished together.  A class's work is the
+    same whichever other classes are timed."""
+    b = synth.make_batch(2, 2, (30, 170), "prefix", seed=21)
+    layers, x, dy = _inputs(b, dt, seed=21)
+    g = GpuStack(SHAPE, layers, dt)
+
+    def run(mask):
+        F.fl_stack_profile_classes(g.ss.handle, mask)
+        r = g.run(b, x, dy)
+        return [r["y"], r["dx"]] + [v for d in r["grads"] for v in d.values()], F.profile_table(g.ss.handle)
+    want, _ = run(0)
+    every = (1 << F.FL_PROF_NUM_CLASSES) - 1
+    got, full = run(every)
+    assert all(torch.equal(p, q) for p, q in zip(want, got))
+    for c in range(F.FL_PROF_NUM_CLASSES):
+        got, one = run(1 << c)
+        assert all(torch.equal(p, q) for p, q in zip(want, got)), F.fl_profile_class_name(c)
+        assert all(one[k][f] == full[k][f] for k in one for f in ("launches", "flops", "bytes"))
+    g.close()
+
+
 @pytest.mark.parametrize("seqs", [1, 255, 256, 257, 300])
 @pytest.mark.parametrize("rotary_2d", [False, True])
 def test_bounds_in_arguments_and_staged(seqs, rotary_2d):
