@@ -706,17 +706,27 @@ __global__ void __launch_bounds__(1024) colsum_finish_kernel(FinishSet fs) {
 }
 
 hipError_t colsum_finish_n(const ColsumJob* jobs, int count, hipStream_t st) {
-  if (count <= 0) return hipSuccess;
   if (count > kColsumJobs) return hipErrorInvalidValue;
-  FinishSet fs{};
-  int N = 0;
-  for (int i = 0; i < count; ++i) {
-    fs.job[i] = jobs[i];
-    N = std::max(N, jobs[i].N);
+  for (int i = 0; i < count;) {
+    // Jobs of one launch add concurrently, so a job whose output overlaps one
+    // already taken (a caller may give two parameters one gradient array)
+    // starts the next launch.
+    FinishSet fs{};
+    int n = 0, N = 0;
+    for (; i < count; ++i) {
+      const ColsumJob& j = jobs[i];
+      bool clash = false;
+      for (int k = 0; k < n; ++k) clash = clash || (j.out < fs.job[k].out + fs.job[k].N && fs.job[k].out < j.out + j.N);
+      if (clash) break;
+      fs.job[n++] = j;
+      N = std::max(N, j.N);
+    }
+    if (N <= 0) continue;
+    hipLaunchKernelGGL(colsum_finish_kernel, dim3((N + 63) / 64, n), dim3(1024), 0, st, fs);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  if (N <= 0) return hipSuccess;
-  hipLaunchKernelGGL(colsum_finish_kernel, dim3((N + 63) / 64, count), dim3(1024), 0, st, fs);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t colsum_finish(const float* part, int nblk, int N, float* out, hipStream_t st) {

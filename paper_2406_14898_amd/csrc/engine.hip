@@ -668,7 +668,9 @@ int block_backward(fl_stack* st, const BatchInfo& bi, const Plan& plan, const Wo
     const int n_out = gd.K, n_in = gd.N;
     const ClassWork cd{cls, gemm_flops(T, n_in, n_out), gemm_bytes(T, n_in, n_out, E, epi == EPI_GELU_BWD ? 2 * E : E)};
     const ClassWork cw{FL_PROF_GEMM_TN_ACC, gemm_flops(n_out, n_in, T), gemm_bytes(n_out, n_in, T, E, 8)};
-    if (train_w && gemm_pair_ok(dt, epi, gd, gw)) {
+    // (bias and weight gradients in one array add in launches of their own)
+    const bool apart = overlap(bias, sizeof(float) * n_out, gw.C, sizeof(float) * n_out * n_in);
+    if (train_w && !apart && gemm_pair_ok(dt, epi, gd, gw)) {
       const ClassWork all[3] = {cd, cw, {FL_PROF_COLSUM, 0, (double)T * n_out * E}};
       HIP_OK(timed(st, s, all, bias ? 3 : 2, [&]() { return gemm_pair(dt, epi, gd, gw, bias, s); }));
       return FL_OK;

@@ -155,7 +155,8 @@ hipError_t colsum_finish(const float* partial, int nblk, int N, float* out, hipS
 // multiple of 64): out[n] += sum_t X[t][n].
 constexpr int kColsumDirectRows = 2048;
 hipError_t colsum_direct(DType dt, const void* X, long ldx, int T, int N, float* out, hipStream_t st);
-// Several of them (different out) in one launch.
+// colsum_finish of several partial arrays in one launch; outputs that overlap
+// are added one after the other, in launches of their own.
 struct ColsumJob {
   const float* part;
   float* out;

@@ -374,6 +374,41 @@ def test_launch_timing_runs_the_same_launches(dt):
     g.close()
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("lens", [(30, 170), (600, 900)])
+@pytest.mark.parametrize("what", ["norms", "bias"])
+def test_gradients_that_share_an_array_add_up(dt, lens, what):
+    """Gradients are accumulated, so parameters that are given one gradient
+    array get the sum of their gradients there.  norms: the LayerNorms' gains
+    and shifts, and a shift with the bias gradient summed in the same pass,
+    against separate arrays: fp32 sums of three terms, 1e-6 of their
+    magnitudes.  bias: a bias gradient inside its own weight gradient's array
+    (the layer's products then run apart, so the gradients below it round
+    differently: the element type's tolerance)."""
+    b = synth.make_batch(2, 2, lens, "causal", seed=22)
+    layers, x, dy = _inputs(b, dt, seed=22)
+    g = GpuStack(SHAPE, layers, dt)
+    ref = g.run(b, x, dy)["grads"]
+    H, at = SHAPE.hidden, 512
+    for _ in range(3):
+        shared = g.zero_grads()
+        for d in shared:
+            if what == "norms":
+                d["ln2_g"], d["ln2_b"], d["b_o"] = d["ln1_g"], d["ln1_b"], d["ln1_b"]
+            else:
+                d["b_2"] = d["w_2"].view(-1)[at:at + H]
+        g.run(b, x, dy, grads=shared)
+        for r, d in zip(ref, shared):
+            if what == "norms":
+                for keys, got in ((("ln1_g", "ln2_g"), d["ln1_g"]), (("ln1_b", "ln2_b", "b_o"), d["ln1_b"])):
+                    diff = (got - sum(r[k] for k in keys)).abs()
+                    assert torch.all(diff <= 1e-6 * sum(r[k].abs() for k in keys)), keys
+            else:
+                want = host(r["w_2"].view(-1)[at:at + H] + r["b_2"])
+                assert rel_l2(host(d["b_2"]), want) < TOL[dt]
+    g.close()
+
+
 @pytest.mark.parametrize("seqs", [1, 255, 256, 257, 300])
 @pytest.mark.parametrize("rotary_2d", [False, True])
 def test_bounds_in_arguments_and_staged(seqs, rotary_2d):
