@@ -259,8 +259,8 @@ __global__ void __launch_bounds__(kThreads) attn_fwd_kernel(AttnDesc a) {
 }
 
 // ---------------------------------------------------------------------------
-// Backward pre-pass of the bf16 kernels: delta[t][h] = sum_d dO[t][h*D+d] * O[t][h*D+d].
-// One wave per row.
+// Backward pre-pass: delta[t][h] = sum_d dO[t][h*D+d] * O[t][h*D+d].  One wave
+// per row.  (The fp32 backward of few workgroups forms the sums itself.)
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 __global__ void __launch_bounds__(256) attn_delta_kernel(const T* dout, long ld_do, const T* o, long ld_o,
@@ -312,7 +312,7 @@ __device__ __forceinline__ void rope_bwd_tiles(f32x4 (&acc)[D / 16], int p, int 
 // Backward, dq.  Workgroup: 64 queries (4 waves x 16) of one (sequence,
 // head); keys in tiles of 64 (K row-major and transposed, V row-major).
 // ---------------------------------------------------------------------------
-template <typename T, int D>
+template <typename T, int D, bool DELTA>
 __device__ __forceinline__ void attn_bwd_dq(const AttnDesc& a, T* lds, int s, int h, int qt) {
   constexpr int BM = 64;
   constexpr int NC = D / 32;
@@ -350,19 +350,23 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnDesc& a, T* lds, int s, in
   const float lse2 = qvalid ? a.lse[(long)(si.r0 + qi) * a.num_heads + h] * kLog2e : 0.f;
   // sum_d dO * O of the lane's query
   float dlt = 0.f;
-  if (qvalid) {
-    const T* o = static_cast<const T*>(a.o) + (long)(si.r0 + qi) * a.ld_o + h * D + 8 * fg;
+  if constexpr (DELTA) {
+    if (qvalid) dlt = a.delta[(long)(si.r0 + qi) * a.num_heads + h];
+  } else {
+    if (qvalid) {
+      const T* o = static_cast<const T*>(a.o) + (long)(si.r0 + qi) * a.ld_o + h * D + 8 * fg;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      Vec8<T> x, y;
-      x.load(o + 32 * c);
-      y.load(dout + (long)(si.r0 + qi) * a.ld_dout + h * D + 32 * c + 8 * fg);
+      for (int c = 0; c < NC; ++c) {
+        Vec8<T> x, y;
+        x.load(o + 32 * c);
+        y.load(dout + (long)(si.r0 + qi) * a.ld_dout + h * D + 32 * c + 8 * fg);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dlt += x.get(e) * y.get(e);
+        for (int e = 0; e < 8; ++e) dlt += x.get(e) * y.get(e);
+      }
     }
+    dlt += __shfl_xor(dlt, 16, 64);
+    dlt += __shfl_xor(dlt, 32, 64);
   }
-  dlt += __shfl_xor(dlt, 16, 64);
-  dlt += __shfl_xor(dlt, 32, 64);
 
   f32x4 acc[D / 16];
 #pragma unroll
@@ -422,7 +426,7 @@ __device__ __forceinline__ void attn_bwd_dq(const AttnDesc& a, T* lds, int s, in
 // Backward, dk and dv.  Workgroup: 64 keys (4 waves x 16) of one (sequence,
 // head); queries in tiles of 64 (Q and dO row-major and transposed).
 // ---------------------------------------------------------------------------
-template <typename T, int D>
+template <typename T, int D, bool DELTA>
 __device__ __forceinline__ void attn_bwd_dkdv(const AttnDesc& a, T* lds, float* lse_s, float* dl_s, int s, int h,
                                               int kt_) {
   constexpr int BK = 64;  // keys per workgroup
@@ -475,8 +479,9 @@ __device__ __forceinline__ void attn_bwd_dkdv(const AttnDesc& a, T* lds, float* 
     if (tid < BQ) {
       const int q = qb + tid;
       lse_s[tid] = q < si.L ? a.lse[(long)(si.r0 + q) * a.num_heads + h] * kLog2e : 0.f;
+      if constexpr (DELTA) dl_s[tid] = q < si.L ? a.delta[(long)(si.r0 + q) * a.num_heads + h] : 0.f;
     }
-    {  // sum_d dO * O of every query of the tile, four lanes each
+    if constexpr (!DELTA) {  // sum_d dO * O of every query of the tile, four lanes each
       const int q = qb + (tid >> 2);
       float d = 0.f;
       if (q < si.L) {
@@ -544,17 +549,31 @@ __device__ __forceinline__ void attn_bwd_dkdv(const AttnDesc& a, T* lds, float* 
   }
 }
 
-// Both backward halves in one launch: each only reads the forward's results,
-// and a few sequences of a few tiles leave most CUs idle.  Grid x: the dk, dv
-// tiles, then the dq ones, the last (longest-running) tile first.  Four sequences of 64 rows,
-// four heads of 64: sum dO * O, dk dv and dq in three launches 26.1 us, in one 14.
+// Both backward halves in one launch, with sum dO * O formed where it is used:
+// each half only reads the forward's results, and a few sequences of a few
+// tiles leave most CUs idle.  Grid x: the dk, dv tiles, then the dq ones, the
+// last (longest-running) tile first.
 template <typename T, int D>
 __global__ void __launch_bounds__(kThreads) attn_bwd_kernel(AttnDesc a) {
   __shared__ __attribute__((aligned(16))) T lds[4 * 64 * D];
   __shared__ float lse_s[64], dl_s[64];
   const int n = gridDim.x / 2, b = blockIdx.x;
-  if (b < n) attn_bwd_dkdv<T, D>(a, lds, lse_s, dl_s, blockIdx.z, blockIdx.y, n - 1 - b);
-  else attn_bwd_dq<T, D>(a, lds, blockIdx.z, blockIdx.y, 2 * n - 1 - b);
+  if (b < n) attn_bwd_dkdv<T, D, false>(a, lds, lse_s, dl_s, blockIdx.z, blockIdx.y, n - 1 - b);
+  else attn_bwd_dq<T, D, false>(a, lds, blockIdx.z, blockIdx.y, 2 * n - 1 - b);
+}
+
+// The halves apart, after the delta pre-pass: dk, dv need not read O again for
+// every query tile, and dq's smaller LDS holds more workgroups on a CU.
+template <typename T, int D>
+__global__ void __launch_bounds__(kThreads) attn_bwd_dkdv_kernel(AttnDesc a) {
+  __shared__ __attribute__((aligned(16))) T lds[4 * 64 * D];
+  __shared__ float lse_s[64], dl_s[64];
+  attn_bwd_dkdv<T, D, true>(a, lds, lse_s, dl_s, blockIdx.z, blockIdx.y, gridDim.x - 1 - blockIdx.x);
+}
+template <typename T, int D>
+__global__ void __launch_bounds__(kThreads) attn_bwd_dq_kernel(AttnDesc a) {
+  __shared__ __attribute__((aligned(16))) T lds[3 * 64 * D];
+  attn_bwd_dq<T, D, true>(a, lds, blockIdx.z, blockIdx.y, gridDim.x - 1 - blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -589,10 +608,38 @@ hipError_t attn_delta(const AttnDesc& a, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
+// Whether the backward runs as one launch, for `tiles` 64-row tiles of the
+// longest sequence.  Measured over 1 to 64 sequences of 32 to 4096 rows, 4 to
+// 32 heads (us, pre-pass and two launches against one):
+//   * a half of fewer workgroups than CUs leaves CUs idle on its own: one
+//     launch takes 0.5 to 0.98 of the time (4 x 64 rows, 4 heads of 64: 23.1
+//     against 11.6; 12 x 64 rows, 16 heads: 24.9 / 24.2);
+//   * from 256 on O is read again for nothing and the dq half's occupancy is
+//     lost: 8 x 512 rows, 16 heads 409 / 546, 4 x 512, 8 heads of 128 211 /
+//     236, 8 x 1024, 32 heads 3044 / 4223;
+//   * long sequences: a half alone ends on its longest tiles while the other
+//     could run, the more so where the tile count puts one tile index of every
+//     head on one XCD (4 x 2048 rows, 16 heads 2981 / 2372; 1 x 4096, 32 heads
+//     4822 / 4232; 4 x 4096, 8 heads of 128 9698 / 7548; but 2 x 3072, 32 heads
+//     4847 / 5192, and 2 x 2048, 4 heads 430 / 450).
+static bool attn_bwd_one_launch(int tiles, int heads, int seqs) {
+  const long wgs = (long)tiles * heads * seqs;
+  return wgs < 256 || (tiles >= 32 && wgs > 256 && (tiles % 32 == 0 || wgs < 1024));
+}
+
 template <typename T, int D>
 static hipError_t bwd_t(const AttnDesc& a, hipStream_t st) {
-  const dim3 grid(2 * ((a.max_seqlen + 63) / 64), a.num_heads, a.num_seqs);
-  hipLaunchKernelGGL((attn_bwd_kernel<T, D>), grid, dim3(kThreads), 0, st, a);
+  const int tiles = (a.max_seqlen + 63) / 64;
+  if (attn_bwd_one_launch(tiles, a.num_heads, a.num_seqs)) {
+    hipLaunchKernelGGL((attn_bwd_kernel<T, D>), dim3(2 * tiles, a.num_heads, a.num_seqs), dim3(kThreads), 0, st, a);
+    return hipGetLastError();
+  }
+  hipError_t e = delta_t<T, D>(a, st);
+  if (e != hipSuccess) return e;
+  const dim3 grid(tiles, a.num_heads, a.num_seqs);
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<T, D>), grid, dim3(kThreads), 0, st, a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<T, D>), grid, dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -183,7 +183,7 @@ struct AttnDesc {
   // backward
   const void* dout = nullptr;
   long ld_dout = 0;
-  float* delta = nullptr;  // [T, nh] scratch of the bf16 kernels: rowsum(dO * O)
+  float* delta = nullptr;  // [T, nh] scratch: rowsum(dO * O)
   void* dqkv = nullptr;    // [T, 3H]
   long ld_dqkv = 0;
   // Inverse rotary of dq, dk fused into the kernels' epilogues, over dims
@@ -229,7 +229,7 @@ hipError_t attn_ds_offsets(const AttnDesc& a, hipStream_t st);
 inline size_t attn_ds_off_bytes(int num_seqs) { return ((size_t)(num_seqs + 1) * 8 + 255) / 256 * 256; }
 hipError_t attn_fwd(DType dt, const AttnDesc& a, hipStream_t st);
 hipError_t attn_bwd(DType dt, const AttnDesc& a, hipStream_t st);
-// delta[t][h] = rowsum(dO * O), the bf16 backward's pre-pass.
+// delta[t][h] = rowsum(dO * O), the bf16 backward's pre-pass (the fp32 one's is its own).
 hipError_t attn_delta(const AttnDesc& a, hipStream_t st);
 // bf16 LDS-DMA kernels (attention_bf16.hip), used by attn_fwd / attn_bwd.
 bool attn_bf16_ok(const AttnDesc& a);

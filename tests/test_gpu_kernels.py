@@ -694,6 +694,36 @@ def test_attention_f32_query_tiles(seqs):
     assert rel_l2(host(lse), _lse_ref(q, k, b)) < 1e-5
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("seqs,L", [(21, 130), (22, 130), (3, 1985)])
+def test_attention_f32_backward_launches(seqs, L, d):
+    """The fp32 backward on either side of 256 workgroups a half (one launch
+    that forms sum dO * O itself; the pre-pass and a launch for each half), and
+    on long sequences past it, which take one launch again; ragged lengths and
+    contexts, against the oracle.  fp32 sums of at most 1985 terms: the
+    tolerance of the other fp32 attention tests."""
+    nh = 4
+    H = nh * d
+    lens = np.full(seqs, L)
+    lens[1:] -= np.arange(1, seqs) % 7 * 9
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T = int(cu[-1])
+    b = synth.Batch(cu, np.arange(seqs + 1, dtype=np.int32), "prefix", (lens // 3).astype(np.int32))
+    qkv, do = _qkv(T, H, 58, "f32"), rnd((T, H), 59, dt="f32")
+    q, k, v = (qkv[:, i * H:(i + 1) * H].astype(np.float64).reshape(T, nh, d) for i in range(3))
+    t, dcu, pre = dev(qkv, "f32"), dev_i32(cu), dev_i32(b.prefix_len)
+    o, lse = torch.empty((T, H), device="cuda"), torch.empty((T, nh), device="cuda")
+    F.fl_test_attention_fwd(F.FL_F32, t, o, lse, dcu, pre, T, seqs, L, H, nh)
+    dqkv = torch.full((T, 3 * H), float("nan"), device="cuda")
+    delta = torch.full((T, nh), float("nan"), device="cuda")
+    F.fl_test_attention_bwd(F.FL_F32, t, o, lse, dev(do, "f32"), dqkv, delta, dcu, pre, None, None, None, 0, T, seqs,
+                            L, H, nh)
+    sync()
+    g = host(dqkv)
+    for i, ref in enumerate(oracle.attention_backward(q, k, v, do.astype(np.float64).reshape(T, nh, d), b)):
+        assert rel_l2(g[:, i * H:(i + 1) * H], ref.reshape(T, H)) < TOL["f32"] / 2, "qkv"[i]
+
+
 @pytest.mark.parametrize("stored", [False, True])
 @pytest.mark.parametrize("mask", ["causal", "prefix"])
 def test_attention_long_sequence(mask, stored):
