@@ -51,8 +51,10 @@ int fl_test_gemm(int dtype, int layout, int epi, const void* A, const void* B, v
                  float res_scale, float* colsum, void* stream);
 /* The same with the bf16 LDS-DMA kernel's tile height (64, 128, 192 or 256; not 192 for TN) and
  * number of reduction slices given instead of chosen from the shape (tile 0:
- * chosen).  Slices above 1 are for NT and NN and need part of at least
- * slices * M * N floats (FL_ERR_WORKSPACE). */
+ * chosen).  Slices above 1 are for NT, NN and TN on 256-row tiles; for TN they
+ * are those of the tiles past whole rounds of 256 only.  They need part of at
+ * least slices * M * N floats, for TN slices * 65536 for each such tile
+ * (FL_ERR_WORKSPACE). */
 int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void* B, void* C, int M, int N, int K,
                        int64_t lda, int64_t ldb, int64_t ldc, const void* bias, const void* R, int64_t ldr, void* C2,
                        int64_t ldc2, const void* Z, int64_t ldz, float* part, int64_t part_bytes, int b_rows,

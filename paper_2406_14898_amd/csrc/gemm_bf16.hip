@@ -36,6 +36,7 @@
 //     releases the slot, so the next stage's loads and fragment reads overlap
 //     matrix-core work.
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "kernels.h"
@@ -91,10 +92,13 @@ struct G2Args {
   const bf16* Z;
   long ldz;
   // Split reduction: every tile's reduction is cut into `slices` slices whose
-  // fp32 sums go to `part` ([slices][M][N], EPI_PART); gemm_slices_kernel adds
-  // them in slice order and runs the epilogue.
+  // fp32 sums go to `part` (EPI_PART; token-major products [slices][M][N],
+  // weight gradients [slices][tiles][BM][BN]); gemm_slices_kernel or
+  // gemm_tile_slices_kernel adds them in slice order and runs the epilogue.
   float* part;
   int slices;
+  // The tiles [tile0, tile0 + tiles) of the work order are this launch's.
+  int tile0, tiles;
   int nb;  // rows of B that exist (see GemmDesc::b_rows)
   float res_scale;
   // EPI_GELU_BWD: per 256-row tile, the column sums of the stored C (fp32
@@ -200,21 +204,20 @@ __device__ __forceinline__ float gelu2_grad(float z) {
 }
 
 // Work order: workgroup wg runs on XCD wg % 8, and each XCD takes a contiguous
-// range of work items.  Items walk bands of kBand tile rows column by column
-// (kAlongN: bands of tile columns row by row), one reduction slice of the
-// whole product after another, so that an XCD reads few slices of A
-// (K = 16384 in four to eight slices: 1-3 % faster than a tile's slices side
-// by side).
-template <int kBand, bool kAlongN>
-__device__ __forceinline__ void work_coords(int wg, int nwg, int tiles_m, int tiles_n, int slices, int& tm, int& tn,
-                                            int& slice) {
+// range of work items, one reduction slice of the launch's tiles after
+// another, so that an XCD reads few slices of A (K = 16384 in four to eight
+// slices: 1-3 % faster than a tile's slices side by side).
+__device__ __forceinline__ int work_id(int wg, int nwg) {
   constexpr int kXcd = 8;
   const int q = nwg / kXcd, r = nwg % kXcd;
   const int x = wg % kXcd, j = wg / kXcd;
-  const int id = (x < r) ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
+  return (x < r) ? x * (q + 1) + j : r * (q + 1) + (x - r) * q + j;
+}
+// Tiles walk bands of kBand tile rows column by column (kAlongN: bands of tile
+// columns row by row).
+template <int kBand, bool kAlongN>
+__device__ __forceinline__ void tile_coords(int tile, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int ta = kAlongN ? tiles_n : tiles_m, tb = kAlongN ? tiles_m : tiles_n;
-  slice = id / (ta * tb);
-  const int tile = id - slice * (ta * tb);
   const int per_band = kBand * tb;
   const int band = tile / per_band;
   const int first = band * kBand;
@@ -383,15 +386,18 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
 
 // Row steps of the epilogue whose global reads are issued together: 8 for the
 // residual epilogues (a 128-row half's whole share: 6 % faster on the 41447 x
-// 4096 x 4096 output projection than 4), 4 elsewhere (8 measured no faster),
-// 8 for the fp32 accumulator, whose reads are what a short weight gradient
-// waits for (4096 x 16384 over 509 tokens on 128 x 128 tiles: 154 us with 2,
-// 148 with 4, 136 with 8; long ones unchanged).  Reading it before the
-// reduction instead was slower (88 -> 103 us, 12288 x 4096 over 509 tokens):
-// the first operand stages then queue behind it.
-template <int EPI>
+// 4096 x 4096 output projection than 4), 4 elsewhere (8 measured no faster).
+// The fp32 accumulator: 8 on small tiles, whose short weight gradients wait for
+// these reads (4096 x 16384 over 509 tokens on 128 x 128 tiles: 154 us with 2,
+// 148 with 4, 136 with 8), 4 on 256-row tiles, the best of both ends (with 2, 4
+// and 8: 130528 x 4096 over 733 tokens 1354, 1334, 1323 us; 4096 x 4096 over
+// 900 57.0, 56.8, 59.4; 16384 x 4096 over 1295 259, 265, 278).  Reading it before the reduction instead was slower
+// (88 -> 103 us, 12288 x 4096 over 509 tokens): the first operand stages then
+// queue behind it.
+template <int EPI, class TL>
 constexpr int epi_steps() {
-  return EPI == EPI_BIAS_RES || EPI == EPI_RES || EPI == EPI_ACC_F32 ? 8 : 4;
+  if (EPI == EPI_ACC_F32) return TL::kBig ? 4 : 8;
+  return EPI == EPI_BIAS_RES || EPI == EPI_RES ? 8 : 4;
 }
 
 // One work item (output tile, reduction slice) of a product; smem holds at
@@ -402,7 +408,7 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
   constexpr int kWTM = TL::kWTM, kWTN = TL::kWTN, kSlot = TL::kSlot, kStages = TL::kStages;
   const int tiles_m = (p.M + kBM - 1) / kBM, tiles_n = p.N / kBN;
   const int nk = (p.K + kBK - 1) / kBK;
-  int tm, tn, slice;
+  int tm, tn;
   // Bands of 4 tile rows for the forward and dgrad products on 256 x 256
   // tiles (the 32 tiles one XCD holds span 4 row panels of A and 8 column
   // panels of B): 1.5-3 % faster than 8 (16: 5-18 % slower than 8).  Their
@@ -411,7 +417,8 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
   // read and written as 4 KB runs (4096 x 16384 x 256 tokens: 116 us against
   // 159 in bands of tile rows).
   constexpr bool kWgrad = !AK && !BKc;
-  work_coords<TL::kBig && !kWgrad ? 4 : 8, kWgrad && !TL::kBig>(wi, nwork, tiles_m, tiles_n, p.slices, tm, tn, slice);
+  const int id = work_id(wi, nwork), slice = id / p.tiles, tile = id - slice * p.tiles;
+  tile_coords<TL::kBig && !kWgrad ? 4 : 8, kWgrad && !TL::kBig>(p.tile0 + tile, tiles_m, tiles_n, tm, tn);
   const int kt0 = p.slices == 1 ? 0 : (int)((long)nk * slice / p.slices);
   const int kt1 = p.slices == 1 ? nk : (int)((long)nk * (slice + 1) / p.slices);
   // Per-lane values are rederived in every tile (the opaque copy keeps the
@@ -602,18 +609,23 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
   barrier();  // every wave is done with the operand tiles
   if constexpr (EPI == EPI_PART) {
     G2Args q = p;
-    q.C = p.part + (long)slice * p.M * p.N;
-    q.ldc = p.N;
-    tile_epilogue<TL, EPI, epi_steps<EPI>()>(q, acc, reinterpret_cast<float*>(&smem[0]), tm, m0, n0, tid);
+    if constexpr (kWgrad) {  // the slice's own dense tile, addressed from the product's first element
+      q.C = p.part + ((long)slice * p.tiles + tile) * (kBM * kBN) - ((long)m0 * kBN + n0);
+      q.ldc = kBN;
+    } else {
+      q.C = p.part + (long)slice * p.M * p.N;
+      q.ldc = p.N;
+    }
+    tile_epilogue<TL, EPI, epi_steps<EPI, TL>()>(q, acc, reinterpret_cast<float*>(&smem[0]), tm, m0, n0, tid);
   } else {
-    tile_epilogue<TL, EPI, epi_steps<EPI>()>(p, acc, reinterpret_cast<float*>(&smem[0]), tm, m0, n0, tid);
+    tile_epilogue<TL, EPI, epi_steps<EPI, TL>()>(p, acc, reinterpret_cast<float*>(&smem[0]), tm, m0, n0, tid);
   }
 }
 
 template <bool AK, bool BKc, int EPI, class TL>
 __global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16_kernel(G2Args p) {
   __shared__ __attribute__((aligned(1024))) bf16 smem[TL::kStages * TL::kSlot];  // [slot][A | B]
-  const int nwork = ((p.M + TL::kBM - 1) / TL::kBM) * (p.N / TL::kBN) * p.slices;
+  const int nwork = p.tiles * p.slices;
   // Persistent where the grid is smaller than the work (256 x 256 tiles: one
   // workgroup per CU); a tile's epilogue stores drain while the next item's
   // first stages load.
@@ -650,6 +662,47 @@ __global__ void __launch_bounds__(256, TD::kOcc < TW::kOcc ? TD::kOcc : TW::kOcc
   }
 }
 
+// v = the sum over `slices` slices, `stride` floats apart, of eight values, in
+// slice order.
+__device__ __forceinline__ void sum_slices(const float* src, long stride, int slices, float (&v)[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = 0.f;
+  for (int s0 = 0; s0 < slices; s0 += 4) {
+    Vec8<float> x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < slices) x[u].load(src + (s0 + u) * stride);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < slices) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += x[u].get(e);
+      }
+  }
+}
+
+// C += the reduction slices of a weight gradient's tiles (fp32
+// [slices][tiles][256][256], in slice order); eight columns per lane, 32
+// workgroups per tile.
+__global__ void __launch_bounds__(256) gemm_tile_slices_kernel(G2Args p) {
+  constexpr int kBM = Tile256::kBM, kBN = Tile256::kBN, kPer = kBM * kBN / (8 * 256);
+  const int tile = blockIdx.x / kPer;
+  const int at = ((blockIdx.x % kPer) * 256 + threadIdx.x) * 8, r = at / kBN, c = at % kBN;
+  int tm, tn;
+  tile_coords<8, false>(p.tile0 + tile, (p.M + kBM - 1) / kBM, p.N / kBN, tm, tn);
+  const long m = (long)tm * kBM + r;
+  if (m >= p.M) return;
+  float* out = static_cast<float*>(p.C) + m * p.ldc + tn * kBN + c;
+  Vec8<float> o;
+  o.load(out);
+  float v[8];
+  sum_slices(p.part + (long)tile * (kBM * kBN) + at, (long)p.tiles * (kBM * kBN), p.slices, v);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] += o.get(e);
+  o.set(v);
+  o.store(out);
+}
+
 // Sums the reduction slices of a whole product (fp32 [slices][M][N], in slice
 // order) and applies the epilogue; eight columns per lane.
 template <int EPI>
@@ -659,37 +712,13 @@ __global__ void __launch_bounds__(256) gemm_slices_kernel(G2Args p) {
   const long m = idx / ng;
   if (m >= p.M) return;
   const int n = (int)(idx % ng) * 8;
-  const long plane = (long)p.M * p.N;
-  const float* src = p.part + m * p.N + n;
-  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < p.slices; s0 += 4) {
-    Vec8<float> x[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (s0 + u < p.slices) x[u].load(src + (s0 + u) * plane);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (s0 + u < p.slices) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] += x[u].get(e);
-      }
-  }
+  float v[8];
+  sum_slices(p.part + m * p.N + n, (long)p.M * p.N, p.slices, v);
   if constexpr (EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU) {
     Vec8<bf16> b;
     b.load(p.bias + n);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] += b.get(e);
-  }
-  if constexpr (EPI == EPI_ACC_F32) {
-    float* c = static_cast<float*>(p.C) + m * p.ldc + n;
-    Vec8<float> o;
-    o.load(c);
-    float t[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) t[e] = o.get(e) + v[e];
-    o.set(t);
-    o.store(c);
-    return;
   }
   if constexpr (EPI == EPI_BIAS_RES || EPI == EPI_RES) {
     Vec8<bf16> r;
@@ -773,6 +802,8 @@ double part_us(const GemmDesc& d, int M, int tile, int s) {
   return part_us(M, d.N, d.K, tile, s) + (pass ? 4.0 + 2.0 * M * (double)d.N / 4.5e6 : 0.0);
 }
 
+// fp32 sums of one slice of a 256 x 256 tile
+constexpr size_t kTileBytes = (size_t)Tile256::kBM * Tile256::kBN * 4;
 constexpr int kTiles[] = {64, 128, 192, 256};
 constexpr int kSlices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
 
@@ -827,9 +858,16 @@ int plan_rows(const GemmDesc& d, GemmPart (&parts)[2]) {
   return n;
 }
 
+template <class TL>
+int tile_count(const G2Args& a) {
+  return ((a.M + TL::kBM - 1) / TL::kBM) * (a.N / TL::kBN);
+}
+
+// All tiles of the product, or those that the arguments name.
 template <bool AK, bool BKc, int EPI, class TL>
-hipError_t launch_tile(const G2Args& a, hipStream_t st) {
-  const int items = ((a.M + TL::kBM - 1) / TL::kBM) * (a.N / TL::kBN) * a.slices;
+hipError_t launch_tile(G2Args a, hipStream_t st) {
+  if (a.tiles == 0) a.tiles = tile_count<TL>(a);
+  const int items = a.tiles * a.slices;
   const int cus = num_cus();
   const int grid = TL::kBig && items > cus ? cus : items;
   hipLaunchKernelGGL((gemm_bf16_kernel<AK, BKc, EPI, TL>), dim3(grid), dim3(TL::kThr), 0, st, a);
@@ -856,7 +894,7 @@ G2Args make_args(const GemmDesc& d, bool bk) {
   a.M = d.M; a.N = d.N; a.K = d.K; a.lda = d.lda; a.ldb = d.ldb; a.ldc = d.ldc;
   a.bias = (const bf16*)d.bias; a.R = (const bf16*)d.R; a.ldr = d.ldr;
   a.C2 = (bf16*)d.C2; a.ldc2 = d.ldc2; a.Z = (const bf16*)d.Z; a.ldz = d.ldz;
-  a.part = d.part; a.slices = 1;
+  a.part = d.part; a.slices = 1; a.tile0 = 0; a.tiles = 0;
   a.nb = gemm_b_rows(bk, d);
   a.res_scale = d.res_scale;
   a.colsum = nullptr;
@@ -903,24 +941,89 @@ hipError_t launch_tokens(const GemmDesc& d, hipStream_t st) {
   return hipSuccess;
 }
 
-// Weight gradients (reduction over the tokens).  Short reductions are bound by
-// the fp32 read-modify-write of C.
+// Estimated time (us) of a weight gradient on 64-, 128- or 256-row tiles, the
+// 256-row tiles past whole rounds of 256 in s reduction slices: fitted to a
+// sweep on MI355X with operands from memory (hidden 256 to 4096, FFN up to 16384
+// wide, vocabularies of 32000 to 130528, 37 to 41447 tokens, every tile and
+// slice count).  Choosing by it comes within 0.3 % (geometric mean; 10 % at
+// worst) of the fastest choice.  Short reductions are bound by the fp32
+// read-modify-write of C, which the small tiles' two or three workgroups per CU
+// overlap with reductions (16384 x 4096 over 509 tokens: 64-row tiles 154 us, 128
+// 155, 256 194; over 1295 277, 250, 257); long ones by the matrix cores, best fed
+// by 256-row tiles (over 8192: 1964, 1069, 880), where few tiles are cut into
+// slices instead of leaving CUs idle (1024 x 1024 over 41447 tokens: 64-row tiles
+// 301, 256-row ones in 16 slices 94; 3072 x 12288, 64 tiles past two rounds,
+// whole 2838, in 4 slices 2280).
+double wgrad_us(int M, int N, int K, int tile, int s) {
+  const double n = (K + kBK - 1) / kBK;
+  const long items = (long)((M + tile - 1) / tile) * (N / (tile == 256 ? 256 : 128));
+  if (tile == 64) {
+    if (items <= 256) return 7.5 + 0.41 * n;  // one workgroup on a CU
+    if (items <= 512) return 8.1 + 0.73 * n;  // two
+    return 6.9 + std::max(1.0, items / 768.0) * (7.0 + 0.95 * n * (1.0 + 0.002 * n));
+  }
+  if (tile == 128) {
+    const long full = items / 512, rem = items % 512;
+    const double two = 12.5 + 0.87 * n, one = 6.2 + 0.8 * n;  // workgroups on a CU
+    const double tail = rem == 0 ? 0.0 : rem <= 256 ? one : two;
+    return 5.5 + std::max(items > 256 ? two : tail, full * two + 0.9 * tail + 0.1 * rem / 512.0 * two);
+  }
+  const long full = items / 256, rem = items % 256;
+  const double t = 4.1 + 6.0 * std::min(full, 4L) + full * (26.0 + 1.38 * n);
+  if (rem == 0) return t;
+  if (s == 1) return t + 10.6 + 20.0 * rem / 256.0 + 1.38 * n;
+  return t + 14.6 + 12.0 * rem * s / 256.0 + 1.38 * std::ceil(n / s) + rem * (0.022 * s + 0.1);
+}
+
+struct WgradPlan {
+  int tile, slices;
+};
+WgradPlan plan_wgrad(const GemmDesc& d) {
+  if (d.tile) return WgradPlan{d.tile, d.slices};
+  WgradPlan best{256, 1};
+  double t = wgrad_us(d.M, d.N, d.K, 256, 1);
+  const int rem = (int)((long)((d.M + 255) / 256) * (d.N / 256) % 256), nk = (d.K + kBK - 1) / kBK;
+  const size_t bytes = d.part ? d.part_bytes : 0;
+  for (int s : kSlices) {
+    // one round of slices of at least two stages each, as far as the scratch allows
+    if (s == 1 || rem == 0) continue;
+    if (rem * s > 256 || 2 * s > nk || (size_t)rem * s * kTileBytes > bytes) break;
+    const double u = wgrad_us(d.M, d.N, d.K, 256, s);
+    if (u < t) {
+      t = u;
+      best = WgradPlan{256, s};
+    }
+  }
+  for (int tile : {64, 128}) {
+    // (2 % for what the estimate does not see)
+    const double u = 1.02 * wgrad_us(d.M, d.N, d.K, tile, 1);
+    if (u < t) {
+      t = u;
+      best = WgradPlan{tile, 1};
+    }
+  }
+  return best;
+}
+
+// Weight gradients (reduction over the tokens).
 hipError_t launch_wgrad(const GemmDesc& d, hipStream_t st) {
   if (d.M <= 0 || d.N <= 0) return hipSuccess;
   const G2Args a = make_args(d, false);
-  const long tiles256 = (long)((d.M + 255) / 256) * (d.N / 256), tiles64 = (long)((d.M + 63) / 64) * (d.N / 128);
-  int tile = d.tile;
-  // (16384 x 4096: 64-row tiles 90 us against 89 on 128-row ones at 37 tokens;
-  // 128-row 148 against 157 on 256-row ones at 509, 211 against 215 at 1024;
-  // a whole step of one 509-token client 1240 us with 64-row tiles up to 640
-  // tokens, 1223 with this rule, and the vocabulary gradient of 733 tokens is
-  // 70 us faster on 256-row tiles.  Too few 256-row tiles to fill the chip,
-  // 3840 x 1280: 64-row 23 us against 36 at 1024, 128-row 48 against 71 at 3072)
-  const bool few = tiles256 < 256;
-  if (!tile) tile = tiles64 <= 512 || d.K <= (few ? 1536 : 300) ? 64 : few || d.K <= 600 ? 128 : 256;
-  if (tile == 256) return launch_tile<false, false, EPI_ACC_F32, Tile256>(a, st);
-  if (tile == 128) return launch_tile<false, false, EPI_ACC_F32, Tile128w>(a, st);
-  if (tiles64 <= 512) return launch_tile<false, false, EPI_ACC_F32, Tile64>(a, st);
+  const WgradPlan pl = plan_wgrad(d);
+  if (pl.tile == 256) {
+    const int tiles = tile_count<Tile256>(a), rem = tiles % 256;
+    if (pl.slices == 1 || rem == 0) return launch_tile<false, false, EPI_ACC_F32, Tile256>(a, st);
+    G2Args b = a;
+    b.tiles = tiles - rem;
+    hipError_t e = b.tiles ? launch_tile<false, false, EPI_ACC_F32, Tile256>(b, st) : hipSuccess;
+    if (e != hipSuccess) return e;
+    b.tile0 = b.tiles; b.tiles = rem; b.slices = pl.slices;
+    if ((e = launch_tile<false, false, EPI_PART, Tile256>(b, st)) != hipSuccess) return e;
+    hipLaunchKernelGGL(gemm_tile_slices_kernel, dim3(32 * rem), dim3(256), 0, st, b);
+    return hipGetLastError();
+  }
+  if (pl.tile == 128) return launch_tile<false, false, EPI_ACC_F32, Tile128w>(a, st);
+  if (tile_count<Tile64>(a) <= 512) return launch_tile<false, false, EPI_ACC_F32, Tile64>(a, st);
   return launch_tile<false, false, EPI_ACC_F32, Tile64w>(a, st);
 }
 
@@ -933,8 +1036,10 @@ template <int EPI, class TD, class TW>
 hipError_t launch_pair_tiles(const G2Args& d, const G2Args& w, float* bias, hipStream_t st) {
   PairArgs a;
   a.d = d; a.w = w; a.bias = bias;
-  a.nd = ((d.M + TD::kBM - 1) / TD::kBM) * (d.N / TD::kBN) * d.slices;
-  a.nw = ((w.M + TW::kBM - 1) / TW::kBM) * (w.N / TW::kBN);
+  a.d.tiles = tile_count<TD>(d);
+  a.w.tiles = tile_count<TW>(w);
+  a.nd = a.d.tiles * d.slices;
+  a.nw = a.w.tiles;
   a.chunk = std::min(num_cus(), (a.nd + 7) / 8 * 8);
   const int nseg = (a.nd + a.chunk - 1) / a.chunk;
   a.share = ((a.nw + nseg - 1) / nseg + 7) / 8 * 8;

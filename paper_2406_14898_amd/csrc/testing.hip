@@ -83,9 +83,10 @@ int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void
       return set_error(FL_ERR_ARG, "tile must be 0, 64, 128, 192 (NT and NN) or 256");
     if (dtype != FL_BF16 || !gemm_bf16_dma_ok((GemmLayout)layout, d))
       return set_error(FL_ERR_ARG, "a forced tile needs a product the LDS-DMA kernel takes");
-    if (slices < 1 || (layout == FL_GEMM_TN && slices != 1) || slices > (K + 63) / 64)
-      return set_error(FL_ERR_ARG, "slices outside [1, reduction stages]");
-    if (slices > 1 && d.part_bytes / 4 / slices < (size_t)M * N)
+    if (slices < 1 || (layout == FL_GEMM_TN && slices != 1 && tile != 256) || slices > (K + 63) / 64)
+      return set_error(FL_ERR_ARG, "slices outside [1, reduction stages], or of a TN tile other than 256");
+    const size_t sliced = layout == FL_GEMM_TN ? (size_t)((M + 255) / 256) * (N / 256) % 256 * 65536 : (size_t)M * N;
+    if (slices > 1 && d.part_bytes / 4 / slices < sliced)
       return set_error(FL_ERR_WORKSPACE, "part too small for the slices");
     d.tile = tile;
     d.slices = slices;

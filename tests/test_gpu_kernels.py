@@ -107,8 +107,8 @@ def test_gemm_tiles_and_slices(lay, epi, tile, slices):
     stages than a tile's ring of slots and of many.  Stored bf16 rounds to
     2^-9 of a value and the fp32 sums of K <= 1024 terms stay far below that:
     5e-3 relative L2 (TOL / 4)."""
-    if lay == F.FL_GEMM_TN and (slices > 1 or tile == 192):
-        pytest.skip("weight gradients are not sliced and have no 192-row tile")
+    if lay == F.FL_GEMM_TN and (slices > 1 and tile != 256 or tile == 192):
+        pytest.skip("weight gradients are sliced on 256-row tiles only and have no 192-row tile")
     part = torch.full((16 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
     for M, N, K in ((1, 256, 64), (tile - 1, 256, 192), (tile, 512, 448), (tile + 1, 256, 1024), (300, 768, 512)):
         if lay == F.FL_GEMM_TN:
@@ -302,6 +302,28 @@ def test_gemm_tn_accumulates(dt):
     F.fl_test_gemm(code, F.FL_GEMM_TN, F.FL_EPI_ACC_F32, dev(A, dt), dev(B, dt), C, M, N, K, M, N, N)
     sync()
     assert rel_l2(host(C), ref) < (1e-5 if dt == "f32" else 5e-3)
+
+
+@pytest.mark.parametrize("M,N,K,slices", [(304, 512, 700, 3), (256, 256, 317, 5), (8, 768, 1024, 16),
+                                          (4360, 4096, 200, 2), (4360, 4096, 190, 3)])
+def test_gemm_tn_tail_slices(M, N, K, slices):
+    """bf16 weight gradient on 256 x 256 tiles with the tiles past whole rounds
+    of 256 in reduction slices: none but those (1 to 6 tiles), and 32 of 288;
+    ragged rows and reductions, slices of one stage.  Every element of C is
+    added to once: fp32 sums of K <= 1024 terms and of the slices, 1e-6."""
+    A, B = rnd((K, M), 90 + K), rnd((K, N), 91 + K)
+    C0 = rnd((M, N), 92, dt="f32")
+    ref = C0.astype(np.float64) + A.astype(np.float64).T @ B.astype(np.float64)
+    part = torch.full((64 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
+    C = torch.from_numpy(C0).cuda()
+    F.fl_test_gemm(F.FL_BF16, F.FL_GEMM_TN, F.FL_EPI_ACC_F32, dev(A, "bf16"), dev(B, "bf16"), C, M, N, K, M, N, N,
+                   part=part, tile=256, slices=slices)
+    sync()
+    assert rel_l2(host(C), ref) < 1e-6
+    with pytest.raises(F.FlglmError) as e:
+        F.fl_test_gemm(F.FL_BF16, F.FL_GEMM_TN, F.FL_EPI_ACC_F32, dev(A, "bf16"), dev(B, "bf16"), C, M, N, K, M, N, N,
+                       part=part[:slices * 65536 - 4], tile=256, slices=slices)
+    assert e.value.code == F.FL_ERR_WORKSPACE
 
 
 @pytest.mark.parametrize("K", [1, 63, 64, 65, 128, 129, 192])
