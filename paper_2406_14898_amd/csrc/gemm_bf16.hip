@@ -769,11 +769,13 @@ struct GemmPart {
 // 16 .. 6000, N and K of hidden 1280 and 4096, every tile and slice count): a
 // 64-wide stage takes 0.45 us with one 64-row workgroup on a CU and 0.64 with
 // two, 0.79 for a 128-row one and 1.31 for a 256-row one; slices cost the
-// round trip of their fp32 sums and a launch.  Choosing by it comes within 1 %
-// (geometric mean) of the fastest choice of each product.  192-row tiles are
-// taken as 0.79 of a 256-row one, as measured on long products, where the
-// clock falls as more CUs are busy (1295 x 130560 x 4096: 1244 us against
-// 1375); short ones reach 0.77.
+// round trip of their fp32 sums and a launch.  192-row tiles are taken as 0.79
+// of a 256-row one, as measured on long products, where the clock falls as more
+// CUs are busy (1295 x 130560 x 4096: 1244 us against 1375); short ones reach
+// 0.77.  The sweep's operands were in cache and its epilogue a plain store: the
+// estimate sees neither the operands' way from memory, which the smaller tiles
+// read more often, nor the epilogues' further reads and writes, nor the clock.
+// plan_rows allows for that where it matters.
 double part_us(int M, int N, int K, int tile, int s) {
   const double n = (double)(K / kBK) / s;
   const long items = (long)((M + tile - 1) / tile) * (N / (tile == 64 ? 128 : 256)) * s;
@@ -781,7 +783,8 @@ double part_us(int M, int N, int K, int tile, int s) {
   double t;
   if (tile == 64) {
     const long full = items / 512, rem = items % 512;
-    t = 2.0 + 0.97 * (full + (rem > 0)) + n * (0.64 * full + (rem > 256 ? 0.64 : rem > 0 ? 0.449 : 0.0));
+    // (full rounds stay behind each other's stores)
+    t = 2.0 + 1.5 * full + 0.97 * (rem > 0) + n * (0.64 * full + (rem > 256 ? 0.64 : rem > 0 ? 0.449 : 0.0));
   } else if (tile == 128) {
     t = 2.4 + rounds * (4.5 + 0.791 * n);
   } else {
@@ -815,7 +818,7 @@ bool slices_fit(const GemmDesc& d, int M, int tile, int s) {
   return s == 1 || (tile != 192 && (size_t)s * M * d.N * 4 <= bytes && 2 * s <= d.K / kBK);
 }
 
-// Best single launch for M rows on tiles of at most `most` rows.
+// Best single launch for M rows on tiles of at most `most` rows by the estimate.
 double best_part(const GemmDesc& d, int M, int most, GemmPart* out) {
   double best = 1e30;
   for (int tile : kTiles)
@@ -832,11 +835,33 @@ double best_part(const GemmDesc& d, int M, int most, GemmPart* out) {
 
 // NT / NN: one launch over all rows, or two: as many whole rounds of large
 // tiles as fill every CU, and the remaining rows on the shape that suits them.
-int plan_rows(const GemmDesc& d, GemmPart (&parts)[2]) {
-  double best = best_part(d, d.M, 256, &parts[0]);
-  int n = 1;
-  if (d.M <= 256) return n;
+// Other tiles than 256-row ones read the operands more often, which the
+// estimate does not see: where 256-row tiles fill most of the chip, their
+// estimate has to be a tenth lower, in forward products of up to eight stages,
+// which are bound by their stores, a quarter (us, the smaller tiles that the
+// plain estimate takes against 256-row ones, operands from memory: 6000 x 11520
+// x 3840 485 / 444, 12000 x 10240 x 3840 847 / 790, 41447 x 768 x 256 41.7 /
+// 35.4, 8192 x 2048 x 512 36.4 / 31.0; whole rounds of 256-row tiles and the
+// rest apart against one launch of 192-row tiles: 18000 x 4096 x 16384 1846 /
+// 2103, 4409 x 16384 x 4096 509 / 549).  Not for few rows against the columns,
+// where A, the operand read again, stays in cache (600 x 130560 x 4096: 128-row
+// tiles 629, 256 and 344 rows apart 667).
+int plan_rows(const GemmDesc& d, bool forward, GemmPart (&parts)[2]) {
   const int nt = d.N / 256;
+  const bool large = (long)((d.M + 255) / 256) * nt >= 160 && 32L * d.M >= d.N;
+  const double small = !large ? 1.0 : forward && d.K <= 8 * kBK ? 1.0 / 0.75 : 1.0 / 0.9;
+  double best = 1e30;
+  int n = 1;
+  for (int tile : kTiles)
+    for (int s : kSlices) {
+      if (!slices_fit(d, d.M, tile, s)) break;
+      const double t = part_us(d, d.M, tile, s) * (tile == 256 && s == 1 ? 1.0 : small);
+      if (t < best) {
+        best = t;
+        parts[0] = GemmPart{d.M, tile, s};
+      }
+    }
+  if (d.M <= 256) return n;
   for (int tile : kTiles)
     for (int s = 1; tile > 64 && s <= 4; ++s) {
       const long rows_t = d.M / tile;  // whole tile rows
@@ -845,10 +870,11 @@ int plan_rows(const GemmDesc& d, GemmPart (&parts)[2]) {
       if (d.colsum) m1 = m1 / kColsumRows * kColsumRows;  // the second launch starts a block of column sums
       if (m1 <= 0 || m1 >= d.M || !slices_fit(d, m1, tile, s)) continue;
       GemmPart rest;
-      const double t = part_us(d, m1, tile, s) + best_part(d, d.M - m1, 128, &rest);
       // (5 % for what the estimate does not see; also keeps the choice of rows
       // that are close to whole rounds anyway)
-      if (t < 0.95 * best) {
+      const double t = (part_us(d, m1, tile, s) + best_part(d, d.M - m1, 128, &rest)) / 0.95 *
+                       (tile == 256 && s == 1 ? 1.0 : small);
+      if (t < best) {
         best = t;
         parts[0] = GemmPart{m1, tile, s};
         parts[1] = rest;
@@ -908,7 +934,7 @@ hipError_t launch_tokens(const GemmDesc& d, hipStream_t st) {
   GemmPart parts[2];
   int n = 1;
   if (d.tile) parts[0] = GemmPart{d.M, d.tile, d.slices};
-  else n = plan_rows(d, parts);
+  else n = plan_rows(d, BKc, parts);
   long m0 = 0;
   for (int i = 0; i < n; ++i) {
     G2Args a = make_args(d, BKc);
@@ -1132,7 +1158,7 @@ bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d) 
 
 bool gemm_epilogue_colsum(const GemmDesc& d) {
   GemmPart parts[2];
-  return plan_rows(d, parts) == 1 && parts[0].tile == 256 && parts[0].slices == 1;
+  return plan_rows(d, false, parts) == 1 && parts[0].tile == 256 && parts[0].slices == 1;
 }
 
 hipError_t gemm_bf16_dma(GemmLayout layout, int epi, const GemmDesc& d, hipStream_t st) {
