@@ -436,13 +436,15 @@ __global__ void __launch_bounds__(512) gemm_f32_pair_kernel(SmallPairArgs p) {
 // ---------------------------------------------------------------------------
 
 // 16-row tiles along each side of the small kernel's tile for an fp32 product,
-// or 0: enough 128 x 128 tiles to fill the chip.  Measured (us): 128 tiles
-// (2048 x 1024 x 256) 25 on 32 x 32 against 35 on 128 x 128, 248 tiles (3900 x
-// 1024 x 256) 35 against 37; 64 tiles of 32 x 32 (256 x 256 x 1024) 11 against
-// 6.9 on 16 x 16, 192 of them (256 x 768 x 256) 5.4 against 5.9.
+// or 0: enough 128 x 128 tiles to fill the chip.  Measured (us, all three layouts,
+// N 512 to 2048, K 256 to 3840; 32 x 32 against 128 x 128): 144 tiles of 128 x
+// 128 0.81 to 0.97 of the time, 160 tiles 0.86 to 1.07 (2048 x 1280 x 3840 NN
+// 319 / 300, NT 291 / 296), 176 tiles 0.95 to 1.17 (380 / 343 TN); 64 tiles of 32
+// x 32 (256 x 256 x 1024) 11 against 6.9 on 16 x 16, 192 of them (256 x 768 x
+// 256) 5.4 against 5.9.
 static int small_tiles(int M, int N) {
   if ((long)((M + 31) / 32) * (N / 32) <= 128) return 1;
-  return (long)((M + 127) / 128) * ((N + 127) / 128) < 192 ? 2 : 0;
+  return (long)((M + 127) / 128) * ((N + 127) / 128) < 160 ? 2 : 0;
 }
 
 template <typename T, int BM, int BN, int WTM, int WTN, bool AK, bool BKc, int EPI>

@@ -190,6 +190,22 @@ def test_gemm_f32_few_tiles(lay, epi):
             assert rel_l2(host(C), full) < 1e-6, (M, N, K)
 
 
+@pytest.mark.parametrize("M,N", [(6784, 384), (6785, 384), (4096, 640)])
+@pytest.mark.parametrize("lay,epi", [(F.FL_GEMM_NT, F.FL_EPI_BIAS), (F.FL_GEMM_NN, F.FL_EPI_STORE),
+                                     (F.FL_GEMM_TN, F.FL_EPI_ACC_F32)])
+def test_gemm_f32_around_the_tile_choice(lay, epi, M, N):
+    """fp32 products of 159 tiles of 128 x 128, which run on 32 x 32 ones, and of
+    162 and 160, which do not.  fp32 sums of K = 64 terms: 1e-6 relative L2."""
+    K = 64
+    M = (M + 7) // 8 * 8 if lay == F.FL_GEMM_TN else M
+    A, B, bias, R, C0, ref, _ = _tiled_case(lay, epi, M, N, K, dt="f32")
+    C = dev(C0, "f32") if epi == F.FL_EPI_ACC_F32 else torch.full((M, N), float("nan"), device="cuda")
+    F.fl_test_gemm(F.FL_F32, lay, epi, dev(A, "f32"), dev(B, "f32"), C, M, N, K, A.shape[1], B.shape[1], N,
+                   bias=dev(bias, "f32"))
+    sync()
+    assert rel_l2(host(C), ref) < 1e-6
+
+
 @pytest.mark.parametrize("lay,epi", [t for t in TILED if t[0] != F.FL_GEMM_TN])
 def test_gemm_rows_in_two_launches(lay, epi):
     """Row counts just past whole rounds of large tiles: the product runs as
