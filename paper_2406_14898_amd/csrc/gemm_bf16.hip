@@ -1084,17 +1084,17 @@ hipError_t launch_pair(const PairPlan& pl, const G2Args& d, const G2Args& w, flo
 }
 
 // Tile heights, slices and whether one launch is the faster form, from a sweep
-// of every choice on MI355X (rows 9 .. 2048; hidden 256 to 4096, FFN 3.25 and 4
+// of every choice on MI355X (rows 9 .. 2048; hidden 256 to 4096, FFN 2.6 to 4
 // times as wide).  The input gradient wants about as many items as there are
 // CUs, each of six stages or more; the weight gradient's items fill in behind.
-// Two launches against one (us): hidden 1280, FFN 3328, 1458 rows FFN-down 51
-// -> 45, FFN-up 50 -> 38, 1024 rows QKV 45 -> 35; hidden 4096 output projection
-// 509 rows 65 -> 55, 1024 rows 104 -> 80; 64 rows FFN-down 140 -> 128.
+// One launch against the products apart (us): hidden 1280, FFN 3328, 1458 rows
+// FFN-down 51 / 61, FFN-up 51 / 67, 1024 rows QKV 50 / 56; hidden 4096 output
+// projection 512 rows 72 / 81, 1024 rows 96 / 109; 64 rows FFN-down 135 / 145.
 // Wide layers of more rows are bound by the matrix cores and by the weight
-// gradient's traffic, where the large tiles of the separate launches win (4096
-// x 16384: 400 rows 199 against 206, 1458 rows 436 against 473) except where
-// their 256-row tiles would be mostly padding (640 rows 291 against 256, 733
-// rows 310 against 278, 820 rows 314 against 310).
+// gradient's traffic, where the larger tiles of the separate launches win
+// (hidden 4096 FFN-up: 340 rows 182 / 194, 384 rows 187 / 200, 448 rows 263 /
+// 215, 640 rows 284 / 260; output projection: 1024 rows 96 / 109, 1200 rows 125 /
+// 114; hidden 3072 output projection: 2048 rows 95 / 107).
 bool plan_pair(const GemmDesc& d, const GemmDesc& w, PairPlan* pl) {
   if (d.tile) {
     *pl = PairPlan{d.tile, d.slices, w.tile};
@@ -1103,13 +1103,14 @@ bool plan_pair(const GemmDesc& d, const GemmDesc& w, PairPlan* pl) {
   const long n64 = (long)((d.M + 63) / 64) * (d.N / 128), n128 = (long)((d.M + 127) / 128) * (d.N / 128);
   const long w128 = (long)((w.M + 127) / 128) * (w.N / 128);
   const int stages = d.K / kBK;
-  pl->tile_d = d.M < 200 || (n64 < 256 && (stages < 32 || n64 >= 200)) ? 64 : 128;
+  // (820 x 2048 x 8192, 128 stages: 208 unsliced 64-row items 122 us, 112 of 128
+  // rows in two slices 95)
+  pl->tile_d = d.M < 200 || (n64 < 256 && (stages < 32 || (n64 >= 200 && stages <= 64))) ? 64 : 128;
   const long n = pl->tile_d == 64 ? n64 : n128;
   pl->slices = (int)std::max(1L, std::min({8L, (long)stages / 6, 256 / n}));
   while (pl->slices > 1 && (!d.part || (size_t)pl->slices * d.M * d.N * 4 > d.part_bytes)) --pl->slices;
   pl->tile_w = (w128 > 512 && d.M < 200) || (w128 < 200 && d.M > 900) ? 64 : 128;
-  if (w128 <= 1024) return d.M <= kColsumDirectRows;
-  return d.M <= 340 || (d.M > 600 && d.M <= 820);
+  return d.M <= (w128 <= 768 ? kColsumDirectRows : w128 <= 1024 ? 1024 : 384);
 }
 
 }  // namespace

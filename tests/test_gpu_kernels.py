@@ -267,6 +267,38 @@ def test_linear_backward_in_one_launch(dt, tile_d, slices, tile_w, gelu):
         assert np.all(np.abs(host(db) - want) <= 1e-6 * (np.abs(y64).sum(0) + np.abs(db0))), (T, n_out, n_in)
 
 
+@pytest.mark.parametrize("n_out,n_in,most", [(2560, 1280, 2048), (4096, 3072, 2048), (4096, 4096, 1024),
+                                             (8192, 4096, 384)])
+def test_linear_backward_row_limits(n_out, n_in, most):
+    """Rows up to which a layer's gradients share a launch: accepted and right
+    at the limit, apart one row past it; 200, 768, 1024 and 2048 weight-gradient
+    tiles of 128 x 128.  Against fp32 products of the same bf16 values: a stored
+    bf16 rounds to 2^-9, fp32 sums of at most 8192 terms stay below 3e-6 of the
+    terms' norm."""
+    g = torch.Generator(device="cuda").manual_seed(n_in)
+    part = torch.empty(64 << 20 >> 2, dtype=torch.float32, device="cuda")
+
+    def draw(*s, std=1.0):
+        return torch.randn(s, generator=g, device="cuda").mul_(std)
+    W = draw(n_out, n_in, std=0.1).bfloat16()
+    for T in (most, most + 1):
+        dy, X = draw(T, n_out).bfloat16(), draw(T, n_in).bfloat16()
+        dX = torch.full((T, n_in), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dW0, db0 = draw(n_out, n_in), draw(n_out)
+        dW, db = dW0.clone(), db0.clone()
+        args = (F.FL_BF16, dy, W, X, None, dX, dW, db, T, n_out, n_in, part)
+        if T > most:
+            with pytest.raises(F.FlglmError) as e:
+                F.fl_test_linear_backward(*args)
+            assert e.value.code == F.FL_ERR_ARG
+            continue
+        F.fl_test_linear_backward(*args)
+        y = dy.float()
+        for got, want, tol in ((dX.float(), y @ W.float(), TOL["bf16"] / 4), (dW, dW0 + y.t() @ X.float(), 3e-6),
+                               (db, db0 + y.sum(0), 3e-6)):
+            assert float((got - want).norm() / want.norm()) < tol
+
+
 @pytest.mark.parametrize("M", [700, 256, 1])
 def test_gemm_gelu_bwd_column_sums(M):
     """The GeLU' input-gradient GEMM also writes, per 256-row block, the
