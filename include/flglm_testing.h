@@ -60,6 +60,13 @@ int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void
                        int64_t ldc2, const void* Z, int64_t ldz, float* part, int64_t part_bytes, int b_rows,
                        float res_scale, float* colsum, int tile, int slices, void* stream);
 
+/* How fl_test_gemm (bf16, no forced tile) runs a product: *count launches (1 or
+ * 2) over its rows in order, parts[3 i] rows of tile height parts[3 i + 1] in
+ * parts[3 i + 2] reduction slices (TN: of the tiles past whole rounds of 256).
+ * colsum: column sums are asked for.  Host only; FL_ERR_ARG for a product that
+ * the LDS-DMA kernel does not take. */
+int fl_test_gemm_plan(int layout, int M, int N, int K, int64_t part_bytes, int colsum, int* parts, int* count);
+
 /* The backward of one linear layer in one launch (few rows): dX[T][in] =
  * dY W (times gelu_tanh'(Z) where Z is given), dW[out][in] (fp32) += dY^T X
  * and, where db is given, db[out] (fp32) += the column sums of dY.  All arrays

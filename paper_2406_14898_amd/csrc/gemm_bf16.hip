@@ -759,11 +759,6 @@ int num_cus() {
   return cached[dev];
 }
 
-// One launch of a product's rows on one tile shape.
-struct GemmPart {
-  int rows, tile, slices;
-};
-
 // Estimated time (us) of an NT or NN product of M rows on 64-, 128-, 192- or
 // 256-row tiles with its reduction in s slices, fitted to a sweep on MI355X (M
 // 16 .. 6000, N and K of hidden 1280 and 4096, every tile and slice count): a
@@ -1155,6 +1150,13 @@ bool gemm_bf16_dma_ok(GemmLayout layout, const GemmDesc& d) {
 bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d) {
   return dt == DT_BF16 && layout == GEMM_NN && epi == EPI_GELU_BWD && Tile256::kBM == kColsumRows &&
          gemm_bf16_dma_ok(layout, d);
+}
+
+int gemm_bf16_plan(GemmLayout layout, const GemmDesc& d, GemmPart (&parts)[2]) {
+  if (layout != GEMM_TN) return plan_rows(d, layout == GEMM_NT, parts);
+  const WgradPlan pl = plan_wgrad(d);
+  parts[0] = GemmPart{d.M, pl.tile, pl.slices};
+  return 1;
 }
 
 bool gemm_epilogue_colsum(const GemmDesc& d) {

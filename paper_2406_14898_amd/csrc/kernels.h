@@ -65,6 +65,13 @@ bool gemm_fuses_colsum(DType dt, GemmLayout layout, int epi, const GemmDesc& d);
 // Whether it does so in the product's own epilogue, without another pass.
 bool gemm_epilogue_colsum(const GemmDesc& d);
 hipError_t gemm_bf16_dma(GemmLayout layout, int epi, const GemmDesc& d, hipStream_t st);
+// How the LDS-DMA kernel runs a product: one or two launches over its rows, on
+// one tile height and number of reduction slices each (weight gradients: one,
+// with the slices of the tiles past whole rounds).  Host only.
+struct GemmPart {
+  int rows, tile, slices;
+};
+int gemm_bf16_plan(GemmLayout layout, const GemmDesc& d, GemmPart (&parts)[2]);
 // The backward of one linear layer with few rows in one launch: the input
 // gradient d (NN, EPI_STORE or EPI_GELU_BWD), the weight gradient w (TN,
 // EPI_ACC_F32; d.A == w.A is the layer's output gradient) and, where bias is

@@ -100,6 +100,28 @@ int fl_test_gemm_tiled(int dtype, int layout, int epi, const void* A, const void
   return herr(gemm((DType)dtype, (GemmLayout)layout, epi, d, (hipStream_t)stream));
 }
 
+int fl_test_gemm_plan(int layout, int M, int N, int K, int64_t part_bytes, int colsum, int* parts, int* count) {
+  if (!parts || !count) return set_error(FL_ERR_NULL, "parts / count is NULL");
+  GemmDesc d;
+  d.M = M; d.N = N; d.K = K;
+  d.lda = layout == FL_GEMM_TN ? M : K; d.ldb = layout == FL_GEMM_NT ? K : N; d.ldc = N;
+  if (layout < 0 || layout > 2 || M < 1 || N < 1 || K < 1 || part_bytes < 0 || !gemm_bf16_dma_ok((GemmLayout)layout, d))
+    return set_error(FL_ERR_ARG, "not a product of the LDS-DMA kernel");
+  // never followed: only whether they are given decides
+  float some = 0.f;
+  d.part = part_bytes > 0 ? &some : nullptr;
+  d.part_bytes = (size_t)part_bytes;
+  d.colsum = colsum ? &some : nullptr;
+  GemmPart p[2];
+  *count = gemm_bf16_plan((GemmLayout)layout, d, p);
+  for (int i = 0; i < *count; ++i) {
+    parts[3 * i] = p[i].rows;
+    parts[3 * i + 1] = p[i].tile;
+    parts[3 * i + 2] = p[i].slices;
+  }
+  return FL_OK;
+}
+
 int fl_test_linear_backward(int dtype, const void* dY, const void* W, const void* X, const void* Z, void* dX,
                             float* dW, float* db, int T, int out, int in, float* part, int64_t part_bytes,
                             int tile_d, int slices, int tile_w, void* stream) {

@@ -43,7 +43,8 @@ EXPORTS = (
     "fl_client_create", "fl_client_destroy", "fl_client_workspace_bytes", "fl_embedding_forward",
     "fl_embedding_backward", "fl_lm_head_forward", "fl_lm_head_backward",
     "fl_stack_profile", "fl_stack_profile_classes", "fl_stack_profile_read", "fl_profile_class_name",
-    "fl_test_gemm", "fl_test_gemm_tiled", "fl_test_linear_backward",
+    "fl_test_gemm", "fl_test_gemm_tiled", "fl_test_gemm_plan",
+    "fl_test_linear_backward",
     "fl_test_layernorm_fwd", "fl_test_layernorm_bwd", "fl_test_layernorm_bwd_fused",
     "fl_test_colsum",
     "fl_test_rope", "fl_test_attention_fwd", "fl_test_attention_bwd", "fl_test_attention_ds_bytes",
@@ -130,6 +131,7 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         "fl_test_gemm_tiled": [ctypes.c_int] * 3 + [vp] * 3 + [ctypes.c_int] * 3 + [i64] * 3 +
                               [vp, vp, i64, vp, i64, vp, i64, vp, i64, ctypes.c_int, ctypes.c_float, vp, ctypes.c_int,
                                ctypes.c_int, vp],
+        "fl_test_gemm_plan": [ctypes.c_int] * 4 + [i64, ctypes.c_int, vp, vp],
         "fl_test_linear_backward": [ctypes.c_int] + [vp] * 7 + [ctypes.c_int] * 3 + [vp, i64] + [ctypes.c_int] * 3 + [vp],
         "fl_test_layernorm_fwd": [ctypes.c_int, vp, vp, vp, vp, vp, vp, ctypes.c_int, ctypes.c_int, ctypes.c_float,
                                   vp],
@@ -421,6 +423,13 @@ def fl_test_gemm(dtype, layout, epi, A, B, C, M, N, K, lda, ldb, ldc, bias=None,
         _check(load().fl_test_gemm_tiled(*args, tile, slices, _stream(stream)))
     else:
         _check(load().fl_test_gemm(*args, _stream(stream)))
+
+
+def fl_test_gemm_plan(layout, M, N, K, part_bytes=64 << 20, colsum=False):
+    """[(rows, tile, slices)] of the launches fl_test_gemm makes for a bf16 product."""
+    parts, n = (ctypes.c_int * 6)(), ctypes.c_int(0)
+    _check(load().fl_test_gemm_plan(layout, M, N, K, part_bytes, int(colsum), parts, ctypes.byref(n)))
+    return [tuple(parts[3 * i:3 * i + 3]) for i in range(n.value)]
 
 
 def fl_test_linear_backward(dtype, dY, W, X, Z, dX, dW, db, T, out, inn, part=None, tile_d=0, slices=1, tile_w=0,

@@ -3,7 +3,9 @@ headers declare, and rejects malformed descriptors with the documented
 error codes before any device work (validation is host-only)."""
 
 import ctypes
+import math
 import os
+import random
 import re
 
 import pytest
@@ -335,3 +337,40 @@ def test_host_tensors_are_refused_before_the_library():
         F._ptr(torch.zeros(4))
     assert e.value.code == F.FL_ERR_ARG
     assert F._ptr(None) is None and F._ptr(4096) == 4096
+
+
+@pytest.mark.parametrize("layout", [F.FL_GEMM_NT, F.FL_GEMM_NN, F.FL_GEMM_TN])
+def test_gemm_plans_cover_the_product(layout):
+    """The launches that the bf16 GEMM's planner chooses (host code): over any
+    shape, scratch and column sums asked for or not, they cover every row once,
+    a first launch ends at a whole tile (at a whole 256-row block where column
+    sums are formed), slices have at least two stages (weight gradients:
+    of the tiles past whole rounds only) and their fp32 sums fit the scratch."""
+    rng = random.Random(layout)
+    two = sliced = 0
+    for _ in range(3000):
+        M = int(math.exp(rng.uniform(0, math.log(60000))))
+        N, K = 256 * rng.randint(1, 64), 64 * int(math.exp(rng.uniform(0, math.log(256))))
+        if layout == F.FL_GEMM_TN:
+            M, K = 256 * rng.randint(1, 64), int(math.exp(rng.uniform(0, math.log(60000))))
+        part = rng.choice((0, 1 << 20, 64 << 20))
+        sums = layout == F.FL_GEMM_NN and rng.random() < 0.5
+        plan = F.fl_test_gemm_plan(layout, M, N, K, part, sums)
+        what = (layout, M, N, K, part, sums, plan)
+        assert 1 <= len(plan) <= 2 and sum(p[0] for p in plan) == M and all(p[0] > 0 for p in plan), what
+        stages = (K + 63) // 64
+        for rows, tile, slices in plan:
+            assert tile in ((64, 128, 256) if layout == F.FL_GEMM_TN else (64, 128, 192, 256)), what
+            assert slices == 1 or 2 * slices <= stages, what
+            need = 4 * rows * N
+            if layout == F.FL_GEMM_TN:
+                rem = (M + 255) // 256 * (N // 256) % 256
+                need = rem * 256 * 256 * 4
+                assert slices == 1 or (tile == 256 and 0 < rem * slices <= 256), what
+            assert slices == 1 or (slices * need <= part and tile != 192), what
+            sliced += slices > 1
+        if len(plan) == 2:
+            assert layout != F.FL_GEMM_TN and plan[1][1] <= 128, what
+            assert plan[0][0] % (256 if sums else plan[0][1]) == 0, what
+            two += 1
+    assert sliced > 100 and (two > 100 or layout == F.FL_GEMM_TN)

@@ -206,32 +206,37 @@ def test_gemm_f32_around_the_tile_choice(lay, epi, M, N):
     assert rel_l2(host(C), ref) < 1e-6
 
 
+@pytest.mark.parametrize("M,N,K,first", [(4097, 4096, 2048, (4096, 256)), (4396, 4096, 2048, (4096, 256)),
+                                          (2422, 7168, 768, (1728, 192)), (7376, 2304, 640, (7168, 128))])
 @pytest.mark.parametrize("lay,epi", [t for t in TILED if t[0] != F.FL_GEMM_TN])
-def test_gemm_rows_in_two_launches(lay, epi):
-    """Row counts just past whole rounds of large tiles: the product runs as
-    two launches (the whole rounds, then the remaining rows on another tile
-    shape), and the second starts in the right row of every operand."""
-    part = torch.empty(64 << 20 >> 2, dtype=torch.float32, device="cuda")
-    N, K = 4096, 128
-    for M in (4096 + 1, 4096 + 300):
-        A, B, bias, R, C0, ref, second = _tiled_case(lay, epi, M, N, K)
-        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-        C2 = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
-        nb = (M + 255) // 256
-        cs = torch.full((nb, N), float("nan"), device="cuda") if epi == F.FL_EPI_GELU_BWD else None
-        F.fl_test_gemm(F.FL_BF16, lay, epi, dev(A, "bf16"), dev(B, "bf16"), C, M, N, K, A.shape[1], B.shape[1], N,
-                       bias=dev(bias, "bf16"), R=dev(R, "bf16"), ldr=N, C2=C2, ldc2=N, Z=dev(R, "bf16"), ldz=N,
-                       part=part, res_scale=1.5, colsum=cs)
-        sync()
-        c = host(C)
-        assert rel_l2(c[:4096], ref[:4096]) < TOL["bf16"] / 4 and rel_l2(c[4096:], ref[4096:]) < TOL["bf16"] / 4
-        if second is not None:
-            c2 = host(C2)
-            assert rel_l2(c2[4096:], second[4096:]) < TOL["bf16"] / 4
-        if cs is not None:
-            for blk in range(nb):
-                rows = c[256 * blk:256 * (blk + 1)]
-                assert np.all(np.abs(host(cs)[blk] - rows.sum(0)) <= 1e-6 * (np.abs(rows).sum(0) + 1e-30)), (M, blk)
+def test_gemm_rows_in_two_launches(lay, epi, M, N, K, first):
+    """Row counts past whole rounds of large tiles: the product runs as two
+    launches (the whole rounds, then the remaining rows on another tile shape,
+    at 4097 rows in slices), and the second starts in the right row of every
+    operand, output and block of column sums.  fp32 sums of K <= 2048 terms stay
+    far below the bf16 rounding of the result."""
+    sums = epi == F.FL_EPI_GELU_BWD and first[1] == 256
+    plan = F.fl_test_gemm_plan(lay, M, N, K, 64 << 20, sums)
+    assert len(plan) == 2 and plan[0] == (*first, 1) and plan[1][1] < first[1] and sum(p[0] for p in plan) == M
+    assert (plan[1][2] > 1) == (M == 4097)
+    part = torch.full((64 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
+    A, B, bias, R, C0, ref, second = _tiled_case(lay, epi, M, N, K)
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    C2 = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    nb = (M + 255) // 256
+    cs = torch.full((nb, N), float("nan"), device="cuda") if sums else None
+    F.fl_test_gemm(F.FL_BF16, lay, epi, dev(A, "bf16"), dev(B, "bf16"), C, M, N, K, A.shape[1], B.shape[1], N,
+                   bias=dev(bias, "bf16"), R=dev(R, "bf16"), ldr=N, C2=C2, ldc2=N, Z=dev(R, "bf16"), ldz=N,
+                   part=part, res_scale=1.5, colsum=cs)
+    sync()
+    c, m = host(C), first[0]
+    for got, want in ((c, ref), (host(C2), second)):
+        if want is not None:
+            assert rel_l2(got[:m], want[:m]) < TOL["bf16"] / 4 and rel_l2(got[m:], want[m:]) < TOL["bf16"] / 4
+    if cs is not None:
+        for blk in range(nb):
+            rows = c[256 * blk:256 * (blk + 1)]
+            assert np.all(np.abs(host(cs)[blk] - rows.sum(0)) <= 1e-6 * (np.abs(rows).sum(0) + 1e-30)), (M, blk)
 
 
 @pytest.mark.parametrize("dt,tile_d,slices,tile_w", [("f32", 0, 1, 0), ("bf16", 0, 1, 0), ("bf16", 64, 1, 64),
