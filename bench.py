@@ -40,27 +40,36 @@ MFMA_CLASSES = ("gemm_nt_bias", "gemm_nt_bias_res", "gemm_nt_bias_gelu", "gemm_t
                 "gemm_nn", "attn_fwd", "attn_bwd", "lm_head_fwd", "lm_head_bwd")
 GEMM_CLASSES = MFMA_CLASSES[:6]   # the block GEMMs
 # Fragments of the kernel names rocprofv3 prints for each launch class of the
-# bf16 path (a class may launch several kernels), and the sources they are
-# built from (a stored counter reading is stale once their code, comments
-# aside, changes).
+# bf16 path: the kernels that start an engine launch, then its later parts.
+# CLASS_SOURCES: what they are built from (a stored counter reading is stale
+# once their code, comments aside, changes).
 CLASS_KERNELS = {
-    # (the epilogue's row-batch template argument follows the epilogue code)
-    "gemm_nt_bias": ("gemm_bf16_kernel<true, true, 1,",),
-    "gemm_nt_bias_res": ("gemm_bf16_kernel<true, true, 2,",),
-    "gemm_nt_bias_gelu": ("gemm_bf16_kernel<true, true, 3,",),
-    "gemm_nn_gelu_bwd": ("gemm_bf16_kernel<true, false, 4,",),
-    "gemm_nn": ("gemm_bf16_kernel<true, false, 0,", "gemm_bf16_kernel<true, false, 6,"),
-    "gemm_tn_acc": ("gemm_bf16_kernel<false, false",),
-    "attn_fwd": ("::fwd_kernel<",),
-    "attn_bwd": ("attn_delta_kernel", "::dkdv_kernel<", "::dq_kernel<", "::dq_ds_kernel<"),
-    "layernorm_fwd": ("ln_fwd_kernel",),
-    "layernorm_bwd": ("ln_bwd_fused_kernel", "ln_bwd_dx_kernel"),
-    "rope_qk": ("rope_qk_kernel",),
-    "colsum": ("colsum_partial_kernel", "colsum_finish_kernel"),
-    "prefix_grad": ("prefix_grad_reduce_kernel",),
-    "adam": ("adam_kernel",),
-    "average": ("average_kernel",),
+    # (layout, layout, epilogue; the tile shape follows.  One product may take
+    # two launches on different tiles, and reduction slices: _classes)
+    "gemm_nt_bias": (("gemm_bf16_kernel<true, true, 1,",), ()),
+    "gemm_nt_bias_res": (("gemm_bf16_kernel<true, true, 2,",), ()),
+    "gemm_nt_bias_gelu": (("gemm_bf16_kernel<true, true, 3,",), ()),
+    "gemm_nn_gelu_bwd": (("gemm_bf16_kernel<true, false, 4,",), ()),
+    "gemm_nn": (("gemm_bf16_kernel<true, false, 0,", "gemm_bf16_kernel<true, false, 6,"), ()),
+    "gemm_tn_acc": (("gemm_bf16_kernel<false, false",), ("gemm_tile_slices_kernel",)),
+    # few rows: a layer's input, weight and bias gradients in one launch (the
+    # engine's launch timing shares it out among their classes)
+    "gemm_pair": (("gemm_pair_kernel<",), ()),
+    "attn_fwd": (("::fwd_kernel<",), ()),
+    "attn_bwd": (("attn_delta_kernel",), ("::dkdv_kernel<", "::dq_kernel<", "::dq_ds_kernel<")),
+    "layernorm_fwd": (("ln_fwd_kernel", "ln_fwd_row_kernel"), ()),
+    "layernorm_bwd": (("ln_bwd_fused_kernel", "ln_bwd_dx_kernel"), ()),
+    "rope_qk": (("rope_qk_kernel",), ()),
+    "colsum": (("colsum_partial_kernel", "colsum_direct_kernel"), ("colsum_finish_kernel",)),
+    "prefix_grad": (("prefix_grad_reduce_kernel",), ()),
+    "adam": (("adam_kernel",), ()),
+    "average": (("average_kernel",), ()),
 }
+# The fp32 sums of a token-major product's reduction slices (epilogue 7) belong
+# to the class whose epilogue the kernel that adds them runs.
+SLICED_KERNELS = {"gemm_bf16_kernel<true, true, 7,": {1: "gemm_nt_bias", 2: "gemm_nt_bias_res", 3: "gemm_nt_bias_gelu"},
+                  "gemm_bf16_kernel<true, false, 7,": {0: "gemm_nn", 4: "gemm_nn_gelu_bwd", 6: "gemm_nn"}}
+SLICE_SUM_KERNEL = "gemm_slices_kernel<"
 CSRC = os.path.join(ROOT, "paper_2406_14898_amd", "csrc")
 CLASS_SOURCES = {"gemm": ("gemm_bf16.hip", "common.h", "kernels.h"),
                  "attn": ("attention_bf16.hip", "attention.hip", "common.h", "kernels.h"),
@@ -222,33 +231,56 @@ def _pmc_dispatches(d: str, counter: str, with_duration: bool = False) -> list:
 
 def _class_of(name: str):
     """(class, starts a launch) of a kernel name, or (None, False).  A class's
-    first pattern starts an engine launch; its other patterns are later parts
-    of the same launch (the attention backward's three kernels, a column sum's
+    starting kernels begin an engine launch; its others are later parts of the
+    same launch (the attention backward's three kernels, a column sum's
     finish)."""
-    for cls, pats in CLASS_KERNELS.items():
-        hit = [p for p in pats if p in name]
-        if hit:
-            return cls, hit[0] == pats[0]
+    for cls, (starts, parts) in CLASS_KERNELS.items():
+        if any(p in name for p in starts):
+            return cls, True
+        if any(p in name for p in parts):
+            return cls, False
     return None, False
+
+
+def _classes(dispatches) -> list:
+    """_class_of every (queue, id, name, ...) dispatch in order.  A product in
+    reduction slices is two dispatches in a row on its queue, the slices and
+    their sum; the sum tells the class (a joint launch's sum follows it)."""
+    out = [_class_of(d[2]) for d in dispatches]
+    open_at = {}  # queue: index of the dispatch right before
+    for i, d in enumerate(dispatches):
+        q, name = d[0], d[2]
+        j = open_at.get(q)
+        if SLICE_SUM_KERNEL in name and j is not None:
+            epi = int(name.split(SLICE_SUM_KERNEL)[1].split(">")[0])
+            for pat, by_epi in SLICED_KERNELS.items():
+                if pat in dispatches[j][2]:
+                    out[j] = out[i] = (by_epi.get(epi), True)
+            if out[j][0] == "gemm_pair":
+                out[i] = ("gemm_pair", False)
+        open_at[q] = i
+    return out
 
 
 def _class_launches(dispatches) -> dict:
     """{class: [engine launches, value total]} from (queue, id, name, value)
     dispatches in order.  A dispatch of the same kernel as the one right
-    before it on its queue belongs to the same engine launch: a GEMM's
-    split-reduction fix-up, or the next piece of a GEMM cut along its
-    reduction.  A class's later kernel continues the launch its first kernel
-    began, unless another class ran in between (a column-sum finish whose
-    partial sums a GEMM epilogue produced is a launch of its own)."""
+    before it on its queue belongs to the same engine launch (the next piece
+    of a GEMM cut along its reduction), and so does a GEMM dispatch of the same
+    class (its rows past whole rounds on another tile, its reduction slices and
+    their sum): the engine never runs two products of one class in a row.  A
+    class's later kernel continues the launch its first kernel began, unless
+    another class ran in between (a column-sum finish whose partial sums a GEMM
+    epilogue produced is a launch of its own)."""
     out = {}
     prev, prev_cls = {}, {}
-    for d in dispatches:
+    for d, (cls, first) in zip(dispatches, _classes(dispatches)):
         q, name, v = d[0], d[2], d[3]
-        cls, first = _class_of(name)
         if cls is not None:
             e = out.setdefault(cls, [0, 0.0])
             e[1] += v
-            if prev.get(q) != name and (first or prev_cls.get(q) != cls):
+            same = prev_cls.get(q) == cls
+            if not (same and cls in GEMM_CLASSES) and prev.get(q) != name and (first or not same):
                 e[0] += 1
         prev[q], prev_cls[q] = name, cls
     return out
@@ -299,8 +331,8 @@ def summarize_mfma(root: str, bench_json: str = "") -> str:
     while the class ran (MfmaUtil, weighted by dispatch duration)."""
     fl = _class_launches(_pmc_dispatches(root, "MfmaFlopsBF16"))
     util = {}
-    for _, _, name, v, dur in _pmc_dispatches(root, "MfmaUtil", with_duration=True):
-        cls, _ = _class_of(name)
+    busy = _pmc_dispatches(root, "MfmaUtil", with_duration=True)
+    for (_, _, _, v, dur), (cls, _) in zip(busy, _classes(busy)):
         if cls is not None:
             e = util.setdefault(cls, [0.0, 0.0])
             e[0] += v * dur

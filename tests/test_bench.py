@@ -94,6 +94,40 @@ def test_finish_after_a_gemm_is_a_column_sum_launch():
     assert r["gemm_nn_gelu_bwd"] == [1, 1.0]
 
 
+def _gemm(layout, epi, tile):
+    return f"void flglm::(anonymous namespace)::gemm_bf16_kernel<{layout}, {epi}, flglm::(anonymous namespace)::Tile<{tile}> >(...)"
+
+
+T256, T192, T64 = "256, 256, 2, 4, 2, 1", "192, 256, 2, 4, 2, 1", "64, 128, 1, 4, 3, 2"
+
+
+def _sum(epi):
+    return f"void flglm::(anonymous namespace)::gemm_slices_kernel<{epi}>(...)"
+
+
+def test_a_product_in_parts_is_one_launch():
+    """Rows past whole rounds on another tile shape, reduction slices and the
+    kernel that adds them belong to the product's engine launch and class."""
+    nt, nn, tn = "true, true", "true, false", "false, false"
+    r = bench._class_launches(_disp(
+        _gemm(nt, 1, T256), _gemm(nt, 1, T64), LN,                    # two tile shapes
+        _gemm(nt, 2, T256), _gemm(nt, 7, T64), _sum(2), LN,           # the rest in slices
+        _gemm(nt, 7, T64), _sum(3), _gemm(nt, 7, T64), _sum(2), LN,   # FFN up, then down, all in slices
+        _gemm(nn, 7, T64), _sum(4), PART, FIN,
+        _gemm(tn, 5, T256), _gemm(tn, 7, T256), "void flglm::(anonymous namespace)::gemm_tile_slices_kernel(...)",
+        _gemm(nn, 7, T64), _sum(0), LN, _gemm(nn, 6, T192)))
+    assert r == {"gemm_nt_bias": [1, 2.0], "gemm_nt_bias_res": [2, 5.0], "gemm_nt_bias_gelu": [1, 2.0],
+                 "gemm_nn_gelu_bwd": [1, 2.0], "gemm_tn_acc": [1, 3.0], "gemm_nn": [2, 3.0], "colsum": [1, 2.0],
+                 "layernorm_fwd": [4, 4.0]}
+
+
+def test_few_row_kernels_have_a_class():
+    pair = "void flglm::(anonymous namespace)::gemm_pair_kernel<7, Tile<64> >(...)"
+    r = bench._class_launches(_disp(pair, _sum(4), pair, _sum(0), "void flglm::ln_fwd_row_kernel<bf16, 512>(...)",
+                                    "void flglm::colsum_direct_kernel<bf16>(...)", GEMM_TN, pair.replace("7,", "0,")))
+    assert r == {"gemm_pair": [3, 5.0], "layernorm_fwd": [1, 1.0], "colsum": [1, 1.0], "gemm_tn_acc": [1, 1.0]}
+
+
 def test_queues_are_grouped_separately():
     d = [("1", 0, GEMM_RES, 1.0), ("2", 1, GEMM_RES, 1.0)]
     assert bench._class_launches(d)["gemm_nt_bias_res"] == [2, 2.0]
