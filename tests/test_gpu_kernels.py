@@ -138,10 +138,9 @@ def test_gemm_tiles_and_slices(lay, epi, tile, slices):
 @pytest.mark.parametrize("slices", [1, 2])
 @pytest.mark.parametrize("lay,epi", [t for t in TILED if t[0] != F.FL_GEMM_TN])
 def test_gemm_64_rows_long_reduction(lay, epi, slices):
-    """64-row tiles of at most one workgroup per CU around the reduction
-    length (48 stages a slice) from which they keep six stages in flight, and
-    with more workgroups than CUs, which never do.  fp32 sums of K <= 6144
-    terms stay far below the bf16 rounding of the result."""
+    """64-row tiles over reductions of 47 to 96 stages, with one workgroup per
+    CU at most and with more.  fp32 sums of K <= 6144 terms stay far below the
+    bf16 rounding of the result."""
     part = torch.full((16 << 20 >> 2,), float("nan"), dtype=torch.float32, device="cuda")
     for M, N, K in ((1, 256, 3008), (65, 256, 3072), (300, 256, 6144), (1200, 2048, 3072)):
         A, B, bias, R, _, ref, second = _tiled_case(lay, epi, M, N, K)
