@@ -317,7 +317,7 @@ struct Work {
   void* ping[2];  // block outputs (inference) / gradient ping-pong (backward)
   void *dz, *dh, *tmp, *dqkv;
   float* delta;
-  float *part, *part2;
+  float* part;
   // fused LayerNorm backward partials of both LayerNorms: gain, shift, output
   // sums, [ln_blocks(T)][H] each
   float* lnp[2][3];
@@ -351,7 +351,6 @@ void carve_work(Carver& cv, const fl_stack* st, const BatchInfo& bi, Work* w) {
   w->delta = (float*)cv.take(sizeof(float) * T * st->d.num_heads);
   const size_t nmax = std::max(F, 3 * H);
   w->part = (float*)cv.take(sizeof(float) * colsum_blocks(bi.T) * nmax);
-  w->part2 = (float*)cv.take(sizeof(float) * colsum_blocks(bi.T) * nmax);
   for (int i = 0; i < 6; ++i) w->lnp[i / 3][i % 3] = (float*)cv.take(sizeof(float) * ln_blocks(bi.T) * H);
   // per-sequence P-tuning v2 prefix gradients, [2][S][L_p][H] fp32
   const size_t np = st->d.num_prefix;

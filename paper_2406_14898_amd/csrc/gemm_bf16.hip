@@ -235,17 +235,18 @@ __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Epilogue of one 256 x 256 tile from the wave accumulators acc[i][j]
-// (wave tile rows 128 (wave & 1) + 16 j, columns 64 (wave >> 1) + 16 i), with
-// the LDS at stg (at least 128 KB, free: every wave is past its operand
-// reads) as staging.  The accumulators of one 128-row half of the tile go to
-// LDS as fp32 ([128][256]); then a lane owns eight consecutive columns
-// (group cg = lane % 32) and the two halves of a wave take alternate rows,
-// so bias, residual, GeLU-input and output rows are read and written
-// contiguously, 16 bytes per lane, two rows per wave instruction (a lane of
-// the matrix core holds 4 columns of 16 different rows, which as direct
-// stores cost more than the reduction for K = 4096; a CU's store
-// instructions cost about the same at 8 and at 16 bytes per lane, so the
+// Epilogue of one BM x BN tile from the wave accumulators acc[i][j] (wave tile
+// rows 16 kWTM (wave % WM) + 16 j, columns 16 kWTN (wave / WM) + 16 i), with
+// the LDS at stg (the S operand slots, free: every wave is past its operand
+// reads) as staging.  The accumulators go to LDS as fp32, [BM / NP][BN] in each
+// of NP passes: the whole tile where it fits, else one wave row at a time (a
+// 256 x 256 tile: two halves of 128 KB).  Then a lane owns eight consecutive
+// columns (group cg = lane % (BN / 8)) and the 512 / BN row groups of a wave
+// take successive rows, so bias, residual, GeLU-input and output rows are read
+// and written contiguously, 16 bytes per lane, two or four rows per wave
+// instruction (a lane of the matrix core holds 4 columns of 16 different rows,
+// which as direct stores cost more than the reduction for K = 4096; a CU's
+// store instructions cost about the same at 8 and at 16 bytes per lane, so the
 // wide form halves the row loop's memory instructions).  Staging puts
 // 16-byte chunk c of row r at c ^ (r & 15) ^ ((c >> 4) & 1): the row writes
 // of the matrix-core lanes and the 16-lane reads of even (or odd) chunks
@@ -557,7 +558,7 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
   // instructions (one A fragment against the four B fragments) is preceded
   // by one or two fragment reads for the next half and, in the second half,
   // by one (each wave) or two (loading waves of the wgrad) of the DMA
-  // instructions for stage kt + 2, so the memory pipes are fed steadily
+  // instructions for stage kt + kStages, so the memory pipes are fed steadily
   // instead of in bursts that stall issue.
   // The last stage is peeled so that every path through the body passes the
   // barrier (the compiler then never waits for next-half reads early).
