@@ -51,8 +51,10 @@ constexpr int kMBlock = 528, kMCol = 8 * kMBlock, kKBlock = 520;
 
 // Output tile of one workgroup: BM x BN by WM x WN waves of (16 kWTM) x
 // (16 kWTN), a ring of S operand slots of a 64-wide reduction stage in LDS.
-template <int BM, int BN, int WM, int WN, int S, int OCC>
+// ACC: row steps of the fp32 accumulator that the epilogue reads together.
+template <int BM, int BN, int WM, int WN, int S, int OCC, int ACC = 8>
 struct Tile {
+  static constexpr int kAccSteps = ACC;
   static constexpr int kBM = BM, kBN = BN, kWM = WM, kWN = WN, kWaves = WM * WN, kThr = 64 * kWaves;
   static constexpr int kStages = S;
   static constexpr int kOcc = OCC;  // workgroups per CU the LDS holds
@@ -65,6 +67,7 @@ struct Tile {
   static_assert(BM / kPasses * BN * 4 <= S * kSlot * 2, "staging");
 };
 using Tile256 = Tile<256, 256, 2, 4, 2, 1>;   // 132 KB
+using Tile256w = Tile<256, 256, 2, 4, 2, 1, 4>;
 using Tile192 = Tile<192, 256, 2, 4, 2, 1>;   // 116 KB
 using Tile128 = Tile<128, 256, 2, 4, 3, 1>;   // 149 KB
 // (six stages for reductions of 48 or more with one workgroup on a CU measured
@@ -97,13 +100,14 @@ struct G2Args {
   // gemm_tile_slices_kernel adds them in slice order and runs the epilogue.
   float* part;
   int slices;
-  // The tiles [tile0, tile0 + tiles) of the work order are this launch's.
-  int tile0, tiles;
   int nb;  // rows of B that exist (see GemmDesc::b_rows)
   float res_scale;
   // EPI_GELU_BWD: per 256-row tile, the column sums of the stored C (fp32
   // [tiles_m][N]), or null
   float* colsum;
+  // Weight gradients: the tiles [tile0, tile0 + tiles) of the work order are
+  // this launch's (the others': all).
+  int tile0, tiles;
 };
 
 
@@ -226,6 +230,12 @@ __device__ __forceinline__ void tile_coords(int tile, int tiles_m, int tiles_n, 
   const int a = first + in_band % size, b = in_band / size;
   tm = kAlongN ? b : a;
   tn = kAlongN ? a : b;
+}
+
+// Output tiles of a product.
+template <class TL>
+__host__ __device__ __forceinline__ int tile_count(const G2Args& a) {
+  return ((a.M + TL::kBM - 1) / TL::kBM) * (a.N / TL::kBN);
 }
 
 // Bare workgroup barrier: a fence would also wait for DMA stages in flight.
@@ -390,14 +400,14 @@ __device__ __forceinline__ void tile_epilogue(const G2Args& p, const f32x4 (&acc
 // 4096 x 4096 output projection than 4), 4 elsewhere (8 measured no faster).
 // The fp32 accumulator: 8 on small tiles, whose short weight gradients wait for
 // these reads (4096 x 16384 over 509 tokens on 128 x 128 tiles: 154 us with 2,
-// 148 with 4, 136 with 8), 4 on 256-row tiles, the best of both ends (with 2, 4
-// and 8: 130528 x 4096 over 733 tokens 1354, 1334, 1323 us; 4096 x 4096 over
-// 900 57.0, 56.8, 59.4; 16384 x 4096 over 1295 259, 265, 278).  Reading it before the reduction instead was slower
-// (88 -> 103 us, 12288 x 4096 over 509 tokens): the first operand stages then
-// queue behind it.
+// 148 with 4, 136 with 8); on 256-row tiles 4, and 8 from eight rounds of tiles
+// on (with 2, 4 and 8: 130528 x 4096 over 733 tokens 1354, 1334, 1323 us; 4096 x
+// 4096 over 900 57.0, 56.8, 59.4; 16384 x 4096 over 1295 259, 265, 278).
+// Reading it before the reduction instead was slower (88 -> 103 us, 12288 x
+// 4096 over 509 tokens): the first operand stages then queue behind it.
 template <int EPI, class TL>
 constexpr int epi_steps() {
-  if (EPI == EPI_ACC_F32) return TL::kBig ? 4 : 8;
+  if (EPI == EPI_ACC_F32) return TL::kAccSteps;
   return EPI == EPI_BIAS_RES || EPI == EPI_RES ? 8 : 4;
 }
 
@@ -418,8 +428,10 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
   // read and written as 4 KB runs (4096 x 16384 x 256 tokens: 116 us against
   // 159 in bands of tile rows).
   constexpr bool kWgrad = !AK && !BKc;
-  const int id = work_id(wi, nwork), slice = id / p.tiles, tile = id - slice * p.tiles;
-  tile_coords<TL::kBig && !kWgrad ? 4 : 8, kWgrad && !TL::kBig>(p.tile0 + tile, tiles_m, tiles_n, tm, tn);
+  const int tiles = kWgrad ? p.tiles : tiles_m * tiles_n;
+  const int id = work_id(wi, nwork), slice = id / tiles, tile = id - slice * tiles;
+  tile_coords<TL::kBig && !kWgrad ? 4 : 8, kWgrad && !TL::kBig>((kWgrad ? p.tile0 : 0) + tile, tiles_m, tiles_n, tm,
+                                                                tn);
   const int kt0 = p.slices == 1 ? 0 : (int)((long)nk * slice / p.slices);
   const int kt1 = p.slices == 1 ? nk : (int)((long)nk * (slice + 1) / p.slices);
   // Per-lane values are rederived in every tile (the opaque copy keeps the
@@ -626,7 +638,7 @@ __device__ __forceinline__ void gemm_item(const G2Args& p, bf16* smem, int wi, i
 template <bool AK, bool BKc, int EPI, class TL>
 __global__ void __launch_bounds__(TL::kThr, TL::kOcc * TL::kWaves / 4) gemm_bf16_kernel(G2Args p) {
   __shared__ __attribute__((aligned(1024))) bf16 smem[TL::kStages * TL::kSlot];  // [slot][A | B]
-  const int nwork = p.tiles * p.slices;
+  const int nwork = (!AK && !BKc ? p.tiles : tile_count<TL>(p)) * p.slices;
   // Persistent where the grid is smaller than the work (256 x 256 tiles: one
   // workgroup per CU); a tile's epilogue stores drain while the next item's
   // first stages load.
@@ -880,11 +892,6 @@ int plan_rows(const GemmDesc& d, bool forward, GemmPart (&parts)[2]) {
   return n;
 }
 
-template <class TL>
-int tile_count(const G2Args& a) {
-  return ((a.M + TL::kBM - 1) / TL::kBM) * (a.N / TL::kBN);
-}
-
 // All tiles of the product, or those that the arguments name.
 template <bool AK, bool BKc, int EPI, class TL>
 hipError_t launch_tile(G2Args a, hipStream_t st) {
@@ -1029,10 +1036,14 @@ hipError_t launch_wgrad(const GemmDesc& d, hipStream_t st) {
   const WgradPlan pl = plan_wgrad(d);
   if (pl.tile == 256) {
     const int tiles = tile_count<Tile256>(a), rem = tiles % 256;
-    if (pl.slices == 1 || rem == 0) return launch_tile<false, false, EPI_ACC_F32, Tile256>(a, st);
+    auto whole = [&](const G2Args& x) {
+      return tiles >= 8 * 256 ? launch_tile<false, false, EPI_ACC_F32, Tile256>(x, st)
+                              : launch_tile<false, false, EPI_ACC_F32, Tile256w>(x, st);
+    };
+    if (pl.slices == 1 || rem == 0) return whole(a);
     G2Args b = a;
     b.tiles = tiles - rem;
-    hipError_t e = b.tiles ? launch_tile<false, false, EPI_ACC_F32, Tile256>(b, st) : hipSuccess;
+    hipError_t e = b.tiles ? whole(b) : hipSuccess;
     if (e != hipSuccess) return e;
     b.tile0 = b.tiles; b.tiles = rem; b.slices = pl.slices;
     if ((e = launch_tile<false, false, EPI_PART, Tile256>(b, st)) != hipSuccess) return e;
