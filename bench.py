@@ -200,7 +200,7 @@ class ClockSampler:
 
 
 def _short_kernel(name: str) -> str:
-    name = name[5:] if name.startswith("void ") else name
+    name = (name[5:] if name.startswith("void ") else name).replace("flglm::(anonymous namespace)::", "")
     depth = 0
     for i, ch in enumerate(name):
         if ch == "<":

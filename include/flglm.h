@@ -152,7 +152,8 @@ typedef struct fl_stack fl_stack;
  * unsupported; FL_ERR_NOMEM if the handle cannot be allocated).  Host-only:
  * no HIP call.  On its first device call the
  * handle creates a few events and a small pinned host staging area used to
- * upload per-call batch descriptors; it never owns device memory. */
+ * upload batch descriptors of more than 256 sequences (fewer travel in kernel
+ * arguments); it never owns device memory. */
 int fl_stack_create(const fl_stack_desc* desc, fl_stack** out);
 /* Releases the handle.  Waits for uploads still in flight. NULL is a no-op. */
 int fl_stack_destroy(fl_stack* stack);
